@@ -11,8 +11,8 @@
 //   network   depth hidden layers of `width` with SiLU, then a linear output;
 //             products on v_mfma_f32_16x16x32_bf16 (bf16 operands rounded to
 //             nearest even from float, float accumulation), float master weights
-//   training  MSE over the real outputs, backpropagation by the same GEMM
-//             kernel with transposed operands, Adam with bias correction
+//   training  MSE over the real outputs, backpropagation with the same products
+//             on transposed operands, Adam with bias correction
 //   fallback  a double-precision blocked Cholesky of -chi_out; if it meets a
 //             pivot that is not positive, the full sum is returned instead
 #include <cmath>
@@ -24,7 +24,7 @@ namespace gw {
 
 constexpr int CL_KPAD = 32;  // input features padded to one MFMA K-step
 constexpr int CL_OPAD = 32;  // outputs padded (the real ones first, the rest kept zero)
-constexpr int CL_RT = 64;    // row tile
+constexpr int CL_RT = 128;   // row tile
 constexpr int CL_NFEAT = 7;
 constexpr int CL_NOUT = 2;
 constexpr uint32_t CL_MAGIC = 0x4C4D5747u;  // "GWML"
@@ -95,124 +95,276 @@ __global__ void k_cl_features(const double* __restrict__ qg, const cpx<double>* 
   }
 }
 
-// ------------------------------------------------------------------ bf16 GEMM
-// C[M][N] = sum_k A(m,k) B(k,n) with A(m,k) = TA ? A[k*lda+m] : A[m*lda+k] and
-// B(k,n) = TB ? B[n*ldb+k] : B[k*ldb+n]; float in, bf16 (RNE) operands, float
-// accumulation.  grid.z splits K into chunks of kchunk (EPI_STORE writes the
-// partial of split z at C + z*cstride).
-enum { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_SILU = 2, EPI_DSILU = 3 };
+// ------------------------------------------------------------------ bf16 GEMMs
+// Every product is v_mfma_f32_16x16x32_bf16 with bf16 (RNE) operands rounded from
+// float as they are loaded and float accumulation.  Only the pre-activations Z_l
+// and the gradients dZ_l cross HBM, in float: H = SiLU(Z) is formed again where
+// it is an operand, and the last hidden layer's dZ (two outputs' worth of
+// products) where it is one.
+//
+// These kernels are bound by HBM: 18 rows x width x 4 bytes per hidden unit and
+// step for depth 3.  One epoch over 301 + 433 + 552 + 797 G vectors (width 256,
+// depth 3, 609 k rows, 11 GB) took 36.1 ms with 64 x 64 tiles staged element by
+// element, a separate column-sum pass and one launch per layer and split sum, and
+// takes 4.35 ms with these kernels, half of it in k_cl_wgrad.
 
-template <bool TA, bool TB, int EPI>
-__global__ void __launch_bounds__(256) k_bgemm(int M, int N, int K, const float* __restrict__ A,
-                                               int lda, const float* __restrict__ B, int ldb,
-                                               float* __restrict__ C, int ldc,
-                                               const float* __restrict__ bias,
-                                               float* __restrict__ Zout,
-                                               const float* __restrict__ Zin, int kchunk,
-                                               long long cstride) {
-  __shared__ __align__(16) unsigned short As[64][BKP];
-  __shared__ __align__(16) unsigned short Bs[64][BKP];
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int kb = blockIdx.z * kchunk, ke = min(K, kb + kchunk);
+typedef float f8 __attribute__((ext_vector_type(8)));
+
+// operand of a row: SiLU(Z), the value itself, or the last hidden layer's dZ
+enum { A_ID = 0, A_SILU = 1, A_OUT = 2 };
+// result: Z = v + bias; the real outputs Y = v + bias; dZ = v SiLU'(Zin)
+enum { EPI_Z = 0, EPI_Y = 1, EPI_DZ = 2 };
+
+__device__ __forceinline__ float bf16_round(float x) { return bf16_to_f(bf16_rn_bits(x)); }
+
+constexpr int CG_KC = 64;         // K chunk of B staged in LDS
+constexpr int CG_KP = CG_KC + 8;  // pitch: 16 rows x 16 bytes cover all 64 banks
+
+// C[rows][N] = epi(op(A)[rows][K] B^T), B bf16 [N][K].  A workgroup takes 128 rows
+// and 16 NB columns (the whole width up to 256, so that A is read once); each of
+// its four wavefronts owns 32 rows and loads their operand fragments straight
+// into registers, eight consecutive k per lane, one chunk ahead.
+template <int NB, int AOP, int EPI>
+__global__ void __launch_bounds__(256, 2) k_cl_gemm(
+    int N, int K, const float* __restrict__ A, int lda, const unsigned short* __restrict__ B,
+    const float* __restrict__ bias, const float* __restrict__ Zin, float* __restrict__ C, int ldc,
+    const float2* __restrict__ dy, const float* __restrict__ wo) {
+  __shared__ __align__(16) unsigned short Bs[16 * NB][CG_KP];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1;
   const int l16 = lane & 15, lk = lane >> 4;
-  f4 acc[2][2];
+  const size_t m0 = (size_t)blockIdx.x * CL_RT + wave * 32;
+  const int n0 = blockIdx.y * 16 * NB;
+  f4 acc[2][NB];
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y) acc[x][y] = (f4){0, 0, 0, 0};
-  for (int k0 = kb; k0 < ke; k0 += 32) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int idx = tid + e * 256;
-      int m, k;
-      if (TA) { k = idx / 64; m = idx % 64; } else { m = idx / 32; k = idx % 32; }
-      float a = 0.f;
-      if (m0 + m < M && k0 + k < ke)
-        a = TA ? A[(size_t)(k0 + k) * lda + m0 + m] : A[(size_t)(m0 + m) * lda + k0 + k];
-      As[m][k] = bf16_rn_bits(a);
-      int n, kk;
-      if (TB) { n = idx / 32; kk = idx % 32; } else { kk = idx / 64; n = idx % 64; }
-      float b = 0.f;
-      if (n0 + n < N && k0 + kk < ke)
-        b = TB ? B[(size_t)(n0 + n) * ldb + k0 + kk] : B[(size_t)(k0 + kk) * ldb + n0 + n];
-      Bs[n][kk] = bf16_rn_bits(b);
-    }
-    __syncthreads();
-    bf8 a[2], b[2];
+    for (int y = 0; y < NB; ++y) acc[x][y] = (f4){0, 0, 0, 0};
+  float2 g[2];
+  if (AOP == A_OUT) {
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
-      a[x] = *reinterpret_cast<const bf8*>(&As[wr * 32 + x * 16 + l16][lk * 8]);
-      b[x] = *reinterpret_cast<const bf8*>(&Bs[wc * 32 + x * 16 + l16][lk * 8]);
+      g[x] = dy[m0 + x * 16 + l16];
+      g[x].x = bf16_round(g[x].x);
+      g[x].y = bf16_round(g[x].y);
     }
-    __syncthreads();
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int y = 0; y < 2; ++y)
-        acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], b[y], acc[x][y], 0, 0, 0);
   }
-  float* Cz = C + (size_t)blockIdx.z * cstride;
+  f8 a[2][2];
+  auto fetch = [&](int kc) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      if (kc + s * 32 < K) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+          a[s][x] = *reinterpret_cast<const f8*>(A + (m0 + x * 16 + l16) * lda + kc + s * 32 +
+                                                 lk * 8);
+      }
+  };
+  fetch(0);
+  for (int kc = 0; kc < K; kc += CG_KC) {
+    const int kl = min(CG_KC, K - kc), q8 = kl >> 3;  // 32 or 64: 4 or 8 chunks of 8 per row
+    const int sh = q8 == 8 ? 3 : 2;
+    if (kc) __syncthreads();
+    for (int e = tid; e < 16 * NB * q8; e += 256) {
+      const int n = e >> sh, k = (e & (q8 - 1)) * 8;
+      *reinterpret_cast<uint4*>(&Bs[n][k]) =
+          *reinterpret_cast<const uint4*>(B + (size_t)(n0 + n) * K + kc + k);
+    }
+    bf8 af[2][2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      if (s * 32 < kl) {
+        f8 w0, w1;
+        if (AOP == A_OUT) {
+          w0 = *reinterpret_cast<const f8*>(wo + kc + s * 32 + lk * 8);
+          w1 = *reinterpret_cast<const f8*>(wo + K + kc + s * 32 + lk * 8);
+        }
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          f8 v = a[s][x];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            if (AOP == A_SILU) v[i] = silu_f(v[i]);
+            if (AOP == A_OUT) v[i] = (g[x].x * w0[i] + g[x].y * w1[i]) * dsilu_f(v[i]);
+          }
+          af[s][x] = __builtin_convertvector(v, bf8);
+        }
+      }
+    __syncthreads();
+    if (kc + CG_KC < K) fetch(kc + CG_KC);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      if (s * 32 < kl) {
+#pragma unroll
+        for (int y = 0; y < NB; ++y) {
+          const bf8 b = *reinterpret_cast<const bf8*>(&Bs[y * 16 + l16][s * 32 + lk * 8]);
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[s][x], b, acc[x][y], 0, 0, 0);
+        }
+      }
+  }
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+    for (int y = 0; y < NB; ++y) {
+      const int j = n0 + y * 16 + l16;
+      if (EPI == EPI_Y && j >= CL_NOUT) continue;
+      const size_t o = (m0 + x * 16 + lk * 4) * ldc + j;
+      float z[4];
+      if (EPI == EPI_DZ) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = m0 + wr * 32 + x * 16 + lk * 4 + r;
-        const int j = n0 + wc * 32 + y * 16 + l16;
-        if (i >= M || j >= N) continue;
-        const size_t o = (size_t)i * ldc + j;
-        const float v = acc[x][y][r];
-        if (EPI == EPI_STORE) Cz[o] = v;
-        else if (EPI == EPI_BIAS) C[o] = v + bias[j];
-        else if (EPI == EPI_BIAS_SILU) {
-          const float z = v + bias[j];
-          Zout[o] = z;
-          C[o] = silu_f(z);
-        } else {
-          C[o] = v * dsilu_f(Zin[o]);
-        }
+        for (int r = 0; r < 4; ++r) z[r] = Zin[o + (size_t)r * ldc];
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        C[o + (size_t)r * ldc] = EPI == EPI_DZ ? acc[x][y][r] * dsilu_f(z[r])
+                                               : acc[x][y][r] + bias[j];
+    }
+}
+
+// bf16 copies of the weights for the products: wb [out][in] as stored, wt its
+// transpose [in][out]; wo the two real output rows, rounded, in float.
+constexpr int CL_MAXL = 9;
+struct ClShape {
+  int layers;
+  int din[CL_MAXL], dout[CL_MAXL];
+  unsigned woff[CL_MAXL];
+};
+__global__ void k_cl_pack(const float* __restrict__ p, ClShape sh, unsigned short* __restrict__ wb,
+                          unsigned short* __restrict__ wt, float* __restrict__ wo) {
+  const int l = blockIdx.y, din = sh.din[l], dout = sh.dout[l];
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= din * dout) return;
+  const unsigned short h = bf16_rn_bits(p[sh.woff[l] + i]);
+  const int o = i / din, k = i - o * din;
+  wb[sh.woff[l] + i] = h;
+  wt[sh.woff[l] + (unsigned)k * dout + o] = h;
+  if (l == sh.layers - 1 && o < CL_NOUT) wo[o * din + k] = bf16_to_f(h);
+}
+
+// Weight and bias gradients of every layer in one launch: dW_l = dZ_l^T H_(l-1)
+// over a split of the rows, 128 x 128 outputs per workgroup.  The contraction runs
+// over rows, so 32 rows of the 256 operand columns pass through LDS transposed:
+// one column per thread, its 32 loads coalesced across the wavefront and in
+// flight while the previous slab is multiplied.  The thread of a dZ column also
+// sums it for the bias.  The tiles of one split follow one another on one XCD,
+// where the columns they share stay in L2.
+constexpr int WG_T = 128, WG_P = 40;
+struct ClWgLayer {
+  const float *dz, *h;   // dmode A_ID: dZ, A_OUT: Z of the last hidden layer, A_SILU: dY (outputs)
+  int dout, din, dmode, hmode, tn, tile0;
+  unsigned woff, boff;
+};
+struct ClWg {
+  int layers, tiles;
+  ClWgLayer l[CL_MAXL];
+};
+__global__ void __launch_bounds__(256, 2) k_cl_wgrad(ClWg W, long long rows, int rchunk,
+                                                     const float2* __restrict__ dy,
+                                                     const float* __restrict__ wo, size_t count,
+                                                     float* __restrict__ part) {
+  __shared__ __align__(16) unsigned short S[2][2 * WG_T][WG_P];
+  const int xcd = blockIdx.x % kXcd, idx = blockIdx.x / kXcd;
+  const int tile = idx % W.tiles, split = (idx / W.tiles) * kXcd + xcd;
+  int li = 0;
+  while (li + 1 < W.layers && tile >= W.l[li + 1].tile0) ++li;
+  const ClWgLayer L = W.l[li];
+  const int tm = (tile - L.tile0) / L.tn, tn = (tile - L.tile0) % L.tn;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, lk = lane >> 4, wr = wave >> 1, wc = wave & 1;
+  const bool isd = tid < WG_T;
+  const int col = isd ? tm * WG_T + tid : tn * WG_T + tid - WG_T;
+  const int mode = isd ? L.dmode : L.hmode;
+  const bool outs = isd && L.dmode == A_SILU;  // the output layer's dY columns
+  const bool live = outs ? col < CL_NOUT : col < (isd ? L.dout : L.din);
+  const int ld = outs ? CL_NOUT : isd ? L.dout : L.din;
+  const float* src = (outs ? reinterpret_cast<const float*>(dy) : isd ? L.dz : L.h) +
+                     (live ? col : 0);
+  const long long r0 = (long long)split * rchunk, r1 = min(rows, r0 + rchunk);
+  float w0 = 0.f, w1 = 0.f;
+  if (isd && L.dmode == A_OUT && live) { w0 = wo[col]; w1 = wo[L.dout + col]; }
+  f4 acc[4][4];
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int y = 0; y < 4; ++y) acc[x][y] = (f4){0, 0, 0, 0};
+  float csum = 0.f;
+  float v[32];
+  auto fetch = [&](long long r) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i) v[i] = src[(size_t)(r + i) * ld];
+  };
+  const bool work = tm * WG_T + wr * 64 < L.dout && tn * WG_T + wc * 64 < L.din;
+  if (r0 < r1) fetch(r0);
+  int buf = 0;
+  for (long long r = r0; r < r1; r += 32, buf ^= 1) {
+    if (mode == A_SILU && !outs) {
+#pragma unroll
+      for (int i = 0; i < 32; ++i) v[i] = silu_f(v[i]);
+    } else if (mode == A_OUT) {
+#pragma unroll
+      for (int i = 0; i < 32; ++i) {
+        const float2 g = dy[r + i];
+        v[i] = (bf16_round(g.x) * w0 + bf16_round(g.y) * w1) * dsilu_f(v[i]);
+      }
+    }
+    if (!live) {
+#pragma unroll
+      for (int i = 0; i < 32; ++i) v[i] = 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f8 t;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        t[k] = v[8 * i + k];
+        csum += t[k];
+      }
+      *reinterpret_cast<bf8*>(&S[buf][tid][8 * i]) = __builtin_convertvector(t, bf8);
+    }
+    __syncthreads();
+    if (r + 32 < r1) fetch(r + 32);
+    if (work) {
+      bf8 a[4], b[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        a[x] = *reinterpret_cast<const bf8*>(&S[buf][wr * 64 + x * 16 + l16][lk * 8]);
+        b[x] = *reinterpret_cast<const bf8*>(&S[buf][WG_T + wc * 64 + x * 16 + l16][lk * 8]);
+      }
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+          acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], b[y], acc[x][y], 0, 0, 0);
+    }
+  }
+  float* out = part + (size_t)split * count;
+  if (isd && tn == 0 && col < L.dout) out[L.boff + col] = csum;
+  if (!work) return;
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int y = 0; y < 4; ++y)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = tm * WG_T + wr * 64 + x * 16 + lk * 4 + q;
+        const int j = tn * WG_T + wc * 64 + y * 16 + l16;
+        if (i < L.dout && j < L.din) out[L.woff + (size_t)i * L.din + j] = acc[x][y][q];
       }
 }
 
-// sum of `splits` partials of length n
-__global__ void k_sum_splits(const float* __restrict__ part, int splits, size_t n,
-                             float* __restrict__ out) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float s = 0.f;
-  for (int z = 0; z < splits; ++z) s += part[(size_t)z * n + i];
-  out[i] = s;
-}
-
-// column sums of X[rows][cols] in row chunks: part[chunk][col]
-__global__ void k_colsum(const float* __restrict__ X, long long rows, int cols, long long rchunk,
-                         float* __restrict__ part) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
-  const long long r0 = (long long)blockIdx.y * rchunk, r1 = min(rows, r0 + rchunk);
-  float s = 0.f;
-  for (long long r = r0; r < r1; ++r) s += X[r * cols + c];
-  part[(size_t)blockIdx.y * cols + c] = s;
-}
-
-// dY = 2 (Y - T) / (n nout) on the real outputs; per-block partial sums of (Y-T)^2
+// dY = 2 (Y - T) / (n nout); per-block partial sums of (Y-T)^2
 __global__ void k_cl_dy(const float* __restrict__ Y, const float* __restrict__ T, long long n,
                         long long npad, float* __restrict__ dY, double* __restrict__ part) {
   __shared__ double red[256];
   const long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   double s = 0.0;
   if (r < npad) {
-    for (int o = 0; o < CL_OPAD; ++o) dY[r * CL_OPAD + o] = 0.f;
-    if (r < n) {
-      const double scale = 2.0 / ((double)n * CL_NOUT);
-      for (int o = 0; o < CL_NOUT; ++o) {
-        const float d = Y[r * CL_OPAD + o] - T[r * 2 + o];
-        dY[r * CL_OPAD + o] = (float)(scale * d);
-        s += (double)d * d;
-      }
+    const double scale = 2.0 / ((double)n * CL_NOUT);
+    for (int o = 0; o < CL_NOUT; ++o) {
+      const float d = r < n ? Y[r * CL_NOUT + o] - T[r * CL_NOUT + o] : 0.f;
+      dY[r * CL_NOUT + o] = (float)(scale * d);
+      s += (double)d * d;
     }
   }
   red[threadIdx.x] = s;
@@ -237,12 +389,15 @@ __global__ void k_sum_f64(const double* __restrict__ part, int n, double* __rest
   if (threadIdx.x == 0) out[0] = red[0];
 }
 
-__global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, size_t n, float lr, float b1, float b2, float eps,
-                       float bc1, float bc2) {
+// Adam on the gradient summed over the row splits in their order
+__global__ void k_adam(float* __restrict__ p, const float* __restrict__ part, int splits,
+                       float* __restrict__ m, float* __restrict__ v, size_t n, float lr, float b1,
+                       float b2, float eps, float bc1, float bc2) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const float gi = g[i];
+  float gi = 0.f;
+#pragma unroll 8
+  for (int z = 0; z < splits; ++z) gi += part[(size_t)z * n + i];
   const float mi = b1 * m[i] + (1.f - b1) * gi;
   const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
   m[i] = mi;
@@ -259,7 +414,7 @@ __global__ void k_cl_apply(const cpx<double>* __restrict__ chi, const float* __r
   int i, j;
   tri_rc(r, N, &i, &j);
   const double s = sc[0];
-  const double yr = s * (double)Y[r * CL_OPAD], yi = s * (double)Y[r * CL_OPAD + 1];
+  const double yr = s * (double)Y[r * CL_NOUT], yi = s * (double)Y[r * CL_NOUT + 1];
   const cpx<double> c = chi[(size_t)i * N + j];
   if (i == j) {
     out[(size_t)i * N + i] = mk(c.x + yr, c.y);
@@ -371,7 +526,7 @@ struct gw_mlp {
   std::vector<int> din, dout;          // per linear layer (padded)
   std::vector<size_t> woff, boff;      // offsets (floats) into the flat parameter arrays
   size_t count = 0;
-  float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
+  float *p = nullptr, *m = nullptr, *v = nullptr;
   long long step = 0;
   bool ready = false;                  // trained or loaded
   double tol = 1e-4;                   // INFER with chi0_full: largest accepted rel_F
@@ -394,60 +549,55 @@ static uint64_t splitmix64(uint64_t& s) {
   return z ^ (z >> 31);
 }
 
-template <bool TA, bool TB, int EPI>
-static gw_status bgemm(gw_ctx* c, int M, int N, int K, const float* A, int lda, const float* B,
-                       int ldb, float* C, int ldc, const float* bias, float* Zout,
-                       const float* Zin, int splits, long long cstride, const char* name) {
-  const int kchunk = ((K + splits - 1) / splits + 31) / 32 * 32;
-  dim3 g((N + 63) / 64, (M + 63) / 64, splits);
-  ProfScope ps(c, name);
-  hipLaunchKernelGGL((k_bgemm<TA, TB, EPI>), g, dim3(256), 0, c->stream, M, N, K, A, lda, B, ldb,
-                     C, ldc, bias, Zout, Zin, kchunk, cstride);
-  GW_CHECK_LAUNCH(c, "k_bgemm");
-  return GW_OK;
-}
-
-// activation layout (floats): X[npad][KPAD]; Z_l, H_l [npad][width] for l < depth;
-// Y, dY [npad][OPAD]; dZa, dZb [npad][width]; T [npad][2]; split partials; loss partials
+// activation layout: X[npad][KPAD]; Z_l [npad][width] for l < depth (inference keeps
+// two of them in turn); dZ_l [npad][width] for l < depth - 1 (training); Y, dY, T
+// [npad][2]; gradient partials [splits][count]; bf16 weights; loss partials
 struct ClBufs {
-  float *X, *Y, *dY, *dZa, *dZb, *T, *part, *bpart;
-  std::vector<float*> Z, H;
+  float *X, *Y, *dY, *T, *part, *wo;
+  unsigned short *wb, *wt;
+  std::vector<float*> Z, dZ;
   double *lpart, *loss, *scale, *rpart, *rsum;
   cpx<double>* chol;
   cpx<double>* R;
   cpx<double>* Lw;
 };
 
-static constexpr int kSplits = 32;
-static constexpr int kRowChunks = 64;
+// Row splits of the weight gradients: a multiple of the XCDs.  64 splits of the 12
+// tiles of a 256-wide, 3-deep network are 768 workgroups, and their partials
+// (35 MB) stay below a tenth of the operands' bytes from 60 k rows on.  Larger
+// networks have more tiles and take fewer splits: the partials stay within 256 MB
+// until the smallest number of splits is reached.
+static int cl_splits(size_t count) {
+  return (int)std::max<size_t>(kXcd, std::min<size_t>(64, ((64u << 20) / count) / kXcd * kXcd));
+}
 static constexpr int kRelBlocks = 256;  // workgroups of the fixed-order rel_F reduction
 
-static gw_status cl_buffers(gw_mlp* net, int N, long long npad, ClBufs* b) {
+static gw_status cl_buffers(gw_mlp* net, int N, long long npad, bool train, ClBufs* b) {
   gw_ctx* c = net->ctx;
   const size_t w = net->width;
   std::vector<std::pair<void**, size_t>> parts;
+  auto add = [&](auto** p, size_t bytes) { parts.push_back({reinterpret_cast<void**>(p), bytes}); };
+  const int nz = train ? net->depth : std::min(net->depth, 2), nd = train ? net->depth - 1 : 0;
   b->Z.assign(net->depth, nullptr);
-  b->H.assign(net->depth, nullptr);
-  parts.push_back({reinterpret_cast<void**>(&b->X), (size_t)npad * CL_KPAD * 4});
-  for (int l = 0; l < net->depth; ++l) {
-    parts.push_back({reinterpret_cast<void**>(&b->Z[l]), (size_t)npad * w * 4});
-    parts.push_back({reinterpret_cast<void**>(&b->H[l]), (size_t)npad * w * 4});
-  }
-  parts.push_back({reinterpret_cast<void**>(&b->Y), (size_t)npad * CL_OPAD * 4});
-  parts.push_back({reinterpret_cast<void**>(&b->dY), (size_t)npad * CL_OPAD * 4});
-  parts.push_back({reinterpret_cast<void**>(&b->dZa), (size_t)npad * w * 4});
-  parts.push_back({reinterpret_cast<void**>(&b->dZb), (size_t)npad * w * 4});
-  parts.push_back({reinterpret_cast<void**>(&b->T), (size_t)npad * 2 * 4});
-  parts.push_back({reinterpret_cast<void**>(&b->part), (size_t)kSplits * w * w * 4});
-  parts.push_back({reinterpret_cast<void**>(&b->bpart), (size_t)kRowChunks * w * 4});
-  parts.push_back({reinterpret_cast<void**>(&b->lpart), (size_t)((npad + 255) / 256) * 8});
-  parts.push_back({reinterpret_cast<void**>(&b->loss), 8});
-  parts.push_back({reinterpret_cast<void**>(&b->scale), 8});
-  parts.push_back({reinterpret_cast<void**>(&b->rpart), 2 * kRelBlocks * 8});
-  parts.push_back({reinterpret_cast<void**>(&b->rsum), 2 * 8});
-  parts.push_back({reinterpret_cast<void**>(&b->chol), (size_t)N * N * 16});
-  parts.push_back({reinterpret_cast<void**>(&b->R), (size_t)CB * N * 16});
-  parts.push_back({reinterpret_cast<void**>(&b->Lw), (size_t)CB * CB * 16});
+  b->dZ.assign(net->depth, nullptr);
+  add(&b->X, (size_t)npad * CL_KPAD * 4);
+  for (int l = 0; l < nz; ++l) add(&b->Z[l], (size_t)npad * w * 4);
+  for (int l = 0; l < nd; ++l) add(&b->dZ[l], (size_t)npad * w * 4);
+  add(&b->Y, (size_t)npad * CL_NOUT * 4);
+  add(&b->dY, (size_t)npad * CL_NOUT * 4);
+  add(&b->T, (size_t)npad * CL_NOUT * 4);
+  add(&b->part, train ? (size_t)cl_splits(net->count) * net->count * 4 : 0);
+  add(&b->wo, CL_NOUT * w * 4);
+  add(&b->wb, net->count * 2);
+  add(&b->wt, net->count * 2);
+  add(&b->lpart, (size_t)((npad + 255) / 256) * 8);
+  add(&b->loss, 8);
+  add(&b->scale, 8);
+  add(&b->rpart, 2 * kRelBlocks * 8);
+  add(&b->rsum, 2 * 8);
+  add(&b->chol, train ? 0 : (size_t)N * N * 16);
+  add(&b->R, train ? 0 : (size_t)CB * N * 16);
+  add(&b->Lw, (size_t)CB * CB * 16);
   size_t total = 0;
   for (auto& p : parts) total += align_up(p.second);
   if (total > net->act_cap) {
@@ -468,68 +618,107 @@ static gw_status cl_buffers(gw_mlp* net, int N, long long npad, ClBufs* b) {
     *p.first = net->act + off;
     off += align_up(p.second);
   }
+  for (int l = nz; l < net->depth; ++l) b->Z[l] = b->Z[l % nz];
+  return GW_OK;
+}
+
+// one product over all rows; the column tile is the largest of 256, 128, 64 that
+// divides the width
+template <int AOP, int EPI>
+static gw_status cl_gemm(gw_ctx* c, long long npad, int N, int K, const float* A,
+                         const unsigned short* B, const float* bias, const float* Zin, float* C,
+                         const float* dy, const float* wo, const char* name) {
+  const unsigned gx = (unsigned)(npad / CL_RT);
+  const float2* g = reinterpret_cast<const float2*>(dy);
+  ProfScope ps(c, name);
+  if constexpr (EPI == EPI_Y) {
+    hipLaunchKernelGGL((k_cl_gemm<1, AOP, EPI>), dim3(gx, 1), dim3(256), 0, c->stream, N, K, A, K,
+                       B, bias, Zin, C, CL_NOUT, g, wo);
+  } else if (N % 256 == 0) {
+    hipLaunchKernelGGL((k_cl_gemm<16, AOP, EPI>), dim3(gx, N / 256), dim3(256), 0, c->stream, N, K,
+                       A, K, B, bias, Zin, C, N, g, wo);
+  } else if (N % 128 == 0) {
+    hipLaunchKernelGGL((k_cl_gemm<8, AOP, EPI>), dim3(gx, N / 128), dim3(256), 0, c->stream, N, K,
+                       A, K, B, bias, Zin, C, N, g, wo);
+  } else {
+    hipLaunchKernelGGL((k_cl_gemm<4, AOP, EPI>), dim3(gx, N / 64), dim3(256), 0, c->stream, N, K, A,
+                       K, B, bias, Zin, C, N, g, wo);
+  }
+  GW_CHECK_LAUNCH(c, "k_cl_gemm");
   return GW_OK;
 }
 
 static gw_status cl_forward(gw_mlp* net, long long npad, ClBufs& b) {
   gw_ctx* c = net->ctx;
-  gw_status st;
-  const float* h = b.X;
-  int ld = CL_KPAD;
-  for (int l = 0; l < net->depth; ++l) {
-    st = bgemm<false, true, EPI_BIAS_SILU>(c, (int)npad, net->dout[l], net->din[l], h, ld,
-                                          net->p + net->woff[l], net->din[l], b.H[l],
-                                          net->dout[l], net->p + net->boff[l], b.Z[l], nullptr, 1,
-                                          0, "closure_fwd");
-    if (st != GW_OK) return st;
-    h = b.H[l];
-    ld = net->dout[l];
-  }
   const int L = net->depth;
-  return bgemm<false, true, EPI_BIAS>(c, (int)npad, net->dout[L], net->din[L], h, ld,
-                                      net->p + net->woff[L], net->din[L], b.Y, CL_OPAD,
-                                      net->p + net->boff[L], nullptr, nullptr, 1, 0, "closure_fwd");
+  ClShape sh{};
+  sh.layers = L + 1;
+  int most = 0;
+  for (int l = 0; l <= L; ++l) {
+    sh.din[l] = net->din[l];
+    sh.dout[l] = net->dout[l];
+    sh.woff[l] = (unsigned)net->woff[l];
+    most = std::max(most, net->din[l] * net->dout[l]);
+  }
+  {
+    ProfScope ps(c, "closure_pack");
+    hipLaunchKernelGGL(k_cl_pack, dim3((most + 255) / 256, L + 1), dim3(256), 0, c->stream, net->p,
+                       sh, b.wb, b.wt, b.wo);
+    GW_CHECK_LAUNCH(c, "k_cl_pack");
+  }
+  gw_status st = cl_gemm<A_ID, EPI_Z>(c, npad, net->dout[0], net->din[0], b.X, b.wb + net->woff[0],
+                                      net->p + net->boff[0], nullptr, b.Z[0], nullptr, nullptr,
+                                      "closure_fwd");
+  for (int l = 1; l < L && st == GW_OK; ++l)
+    st = cl_gemm<A_SILU, EPI_Z>(c, npad, net->dout[l], net->din[l], b.Z[l - 1],
+                                b.wb + net->woff[l], net->p + net->boff[l], nullptr, b.Z[l],
+                                nullptr, nullptr, "closure_fwd");
+  if (st != GW_OK) return st;
+  return cl_gemm<A_SILU, EPI_Y>(c, npad, net->dout[L], net->din[L], b.Z[L - 1],
+                                b.wb + net->woff[L], net->p + net->boff[L], nullptr, b.Y, nullptr,
+                                nullptr, "closure_fwd");
 }
 
-// gradients of the loss already expressed in dY into net->g
+// gradients of the loss already expressed in dY, as row-split partials in b.part
 static gw_status cl_backward(gw_mlp* net, long long npad, ClBufs& b) {
   gw_ctx* c = net->ctx;
-  gw_status st;
+  gw_status st = GW_OK;
   const int L = net->depth;
-  float* dz = b.dY;        // gradient w.r.t. the current layer's output (pre-activation)
-  int ldz = CL_OPAD;
-  for (int l = L; l >= 0; --l) {
-    const int din = net->din[l], dout = net->dout[l];
-    const float* hin = l == 0 ? b.X : b.H[l - 1];
-    // dW_l = dz^T hin  (split over rows)
-    st = bgemm<true, false, EPI_STORE>(c, dout, din, (int)npad, dz, ldz, hin, din, b.part, din,
-                                       nullptr, nullptr, nullptr, kSplits,
-                                       (long long)dout * din, "closure_wgrad");
+  // d(pre-activation of layer l-1) = (dZ_l W_l) SiLU'(Z_(l-1)); dZ of layer L-1 is
+  // formed from dY where it is needed
+  for (int l = L - 1; l >= 1; --l) {
+    if (l == L - 1)
+      st = cl_gemm<A_OUT, EPI_DZ>(c, npad, net->din[l], net->dout[l], b.Z[l], b.wt + net->woff[l],
+                                  nullptr, b.Z[l - 1], b.dZ[l - 1], b.dY, b.wo, "closure_bwd");
+    else
+      st = cl_gemm<A_ID, EPI_DZ>(c, npad, net->din[l], net->dout[l], b.dZ[l], b.wt + net->woff[l],
+                                 nullptr, b.Z[l - 1], b.dZ[l - 1], nullptr, nullptr,
+                                 "closure_bwd");
     if (st != GW_OK) return st;
-    {
-      ProfScope ps(c, "closure_reduce");
-      const size_t n = (size_t)dout * din;
-      hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream,
-                         b.part, kSplits, n, net->g + net->woff[l]);
-      GW_CHECK_LAUNCH(c, "k_sum_splits");
-      const long long rchunk = (npad + kRowChunks - 1) / kRowChunks;
-      hipLaunchKernelGGL(k_colsum, dim3((dout + 255) / 256, kRowChunks), dim3(256), 0, c->stream,
-                         dz, npad, dout, rchunk, b.bpart);
-      GW_CHECK_LAUNCH(c, "k_colsum");
-      hipLaunchKernelGGL(k_sum_splits, dim3((dout + 255) / 256), dim3(256), 0, c->stream, b.bpart,
-                         kRowChunks, (size_t)dout, net->g + net->boff[l]);
-      GW_CHECK_LAUNCH(c, "k_sum_splits");
-    }
-    if (l == 0) break;
-    // d(pre-activation of layer l-1) = (dz W_l) * SiLU'(Z_{l-1})
-    float* nd = (dz == b.dZa) ? b.dZb : b.dZa;
-    st = bgemm<false, false, EPI_DSILU>(c, (int)npad, din, dout, dz, ldz, net->p + net->woff[l],
-                                        din, nd, din, nullptr, nullptr, b.Z[l - 1], 1, 0,
-                                        "closure_bwd");
-    if (st != GW_OK) return st;
-    dz = nd;
-    ldz = din;
   }
+  ClWg W{};
+  W.layers = L + 1;
+  for (int l = 0; l <= L; ++l) {
+    ClWgLayer& y = W.l[l];
+    y.dout = net->dout[l];
+    y.din = net->din[l];
+    y.dmode = l == L ? A_SILU : l == L - 1 ? A_OUT : A_ID;
+    y.hmode = l == 0 ? A_ID : A_SILU;
+    y.dz = l == L ? b.dY : l == L - 1 ? b.Z[l] : b.dZ[l];
+    y.h = l == 0 ? b.X : b.Z[l - 1];
+    y.woff = (unsigned)net->woff[l];
+    y.boff = (unsigned)net->boff[l];
+    y.tn = (y.din + WG_T - 1) / WG_T;
+    y.tile0 = W.tiles;
+    W.tiles += y.tn * ((y.dout + WG_T - 1) / WG_T);
+  }
+  const int splits = cl_splits(net->count);
+  const long long rchunk = ((npad + splits - 1) / splits + 31) / 32 * 32;
+  ProfScope ps(c, "closure_wgrad");
+  hipLaunchKernelGGL(k_cl_wgrad, dim3((unsigned)(W.tiles * splits)), dim3(256), 0, c->stream, W,
+                     npad, (int)rchunk, reinterpret_cast<const float2*>(b.dY), b.wo, net->count,
+                     b.part);
+  GW_CHECK_LAUNCH(c, "k_cl_wgrad");
   return GW_OK;
 }
 
@@ -665,16 +854,15 @@ gw_status gw_mlp_create(gw_ctx* c, gw_mlp** out, int nin, int width, int depth, 
       }
   }
   void* mem = nullptr;
-  if (hipMalloc(&mem, 4 * n->count * sizeof(float)) != hipSuccess) {
+  if (hipMalloc(&mem, 3 * n->count * sizeof(float)) != hipSuccess) {
     delete n;
     return fail(c, GW_ENOMEM, "network parameters");
   }
   n->p = static_cast<float*>(mem);
-  n->g = n->p + n->count;
-  n->m = n->g + n->count;
+  n->m = n->p + n->count;
   n->v = n->m + n->count;
   hipError_t e = hipMemcpy(n->p, h.data(), n->count * 4, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemset(n->g, 0, 3 * n->count * 4);
+  if (e == hipSuccess) e = hipMemset(n->m, 0, 2 * n->count * 4);
   if (e != hipSuccess) {
     (void)hipFree(mem);
     delete n;
@@ -776,7 +964,8 @@ gw_status gw_chi0_closure(gw_ctx* c, gw_mlp* net, int mode, int N, const double*
   const long long n = (long long)N * (N + 1) / 2;
   const long long npad = (n + CL_RT - 1) / CL_RT * CL_RT;
   ClBufs b;
-  gw_status st = cl_buffers(net, N, npad, &b);
+  const bool train = mode == GW_CLOSURE_TRAIN_STEP;
+  gw_status st = cl_buffers(net, N, npad, train, &b);
   if (st != GW_OK) return st;
   const cpx<double>* ct = reinterpret_cast<const cpx<double>*>(chi0_trunc);
   const cpx<double>* cf = reinterpret_cast<const cpx<double>*>(chi0_full);
@@ -785,12 +974,12 @@ gw_status gw_chi0_closure(gw_ctx* c, gw_mlp* net, int mode, int N, const double*
     hipLaunchKernelGGL(k_cl_scale, dim3(1), dim3(256), 0, c->stream, ct, N, b.scale);
     GW_CHECK_LAUNCH(c, "k_cl_scale");
     hipLaunchKernelGGL(k_cl_features, dim3((unsigned)((npad + 255) / 256)), dim3(256), 0,
-                       c->stream, qG, ct, mode == GW_CLOSURE_TRAIN_STEP ? cf : nullptr, N, n, npad,
-                       gap, emax, b.scale, b.X, mode == GW_CLOSURE_TRAIN_STEP ? b.T : nullptr);
+                       c->stream, qG, ct, train ? cf : nullptr, N, n, npad,
+                       gap, emax, b.scale, b.X, train ? b.T : nullptr);
     GW_CHECK_LAUNCH(c, "k_cl_features");
   }
   if ((st = cl_forward(net, npad, b)) != GW_OK) return st;
-  if (mode == GW_CLOSURE_TRAIN_STEP) {
+  if (train) {
     const int nblk = (int)((npad + 255) / 256);
     {
       ProfScope ps(c, "closure_loss");
@@ -807,7 +996,8 @@ gw_status gw_chi0_closure(gw_ctx* c, gw_mlp* net, int mode, int N, const double*
     {
       ProfScope ps(c, "closure_adam");
       hipLaunchKernelGGL(k_adam, dim3((unsigned)((net->count + 255) / 256)), dim3(256), 0,
-                         c->stream, net->p, net->g, net->m, net->v, net->count, lr, b1, b2, 1e-8f,
+                         c->stream, net->p, b.part, cl_splits(net->count), net->m, net->v, net->count, lr, b1,
+                         b2, 1e-8f,
                          bc1, bc2);
       GW_CHECK_LAUNCH(c, "k_adam");
     }
