@@ -7,6 +7,7 @@
 #include <tuple>
 
 #include "common.h"
+#include "mtxel_mm.h"
 
 namespace gw {
 
@@ -439,6 +440,16 @@ gw_status gw_mtxel_spinor(gw_ctx* c, const int box[3], int nspinor, int nv, int 
       return fail(c, GW_EALIAS,
                   "box[%d] = %d <= %d + %d + %d: the pair product would alias onto an eps G", a,
                   box[a], sv->gmax[a], sc->gmax[a], se->gmax[a]);
+
+  // spheres for which a dense-transform kernel is built run on their alias-free grid
+  std::shared_ptr<MmTables> mm;
+  if ((st = mm_tables(c, sv, sc, se, geps, nspinor, dtype == GW_C128, &mm)) != GW_OK) return st;
+  if (mm) {
+    if ((st = ws_begin(c, mm_workspace(*mm, nv, nc))) != GW_OK) return st;
+    st = mm_mtxel(c, *mm, nv, ngv, cv, nc, ngc, cc, mtxel, ws_take(c, 0));
+    if (st != GW_OK || !mhead) return st;
+    return mtxel_head(c, dtype, nspinor, nv, ngv, gv, cv, nc, ngc, gc, cc, mhead);
+  }
 
   const size_t elem = dtype == GW_C128 ? 16 : 8;
   const size_t nbox = (size_t)box[0] * box[1] * box[2];

@@ -9,6 +9,7 @@
 #include <memory>
 #include <set>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "../../include/gw.h"
@@ -88,6 +89,8 @@ struct PinRec {
   hipEvent_t ev;   // recorded after that copy
 };
 
+struct MmTables;  // mtxel_mm.h
+
 }  // namespace gw
 
 struct gw_ctx {
@@ -101,6 +104,10 @@ struct gw_ctx {
   size_t ws_used = 0;
   // cached device tables
   std::map<std::string, gw::SphereMap> spheres;
+  // transform tables per (valence, conduction, eps) sphere, spinor count and type; null
+  // where no dense-transform kernel is built for the sizes
+  std::map<std::tuple<const gw::SphereMap*, const gw::SphereMap*, const gw::SphereMap*, int, bool>,
+           std::shared_ptr<gw::MmTables>> mm;
   std::map<std::pair<int, int>, void*> twiddles;  // (n, is_double) -> device table
   std::map<long long, void*> tile_orders;         // (tiles, block shape) -> chi0 tile order (int2)
   int* d_flag = nullptr;                          // device status flags

@@ -23,6 +23,7 @@
 #include <sstream>
 #include <tuple>
 
+#include "mtxel_mm.h"
 #include "tiles.h"
 
 namespace gw {
@@ -199,6 +200,7 @@ struct gw_plan_q {
   double* wts = nullptr;
   void* X = nullptr;  // split-BF16 operands of the contraction
   std::vector<int> match;
+  std::shared_ptr<gw::MmTables> mm;  // dense-transform tables; held for the graph
 };
 
 struct gw_plan {
@@ -213,6 +215,7 @@ struct gw_plan {
   std::vector<gw_plan_q> q;
   bool shared_c = false;
   int nc_shared = 0;
+  bool mm = false;       // every q on the dense-transform path
   bool compact = false;  // conduction kept as compact x-transformed slabs
   // device memory (one allocation)
   char* base = nullptr;
@@ -346,7 +349,7 @@ static gw_status enqueue_front(gw_plan* p) {
     return dbl ? band_to_grid<double>(c, p->box, nbs, ng, cc, sc, p->uc, p->bscr, p->bscr_bytes)
                : band_to_grid<float>(c, p->box, nbs, ng, cc, sc, p->uc, p->bscr, p->bscr_bytes);
   };
-  if (p->shared_c) {
+  if (p->shared_c && !p->mm) {
     const auto& q0 = p->q[0];
     if ((st = conduction(p->nc_shared * ns, q0.d.ngc, q0.d.cc, q0.sc)) != GW_OK) return st;
   }
@@ -354,25 +357,30 @@ static gw_status enqueue_front(gw_plan* p) {
   const void* tcs = p->compact ? p->uc : nullptr;
   for (auto& q : p->q) {
     const int nv = q.d.nv, nc = q.d.nc;
-    if (!p->shared_c) {
-      if ((st = conduction(nc * ns, q.d.ngc, q.d.cc, q.sc)) != GW_OK) return st;
-    }
-    st = dbl ? band_to_grid<double>(c, p->box, nv * ns, q.d.ngv, q.d.cv, q.sv, p->uv, p->bscr,
-                                    p->bscr_bytes)
-             : band_to_grid<float>(c, p->box, nv * ns, q.d.ngv, q.d.cv, q.sv, p->uv, p->bscr,
-                                   p->bscr_bytes);
-    if (st != GW_OK) return st;
-    const int vt = std::min(nv, p->pair_chunk);
-    const int ct = std::max(1, std::min(nc, p->pair_chunk / vt));
-    for (int v0 = 0; v0 < nv; v0 += vt)
-      for (int c0 = 0; c0 < nc; c0 += ct) {
-        const int nvt = std::min(vt, nv - v0), nct = std::min(ct, nc - c0);
-        st = dbl ? pair_to_eps<double>(c, p->box, ns, p->uv, ucf, tcs, q.sc, v0, nvt, c0, nct, nc,
-                                       q.se, q.M, p->pscr)
-                 : pair_to_eps<float>(c, p->box, ns, p->uv, ucf, tcs, q.sc, v0, nvt, c0, nct, nc,
-                                      q.se, q.M, p->pscr);
-        if (st != GW_OK) return st;
+    if (p->mm) {
+      st = mm_mtxel(c, *q.mm, nv, q.d.ngv, q.d.cv, nc, q.d.ngc, q.d.cc, q.M, p->pscr);
+      if (st != GW_OK) return st;
+    } else {
+      if (!p->shared_c) {
+        if ((st = conduction(nc * ns, q.d.ngc, q.d.cc, q.sc)) != GW_OK) return st;
       }
+      st = dbl ? band_to_grid<double>(c, p->box, nv * ns, q.d.ngv, q.d.cv, q.sv, p->uv, p->bscr,
+                                      p->bscr_bytes)
+               : band_to_grid<float>(c, p->box, nv * ns, q.d.ngv, q.d.cv, q.sv, p->uv, p->bscr,
+                                     p->bscr_bytes);
+      if (st != GW_OK) return st;
+      const int vt = std::min(nv, p->pair_chunk);
+      const int ct = std::max(1, std::min(nc, p->pair_chunk / vt));
+      for (int v0 = 0; v0 < nv; v0 += vt)
+        for (int c0 = 0; c0 < nc; c0 += ct) {
+          const int nvt = std::min(vt, nv - v0), nct = std::min(ct, nc - c0);
+          st = dbl ? pair_to_eps<double>(c, p->box, ns, p->uv, ucf, tcs, q.sc, v0, nvt, c0, nct, nc,
+                                         q.se, q.M, p->pscr)
+                   : pair_to_eps<float>(c, p->box, ns, p->uv, ucf, tcs, q.sc, v0, nvt, c0, nct, nc,
+                                        q.se, q.M, p->pscr);
+          if (st != GW_OK) return st;
+        }
+    }
     if (q.mhead) {
       st = head_overlap(c, p->dtype, ns, nv, q.d.ngv, q.d.cv, nc, q.d.ngc, q.d.cc, q.dmatch,
                         q.nmatch, q.mhead);
@@ -563,6 +571,12 @@ gw_status gw_plan_create(gw_ctx* c, gw_plan** out, const int box[3], int nspinor
         delete p;
         return fail(c, GW_EALIAS, "q %d: box[%d] too small, the pair product aliases", i, a);
       }
+    st = mm_tables(c, p->q[i].sv, p->q[i].sc, p->q[i].se, qd[i].geps, nspinor, dtype == GW_C128,
+                   &p->q[i].mm);
+    if (st != GW_OK) {
+      delete p;
+      return st;
+    }
     if (qd[i].head_index >= 0) {
       std::map<std::tuple<int, int, int>, int> lut;
       for (int g = 0; g < qd[i].ngc; ++g)
@@ -605,7 +619,14 @@ gw_status gw_plan_compile(gw_plan* p) {
   const int band_chunk = (int)std::max<size_t>(1, std::min<size_t>(nbs_max, (512ull << 20) / band_per));
   p->bscr_bytes = band_per * band_chunk;
   p->pair_chunk = (int)std::max<size_t>(1, std::min<size_t>(65535, (1ull << 30) / pair_per));
-  const size_t pscr_bytes = pair_per * p->pair_chunk;
+  size_t pscr_bytes = pair_per * p->pair_chunk;
+  p->mm = true;
+  for (auto& q : p->q) p->mm = p->mm && q.mm;
+  if (p->mm) {
+    pscr_bytes = 0;
+    for (auto& q : p->q) pscr_bytes = std::max(pscr_bytes, mm_workspace(*q.mm, q.d.nv, q.d.nc));
+    p->bscr_bytes = 0;
+  }
   // matrices
   p->nmat = (int)p->q.size() * p->nfreq;
   p->nmax = 0;
@@ -632,7 +653,8 @@ gw_status gw_plan_compile(gw_plan* p) {
                                                        (p->shared_c ? p->nc_shared : q.d.nc) * ns,
                                                        elem));
   }
-  const size_t uv_bytes = (size_t)nv_max * ns * nbox * elem;
+  size_t uv_bytes = (size_t)nv_max * ns * nbox * elem;
+  if (p->mm) uc_bytes = uv_bytes = 0;  // the fields are part of the pair scratch
   parts.push_back({&p->uc, uc_bytes});
   parts.push_back({&p->uv, uv_bytes});
   parts.push_back({&p->bscr, p->bscr_bytes});
