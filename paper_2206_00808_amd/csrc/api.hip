@@ -1,5 +1,6 @@
 // C ABI of libgwspinor: argument validation, device tables, workspace,
 // per-kernel event timing, and the entry points declared in include/gw.h.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstring>
@@ -143,23 +144,6 @@ gw_status sphere_map(gw_ctx* c, const int32_t* g, int n, const int box[3], Spher
   }
   GW_HIP(c, hipMalloc(&sm.d_cube, ncube * sizeof(int)));
   GW_HIP(c, hipMemcpy(sm.d_cube, cube.data(), ncube * sizeof(int), hipMemcpyHostToDevice));
-  // columns (jx, jy) with at least one sphere point, y-major
-  const int nxy = sm.ext[0] * sm.ext[1];
-  std::vector<int> disk(nxy, -1), cols;
-  for (int jy = 0; jy < sm.ext[1]; ++jy)
-    for (int jx = 0; jx < sm.ext[0]; ++jx) {
-      bool any = false;
-      for (int jz = 0; jz < sm.ext[2] && !any; ++jz)
-        any = cube[((size_t)jx * sm.ext[1] + jy) * sm.ext[2] + jz] >= 0;
-      if (any) {
-        disk[jy * sm.ext[0] + jx] = (int)cols.size();
-        cols.push_back(jy * sm.ext[0] + jx);
-      }
-    }
-  sm.ndisk = (int)cols.size();
-  disk.insert(disk.end(), cols.begin(), cols.end());
-  GW_HIP(c, hipMalloc(&sm.d_disk, disk.size() * sizeof(int)));
-  GW_HIP(c, hipMemcpy(sm.d_disk, disk.data(), disk.size() * sizeof(int), hipMemcpyHostToDevice));
   auto res = c->spheres.emplace(key, sm);
   *out = &res.first->second;
   return GW_OK;
@@ -211,6 +195,15 @@ static bool factorable(int n) {
   return n == 1;
 }
 
+void fft_grid(const int box[3], const SphereMap* sv, const SphereMap* sc, const SphereMap* se,
+              int grid[3]) {
+  for (int a = 0; a < 3; ++a) {
+    const int g = std::max({sv->gmax[a], sc->gmax[a], se->gmax[a]});
+    grid[a] = std::max(sv->gmax[a] + sc->gmax[a] + se->gmax[a], 2 * g) + 1;
+    while (!factorable(grid[a])) ++grid[a];
+  }
+}
+
 static bool g_ok(const int32_t* g, int n) { return n == 0 || g != nullptr; }
 
 // FP64 G = 0 overlaps of the small-q head (head.hip), from the G vectors the
@@ -235,62 +228,6 @@ static gw_status mtxel_head(gw_ctx* c, gw_dtype dtype, int nspinor, int nv, int 
   int* dmatch = static_cast<int*>(ws_take(c, match.size() * sizeof(int)));
   if ((st = stage_h2d(c, dmatch, match.data(), match.size() * sizeof(int))) != GW_OK) return st;
   return head_overlap(c, dtype, nspinor, nv, ngv, cv, nc, ngc, cc, dmatch, nm, mhead);
-}
-
-// Matrix elements on boxes with a built xy-plane pair kernel (fft_xy.hip):
-// valence bands as full fields in [v][s][z][y][x] order, conduction bands as
-// compact z-transformed slabs, pairs in chunks of at most 4 GiB of intermediate.
-static gw_status mtxel_xy(gw_ctx* c, const int box[3], int nspinor, int nv, int ngv,
-                          const void* cv, int nc, int ngc, const void* cc, gw_dtype dtype,
-                          const SphereMap* sv, const SphereMap* sc, const SphereMap* se,
-                          void* mtxel, int head_index, double* mhead, const int32_t* gv,
-                          const int32_t* gc) {
-  const size_t elem = dtype == GW_C128 ? 16 : 8;
-  const size_t nbox = (size_t)box[0] * box[1] * box[2];
-  const size_t uv_bytes = (size_t)nv * nspinor * nbox * elem;
-  const size_t uc_bytes = band_zc_bytes(box, sc, nc * nspinor, elem);
-  const size_t band_per = band_scratch_bytes(box, sv, 1, elem);
-  const int band_chunk = (int)std::max<size_t>(1, std::min<size_t>((size_t)nv * nspinor,
-                                                                   (512ull << 20) / band_per));
-  const size_t band_bytes = band_per * band_chunk;
-  const size_t pair_per = pair_xy_scratch_bytes(box, se, 1, elem);
-  int max_pairs = (int)std::max<size_t>(1, (4ull << 30) / pair_per);
-  if (max_pairs > 65535) max_pairs = 65535;
-  const int vt = std::min(nv, max_pairs);
-  const int ct = std::max(1, std::min(nc, max_pairs / vt));
-  // the valence fields in (x, y, z) order pass through the pair scratch
-  const size_t pair_bytes = std::max(pair_per * (size_t)vt * ct, uv_bytes);
-  gw_status st = ws_begin(c, align_up(uv_bytes) + align_up(uc_bytes) + align_up(band_bytes) +
-                                 align_up(pair_bytes));
-  if (st != GW_OK) return st;
-  void* uv = ws_take(c, uv_bytes);
-  void* uc = ws_take(c, uc_bytes);
-  void* bscr = ws_take(c, band_bytes);
-  void* pscr = ws_take(c, pair_bytes);
-  const bool dbl = dtype == GW_C128;
-  st = dbl ? band_to_grid<double>(c, box, nv * nspinor, ngv, cv, sv, pscr, bscr, band_bytes)
-           : band_to_grid<float>(c, box, nv * nspinor, ngv, cv, sv, pscr, bscr, band_bytes);
-  if (st != GW_OK) return st;
-  st = dbl ? grid_to_zyx<double>(c, box, nv * nspinor, pscr, uv)
-           : grid_to_zyx<float>(c, box, nv * nspinor, pscr, uv);
-  if (st != GW_OK) return st;
-  st = dbl ? band_zc<double>(c, box, nc * nspinor, ngc, cc, sc, uc)
-           : band_zc<float>(c, box, nc * nspinor, ngc, cc, sc, uc);
-  if (st != GW_OK) return st;
-  for (int v0 = 0; v0 < nv; v0 += vt) {
-    const int nvt = std::min(vt, nv - v0);
-    for (int c0 = 0; c0 < nc; c0 += ct) {
-      const int nct = std::min(ct, nc - c0);
-      st = dbl ? pair_to_eps_xy<double>(c, box, nspinor, uv, uc, sc, v0, nvt, c0, nct, nc, se,
-                                        mtxel, pscr)
-               : pair_to_eps_xy<float>(c, box, nspinor, uv, uc, sc, v0, nvt, c0, nct, nc, se,
-                                       mtxel, pscr);
-      if (st != GW_OK) return st;
-    }
-  }
-  if (mhead)
-    return mtxel_head(c, dtype, nspinor, nv, ngv, gv, cv, nc, ngc, gc, cc, mhead);
-  return GW_OK;
 }
 
 }  // namespace gw
@@ -345,7 +282,6 @@ gw_status gw_ctx_destroy(gw_ctx* c) {
   for (auto e : c->ev_pool) (void)hipEventDestroy(e);
   for (auto& kv : c->spheres) {
     (void)hipFree(kv.second.d_cube);
-    (void)hipFree(kv.second.d_disk);
   }
   for (auto& kv : c->twiddles) (void)hipFree(kv.second);
   for (auto& kv : c->tile_orders) (void)hipFree(kv.second);
@@ -451,89 +387,47 @@ gw_status gw_mtxel_spinor(gw_ctx* c, const int box[3], int nspinor, int nv, int 
     return mtxel_head(c, dtype, nspinor, nv, ngv, gv, cv, nc, ngc, gc, cc, mhead);
   }
 
+  int grid[3];
+  fft_grid(box, sv, sc, se, grid);
   const size_t elem = dtype == GW_C128 ? 16 : 8;
-  const size_t nbox = (size_t)box[0] * box[1] * box[2];
+  const size_t nbox = (size_t)grid[0] * grid[1] * grid[2];
   const size_t uv_bytes = (size_t)nv * nspinor * nbox * elem;
-  if (!pair_compact_shape(box) && pair_xy_shape(box))
-    return mtxel_xy(c, box, nspinor, nv, ngv, cv, nc, ngc, cc, dtype, sv, sc, se, mtxel,
-                    head_index, mhead, gv, gc);
-  // conduction bands: compact x-transformed slabs when the pair kernels build
-  // their planes themselves, full real-space fields otherwise
-  const bool compact = pair_compact_shape(box);
-  const size_t uc_bytes = compact ? band_compact_bytes(box, sc, nc * nspinor, elem)
-                                  : (size_t)nc * nspinor * nbox * elem;
+  const size_t uc_bytes = (size_t)nc * nspinor * nbox * elem;
   // band scratch: a chunk of band-spins of the compact x-pass output
-  const size_t band_per = band_scratch_bytes(box, sv, 1, elem) > band_scratch_bytes(box, sc, 1, elem)
-                              ? band_scratch_bytes(box, sv, 1, elem)
-                              : band_scratch_bytes(box, sc, 1, elem);
+  const size_t band_per = std::max(band_scratch_bytes(grid, sv, 1, elem),
+                                   band_scratch_bytes(grid, sc, 1, elem));
   const int nbs_max = std::max(nv, nc) * nspinor;
   const int band_chunk = (int)std::max<size_t>(1, std::min<size_t>(nbs_max, (512ull << 20) / band_per));
   const size_t band_bytes = band_per * band_chunk;
   // pair scratch: all valence bands times a tile of conduction bands
-  const size_t pair_per = pair_scratch_bytes(box, se, 1, elem);
-  size_t pair_budget = 1ull << 30;
-  int max_pairs = (int)std::max<size_t>(1, pair_budget / pair_per);
-  if (max_pairs > 65535) max_pairs = 65535;
-  int vt = std::min(nv, max_pairs);
-  int ct = std::max(1, std::min(nc, max_pairs / vt));
+  const size_t pair_per = pair_scratch_bytes(grid, se, 1, elem);
+  const int max_pairs = (int)std::max<size_t>(1, std::min<size_t>(65535, (1ull << 30) / pair_per));
+  const int vt = std::min(nv, max_pairs), ct = std::max(1, std::min(nc, max_pairs / vt));
   const size_t pair_bytes = pair_per * (size_t)vt * ct;
-  // head match list
-  std::vector<int> match;
-  if (mhead) {
-    std::map<std::tuple<int, int, int>, int> lut;
-    for (int i = 0; i < ngc; ++i) lut[std::make_tuple(gc[3 * i], gc[3 * i + 1], gc[3 * i + 2])] = i;
-    for (int i = 0; i < ngv; ++i) {
-      auto it = lut.find(std::make_tuple(gv[3 * i], gv[3 * i + 1], gv[3 * i + 2]));
-      if (it != lut.end()) { match.push_back(i); match.push_back(it->second); }
-    }
-  }
-  const size_t match_bytes = match.size() * sizeof(int) + 16;
   st = ws_begin(c, align_up(uv_bytes) + align_up(uc_bytes) + align_up(band_bytes) +
-                       align_up(pair_bytes) + align_up(match_bytes));
+                       align_up(pair_bytes));
   if (st != GW_OK) return st;
   void* uv = ws_take(c, uv_bytes);
   void* uc = ws_take(c, uc_bytes);
   void* bscr = ws_take(c, band_bytes);
   void* pscr = ws_take(c, pair_bytes);
-  int* dmatch = static_cast<int*>(ws_take(c, match_bytes));
-
-  if (dtype == GW_C128) {
-    if ((st = band_to_grid<double>(c, box, nv * nspinor, ngv, cv, sv, uv, bscr, band_bytes)) != GW_OK) return st;
-    st = compact ? band_compact<double>(c, box, nc * nspinor, ngc, cc, sc, uc)
-                 : band_to_grid<double>(c, box, nc * nspinor, ngc, cc, sc, uc, bscr, band_bytes);
-    if (st != GW_OK) return st;
-  } else {
-    if ((st = band_to_grid<float>(c, box, nv * nspinor, ngv, cv, sv, uv, bscr, band_bytes)) != GW_OK) return st;
-    st = compact ? band_compact<float>(c, box, nc * nspinor, ngc, cc, sc, uc)
-                 : band_to_grid<float>(c, box, nc * nspinor, ngc, cc, sc, uc, bscr, band_bytes);
-    if (st != GW_OK) return st;
-  }
+  const bool dbl = dtype == GW_C128;
+  auto bands = [&](int nbs, int ng, const void* coef, const SphereMap* sm, void* u) {
+    return dbl ? band_to_grid<double>(c, grid, nbs, ng, coef, sm, u, bscr, band_bytes)
+               : band_to_grid<float>(c, grid, nbs, ng, coef, sm, u, bscr, band_bytes);
+  };
+  if ((st = bands(nv * nspinor, ngv, cv, sv, uv)) != GW_OK) return st;
+  if ((st = bands(nc * nspinor, ngc, cc, sc, uc)) != GW_OK) return st;
   for (int v0 = 0; v0 < nv; v0 += vt) {
     const int nvt = std::min(vt, nv - v0);
     for (int c0 = 0; c0 < nc; c0 += ct) {
       const int nct = std::min(ct, nc - c0);
-      const void* ucf = compact ? nullptr : uc;
-      const void* tcs = compact ? uc : nullptr;
-      if (dtype == GW_C128)
-        st = pair_to_eps<double>(c, box, nspinor, uv, ucf, tcs, sc, v0, nvt, c0, nct, nc, se,
-                                 mtxel, pscr);
-      else
-        st = pair_to_eps<float>(c, box, nspinor, uv, ucf, tcs, sc, v0, nvt, c0, nct, nc, se,
-                                mtxel, pscr);
+      st = dbl ? pair_to_eps<double>(c, grid, nspinor, uv, uc, v0, nvt, c0, nct, nc, se, mtxel, pscr)
+               : pair_to_eps<float>(c, grid, nspinor, uv, uc, v0, nvt, c0, nct, nc, se, mtxel, pscr);
       if (st != GW_OK) return st;
     }
   }
-  if (mhead) {
-    const int nm = (int)match.size() / 2;
-    if (nm > 0) {
-      if ((st = stage_h2d(c, dmatch, match.data(), match.size() * sizeof(int))) != GW_OK)
-        return st;
-      if ((st = head_overlap(c, dtype, nspinor, nv, ngv, cv, nc, ngc, cc, dmatch, nm, mhead)) != GW_OK)
-        return st;
-    } else {
-      GW_HIP(c, hipMemsetAsync(mhead, 0, (size_t)nv * nc * 16, c->stream));
-    }
-  }
+  if (mhead) return mtxel_head(c, dtype, nspinor, nv, ngv, gv, cv, nc, ngc, gc, cc, mhead);
   return GW_OK;
 }
 

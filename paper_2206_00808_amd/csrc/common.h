@@ -59,6 +59,10 @@ struct FftPlan {
   int radix[12];
 };
 FftPlan make_fft_plan(int n);  // n must factor into 2, 3, 5
+// A grid for the general transforms: per axis the shortest product of 2, 3 and 5 that
+// holds every sphere and keeps the pair product from aliasing, at most the box.
+void fft_grid(const int box[3], const struct SphereMap* sv, const struct SphereMap* sc,
+              const struct SphereMap* se, int grid[3]);
 
 // ---------------------------------------------------------------- geometry
 // A G-sphere placed in a box: compact cube [2gx+1][2gy+1][2gz+1] -> sphere index or -1.
@@ -67,11 +71,6 @@ struct SphereMap {
   int ext[3];            // 2*gmax+1
   int* d_cube = nullptr; // device int32[ext0*ext1*ext2]
   int n = 0;             // sphere size
-  // the (x, y) columns of the compact cube that hold a sphere point: d_disk
-  // [ext1*ext0] maps jy*ext0 + jx to the column's index (or -1), followed by
-  // [ndisk] entries giving each column's jy*ext0 + jx (device, one allocation)
-  int ndisk = 0;
-  int* d_disk = nullptr;
 };
 
 struct ProfRec {
@@ -178,35 +177,11 @@ struct ProfScope {
 template <typename T>
 gw_status band_to_grid(gw_ctx* c, const int box[3], int nbs, int ng, const void* coef,
                        const SphereMap* sm, void* u_out, void* scratch, size_t scratch_bytes);
-// Pairs (v, c) for v in [v0, v0+nvt), c in [c0, c0+nct) into M. The conduction
-// bands come either as full real-space fields uc, or (box shapes for which
-// pair_compact_shape holds) as compact x-transformed slabs tc on sphere sc,
-// from which the pair kernels build each plane themselves.
+// Pairs (v, c) for v in [v0, v0+nvt), c in [c0, c0+nct) into M, from real-space fields.
 template <typename T>
 gw_status pair_to_eps(gw_ctx* c, const int box[3], int nspinor, const void* uv, const void* uc,
-                      const void* tc, const SphereMap* sc, int v0, int nvt, int c0, int nct,
-                      int nc_total, const SphereMap* em, void* mtxel, void* scratch);
-template <typename T>
-gw_status band_compact(gw_ctx* c, const int box[3], int nbs, int ng, const void* coef,
-                       const SphereMap* sm, void* out);
-bool pair_compact_shape(const int box[3]);
-// Boxes whose xy-planes have a built pair kernel (fft_xy.hip): conduction bands
-// as compact z-transformed slabs [c][s][z][jy][jx] on sphere sc, valence bands
-// as full fields in [v][s][z][y][x] order, pair intermediate
-// T[pair][z][jy][jx] on the eps sphere's (x, y) extent.
-bool pair_xy_shape(const int box[3]);
-size_t band_zc_bytes(const int box[3], const SphereMap* sm, int nbs, size_t elem);
-size_t pair_xy_scratch_bytes(const int box[3], const SphereMap* em, int npairs, size_t elem);
-template <typename T>
-gw_status band_zc(gw_ctx* c, const int box[3], int nbs, int ng, const void* coef,
-                  const SphereMap* sm, void* out);
-template <typename T>
-gw_status grid_to_zyx(gw_ctx* c, const int box[3], int nbs, const void* u, void* w);
-template <typename T>
-gw_status pair_to_eps_xy(gw_ctx* c, const int box[3], int nspinor, const void* uvz,
-                         const void* tcz, const SphereMap* sc, int v0, int nvt, int c0, int nct,
-                         int nc_total, const SphereMap* em, void* mtxel, void* scratch);
-size_t band_compact_bytes(const int box[3], const SphereMap* sm, int nbs, size_t elem);
+                      int v0, int nvt, int c0, int nct, int nc_total, const SphereMap* em,
+                      void* mtxel, void* scratch);
 size_t band_scratch_bytes(const int box[3], const SphereMap* sm, int nbs, size_t elem);
 size_t pair_scratch_bytes(const int box[3], const SphereMap* em, int npairs, size_t elem);
 

@@ -32,8 +32,6 @@
 #include <cmath>
 #include <vector>
 
-#include "regfft.h"
-
 namespace gw {
 
 namespace {
