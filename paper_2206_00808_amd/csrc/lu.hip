@@ -13,7 +13,7 @@
 //
 // General path: right-looking blocked LU with partial pivoting (PA = LU), every
 // frequency in the same launches (grid.z / grid.y = frequency):
-//   panel  : one 1024-thread workgroup factors the N x nb column panel
+//   panel  : one workgroup per matrix factors the N x nb column panel
 //            (pivot = largest |re|+|im|, lowest row on ties)
 //   laswp  : the panel's row interchanges applied to the other columns
 //   trsm   : U12 = L11^-1 A12
@@ -21,6 +21,8 @@
 // then eps^-1 = U^-1 L^-1 P by blocked forward/back substitution on P*I.
 #include "common.h"
 #include "tiles.h"
+
+#include <climits>
 
 namespace gw {
 
@@ -97,6 +99,239 @@ __global__ void __launch_bounds__(1024) k_lu_panel(cpx<double>* __restrict__ A, 
   }
 }
 
+// The same factorisation with the panel in registers: a thread holds eight columns of
+// up to R rows, and the panel is factored by sub-panels of eight.  Rows stay with
+// their threads (only a row's position moves, so the choice and the order of the
+// pivots are those of explicit interchanges); a column costs one barrier, because
+// each wavefront publishes its candidate's position and its whole row before it and
+// every thread picks the winner after it.  Sub-panels are left-looking: the eight
+// columns take the earlier ones' L (kept in W by columns, so that a wavefront's rows
+// are contiguous) times U (in LDS, solved by one wavefront) when they are loaded.  The
+// finished panel is moved to the rows' final positions at the end.
+//
+// Bound: latency of the columns' chains; one workgroup per matrix.  A 32-column panel
+// of up to 768 rows takes 101 us, of up to 512 rows 72 and of up to 256 rows 42 (mean
+// over a 613-row factorisation; 265 us with the columns in global memory, two passes
+// over them and 12 barriers per column).  eps^-1 of five 613-row matrices: 8.27 ms
+// before, 3.58 ms with these panels and the four-lane triangular solves.
+constexpr int SW = 8;           // sub-panel width
+constexpr int kPanelT = 256;    // threads: one wavefront per SIMD, up to 12 rows each
+
+// 1 / x: the hardware estimate and two Newton steps
+__device__ __forceinline__ double rcp_newton(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+// largest v of the wavefront, and the lowest position among the lanes that hold it
+__device__ __forceinline__ int dpp16(int v, int step) {
+  switch (step) {
+    case 0: return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xf, 0xf, true);   // lane ^ 1
+    case 1: return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xf, 0xf, true);   // lane ^ 2
+    case 2: return __builtin_amdgcn_mov_dpp(v, 0x141, 0xf, 0xf, true);  // mirror within 8
+    default: return __builtin_amdgcn_mov_dpp(v, 0x140, 0xf, 0xf, true); // mirror within 16
+  }
+}
+__device__ __forceinline__ double dpp16(double v, int step) {
+  const long long b = __double_as_longlong(v);
+  const int lo = dpp16((int)b, step), hi = dpp16((int)(b >> 32), step);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double readlane(double v, int l) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ void wave_best(double* v, int* pos) {
+  double m = *v;
+#pragma unroll
+  for (int st = 0; st < 4; ++st) m = fmax(m, dpp16(m, st));
+  m = fmax(fmax(readlane(m, 0), readlane(m, 16)), fmax(readlane(m, 32), readlane(m, 48)));
+  int p = *v == m ? *pos : INT_MAX;
+#pragma unroll
+  for (int st = 0; st < 4; ++st) p = min(p, dpp16(p, st));
+  p = min(min(__builtin_amdgcn_readlane(p, 0), __builtin_amdgcn_readlane(p, 16)),
+          min(__builtin_amdgcn_readlane(p, 32), __builtin_amdgcn_readlane(p, 48)));
+  *v = m;
+  *pos = p;
+}
+
+template <int R>
+__global__ void __launch_bounds__(kPanelT) k_lu_panel_reg(cpx<double>* __restrict__ A, int N, int k,
+                                                          int nbk, int* __restrict__ ipiv,
+                                                          int* __restrict__ flag,
+                                                          cpx<double>* __restrict__ W) {
+  constexpr int NW = kPanelT / 64;
+  __shared__ cpx<double> slot[2][NW][SW];
+  __shared__ double cv[2][NW];
+  __shared__ int cp[2][NW];
+  __shared__ cpx<double> P[NB][NB + 1];  // pivot rows: L left of the diagonal, U from it on
+  __shared__ int prow[NB];               // their rows
+  __shared__ int fin[kPanelT * R];       // final position of every row
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  A += (size_t)blockIdx.x * N * N;
+  W += (size_t)blockIdx.x * N * NB;
+  ipiv += (size_t)blockIdx.x * N;
+  const int m = N - k;
+  cpx<double> a[R][SW];
+  int pos[R];
+  bool act[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    pos[r] = k + tid + kPanelT * r;
+    act[r] = tid + kPanelT * r < m;
+  }
+  for (int c0 = 0; c0 < nbk; c0 += SW) {
+    const int w = min(SW, nbk - c0);
+    bool had[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      had[r] = act[r];
+      const cpx<double>* row = A + (size_t)(k + tid + kPanelT * r) * N + k + c0;
+#pragma unroll
+      for (int c = 0; c < SW; ++c) a[r][c] = act[r] && c < w ? row[c] : mk(0.0, 0.0);
+    }
+    if (c0) {
+      // the pivot rows so far: their entries here, and the last sub-panel's L
+      for (int e = tid; e < c0 * SW; e += kPanelT) {
+        const int jj = e / SW, c = e % SW;
+        P[jj][c0 + c] = c < w ? A[(size_t)(k + prow[jj]) * N + k + c0 + c] : mk(0.0, 0.0);
+      }
+      for (int e = tid; e < SW * (c0 - SW); e += kPanelT) {
+        const int jj = c0 - SW + e / (c0 - SW), c = e % (c0 - SW);
+        P[jj][c] = W[(size_t)c * N + prow[jj]];
+      }
+      __syncthreads();
+      if (wave == 0) {  // U = L^-1 times them: lane = (row of the block, column)
+        const int jr = lane / SW, c = c0 + lane % SW;
+        for (int b = 0; b < c0; b += SW) {
+          cpx<double> x = P[b + jr][c];
+#pragma unroll 8
+          for (int t = 0; t < b; ++t) x = x - cmul(P[b + jr][t], P[t][c]);
+#pragma unroll
+          for (int t = 0; t < SW - 1; ++t) {
+            const cpx<double> y = mk(__shfl(x.x, t * SW + lane % SW), __shfl(x.y, t * SW + lane % SW));
+            if (jr > t) x = x - cmul(P[b + jr][b + t], y);
+          }
+          P[b + jr][c] = x;
+          __builtin_amdgcn_wave_barrier();
+        }
+      }
+      __syncthreads();
+      for (int e = tid; e < c0 * SW; e += kPanelT) {
+        const int jj = e / SW, c = e % SW;
+        W[(size_t)(c0 + c) * N + prow[jj]] = P[jj][c0 + c];
+      }
+      // rows no longer active take zeros: every row shares the reads of U
+      constexpr int U = R <= 2 ? 8 : R <= 4 ? 4 : 2;  // columns of L in flight
+      for (int j0 = 0; j0 < c0; j0 += U) {
+        cpx<double> lv[U][R];
+#pragma unroll
+        for (int x = 0; x < U; ++x)
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            lv[x][r] = act[r] ? W[(size_t)(j0 + x) * N + tid + kPanelT * r] : mk(0.0, 0.0);
+#pragma unroll
+        for (int x = 0; x < U; ++x) {
+          cpx<double> u[SW];
+#pragma unroll
+          for (int c = 0; c < SW; ++c) u[c] = P[j0 + x][c0 + c];
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < SW; ++c) a[r][c] = a[r][c] - cmul(lv[x][r], u[c]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < SW; ++q) {
+      if (q >= w) break;
+      const int jj = c0 + q, j = k + jj, par = q & 1;
+      double bv = -1.0;
+      int bp = INT_MAX;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const double v = fabs(a[r][q].x) + fabs(a[r][q].y);
+        if (act[r] && (v > bv || (v == bv && pos[r] < bp))) { bv = v; bp = pos[r]; }
+      }
+      wave_best(&bv, &bp);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (act[r] && pos[r] == bp) {
+#pragma unroll
+          for (int c = 0; c < SW; ++c) slot[par][wave][c] = a[r][c];
+        }
+      if (lane == 0) {
+        cv[par][wave] = bv;
+        cp[par][wave] = bp;
+      }
+      __syncthreads();
+      int bw = 0;
+      bv = cv[par][0];
+      bp = cp[par][0];
+#pragma unroll
+      for (int x = 1; x < NW; ++x) {
+        const double v = cv[par][x];
+        const int o = cp[par][x];
+        if (v > bv || (v == bv && o < bp)) { bv = v; bp = o; bw = x; }
+      }
+      const bool none = !(bv >= 0.0);  // no comparable candidate: keep the diagonal
+      const int p = none ? j : bp;
+      if (tid == 0) {
+        ipiv[j] = p;
+        if (!(bv > 0.0)) flag[0] = 1;
+      }
+      cpx<double> u[SW];
+#pragma unroll
+      for (int c = 0; c < SW; ++c) u[c] = slot[par][bw][c];
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (act[r]) {
+          if (pos[r] == p) {
+            act[r] = false;
+            pos[r] = j;
+            prow[jj] = tid + kPanelT * r;
+#pragma unroll
+            for (int c = 0; c < SW; ++c) P[jj][c0 + c] = a[r][c];
+          } else if (pos[r] == j) {
+            pos[r] = p;
+          }
+        }
+      if (bv > 0.0) {
+        const double den = rcp_newton(u[q].x * u[q].x + u[q].y * u[q].y);
+        const cpx<double> inv = mk(u[q].x * den, -u[q].y * den);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          if (act[r]) {
+            const cpx<double> l = cmul(a[r][q], inv);
+            a[r][q] = l;
+#pragma unroll
+            for (int c = q + 1; c < SW; ++c) a[r][c] = a[r][c] - cmul(l, u[c]);
+          }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (had[r]) {
+        cpx<double>* l = W + (size_t)c0 * N + tid + kPanelT * r;
+#pragma unroll
+        for (int c = 0; c < SW; ++c) l[(size_t)c * N] = a[r][c];
+      }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (tid + kPanelT * r < m) fin[tid + kPanelT * r] = pos[r];
+  __syncthreads();
+#pragma unroll 4
+  for (int e = tid; e < m * NB; e += kPanelT) {
+    const int i = e / NB, c = e % NB;
+    if (c < nbk) A[(size_t)fin[i] * N + k + c] = W[(size_t)c * N + i];
+  }
+}
+
 __global__ void k_lu_laswp(cpx<double>* __restrict__ A, int N, int k, int nbk,
                            const int* __restrict__ ipiv) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
@@ -115,58 +350,67 @@ __global__ void k_lu_laswp(cpx<double>* __restrict__ A, int N, int k, int nbk,
 
 // Solve T X = B in place on rows kb..kb+nbk of X for columns c0..c0+ncols, where
 // T is the nbk x nbk diagonal block of the LU factors: unit lower (UPPER=false)
-// or non-unit upper (UPPER=true).  One thread per right-hand-side column.
+// or non-unit upper (UPPER=true).  Four neighbouring lanes share a right-hand side,
+// lane l holding rows 4 r + l: each solved entry is passed inside the four and taken
+// out of all later rows at once.  (One lane per column, 32 dependent sums, took 20-31
+// us on 613 columns.)
+__device__ __forceinline__ double quad_get(double v, int from) {
+  const long long b = __double_as_longlong(v);
+  int lo = (int)b, hi = (int)(b >> 32);
+  switch (from) {
+    case 0: lo = __builtin_amdgcn_mov_dpp(lo, 0x00, 0xf, 0xf, true);
+            hi = __builtin_amdgcn_mov_dpp(hi, 0x00, 0xf, 0xf, true); break;
+    case 1: lo = __builtin_amdgcn_mov_dpp(lo, 0x55, 0xf, 0xf, true);
+            hi = __builtin_amdgcn_mov_dpp(hi, 0x55, 0xf, 0xf, true); break;
+    case 2: lo = __builtin_amdgcn_mov_dpp(lo, 0xAA, 0xf, 0xf, true);
+            hi = __builtin_amdgcn_mov_dpp(hi, 0xAA, 0xf, 0xf, true); break;
+    default: lo = __builtin_amdgcn_mov_dpp(lo, 0xFF, 0xf, 0xf, true);
+             hi = __builtin_amdgcn_mov_dpp(hi, 0xFF, 0xf, 0xf, true);
+  }
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
 template <bool UPPER>
-__global__ void __launch_bounds__(256) k_trsm_block(const cpx<double>* __restrict__ LU, int N,
+__global__ void __launch_bounds__(64) k_trsm_block(const cpx<double>* __restrict__ LU, int N,
                                                    int kb, int nbk, cpx<double>* __restrict__ X,
                                                    int c0, int ncols) {
-  __shared__ cpx<double> T[NB][NB + 1];
+  __shared__ cpx<double> T[NB][NB + 1];  // T[column][row]: the rows a column is taken out of
   __shared__ cpx<double> dinv[NB];
   LU += (size_t)blockIdx.y * N * N;
   X += (size_t)blockIdx.y * N * N;
-  for (int e = threadIdx.x; e < nbk * nbk; e += blockDim.x) {
-    const int r = e / nbk, cc = e % nbk;
-    T[r][cc] = LU[(size_t)(kb + r) * N + kb + cc];
-  }
-  __syncthreads();
-  if (UPPER && threadIdx.x < nbk) {
-    const cpx<double> d = T[threadIdx.x][threadIdx.x];
-    const double den = d.x * d.x + d.y * d.y;
-    dinv[threadIdx.x] = mk(d.x / den, -d.y / den);
-  }
-  __syncthreads();
-  const int cidx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (cidx >= ncols) return;
-  const int col = c0 + cidx;
-  cpx<double> x[NB];
+  const int lane = threadIdx.x, l4 = lane & 3, cidx = blockIdx.x * 16 + (lane >> 2);
+  const bool live = cidx < ncols;
+  cpx<double>* xc = X + (size_t)kb * N + c0 + (live ? cidx : 0);
+  cpx<double> x[NB / 4];
 #pragma unroll
-  for (int i = 0; i < NB; ++i)
-    x[i] = (i < nbk) ? X[(size_t)(kb + i) * N + col] : mk<double>(0, 0);
-  if (!UPPER) {
-#pragma unroll
-    for (int i = 1; i < NB; ++i) {
-      if (i < nbk) {
-        cpx<double> s = x[i];
-#pragma unroll
-        for (int t = 0; t < i; ++t) s = s - cmul(T[i][t], x[t]);
-        x[i] = s;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int i = NB - 1; i >= 0; --i) {
-      if (i < nbk) {
-        cpx<double> s = x[i];
-#pragma unroll
-        for (int t = i + 1; t < NB; ++t)
-          if (t < nbk) s = s - cmul(T[i][t], x[t]);
-        x[i] = cmul(s, dinv[i]);
-      }
+  for (int r = 0; r < NB / 4; ++r)
+    x[r] = 4 * r + l4 < nbk ? xc[(size_t)(4 * r + l4) * N] : mk<double>(0, 0);
+#pragma unroll 4
+  for (int e = lane; e < NB * NB; e += 64) {
+    const int r = e / NB, cc = e % NB;
+    const bool in = r < nbk && cc < nbk;
+    const cpx<double> t = in ? LU[(size_t)(kb + r) * N + kb + cc] : mk(0.0, 0.0);
+    T[cc][r] = (UPPER ? r < cc : r > cc) ? t : mk(0.0, 0.0);
+    if (UPPER && r == cc) {
+      const double den = t.x * t.x + t.y * t.y;
+      dinv[r] = in ? mk(t.x / den, -t.y / den) : mk(0.0, 0.0);
     }
   }
+  __syncthreads();
 #pragma unroll
-  for (int i = 0; i < NB; ++i)
-    if (i < nbk) X[(size_t)(kb + i) * N + col] = x[i];
+  for (int s = 0; s < NB; ++s) {
+    const int t = UPPER ? NB - 1 - s : s, rt = t / 4;
+    cpx<double> y = mk(quad_get(x[rt].x, t & 3), quad_get(x[rt].y, t & 3));
+    if (UPPER) {
+      y = cmul(y, dinv[t]);
+      if (l4 == (t & 3)) x[rt] = y;
+    }
+#pragma unroll
+    for (int r = UPPER ? 0 : rt; r < (UPPER ? rt + 1 : NB / 4); ++r)
+      x[r] = x[r] - cmul(T[t][4 * r + l4], y);
+  }
+#pragma unroll
+  for (int r = 0; r < NB / 4; ++r)
+    if (live && 4 * r + l4 < nbk) xc[(size_t)(4 * r + l4) * N] = x[r];
 }
 
 // Row s of P*I is e_perm[s], perm = identity after the interchanges s <-> ipiv[s].
@@ -668,12 +912,14 @@ __global__ void k_unscale(cpx<double>* __restrict__ A, const double* __restrict_
 gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
                              const double* vcoul, double* epsinv) {
   const size_t nn = (size_t)N * N;
-  const size_t bytes = align_up(nfreq * nn * 16) + 2 * align_up((size_t)nfreq * N * 4);
+  const size_t bytes = align_up(nfreq * nn * 16) + 2 * align_up((size_t)nfreq * N * 4) +
+                       align_up((size_t)nfreq * N * NB * 16);
   gw_status st = ws_begin(c, bytes);
   if (st != GW_OK) return st;
   cpx<double>* LU = static_cast<cpx<double>*>(ws_take(c, nfreq * nn * 16));
   int* ipiv = static_cast<int*>(ws_take(c, (size_t)nfreq * N * 4));
   int* perm = static_cast<int*>(ws_take(c, (size_t)nfreq * N * 4));
+  cpx<double>* W = static_cast<cpx<double>*>(ws_take(c, (size_t)nfreq * N * NB * 16));
   cpx<double>* Y = reinterpret_cast<cpx<double>*>(epsinv);
   {
     ProfScope ps(c, "flags_clear");
@@ -693,8 +939,20 @@ gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
     const int nbk = std::min(NB, N - k);
     {
       ProfScope ps(c, "lu_panel");
-      hipLaunchKernelGGL(k_lu_panel, dim3(nfreq), dim3(1024), 0, c->stream, LU, N, k, nbk, ipiv,
-                         c->d_flag);
+      // rows per thread that fit the registers; more rows stay in global memory
+      switch ((N - k + kPanelT - 1) / kPanelT) {
+#define GW_PANEL(R)                                                                          \
+  case R:                                                                                    \
+    hipLaunchKernelGGL(k_lu_panel_reg<R>, dim3(nfreq), dim3(kPanelT), 0, c->stream, LU, N, k, \
+                       nbk, ipiv, c->d_flag, W);                                             \
+    break;
+        GW_PANEL(1) GW_PANEL(2) GW_PANEL(3) GW_PANEL(4) GW_PANEL(5) GW_PANEL(6) GW_PANEL(7)
+        GW_PANEL(8) GW_PANEL(9) GW_PANEL(10) GW_PANEL(11) GW_PANEL(12)
+#undef GW_PANEL
+        default:
+          hipLaunchKernelGGL(k_lu_panel, dim3(nfreq), dim3(1024), 0, c->stream, LU, N, k, nbk,
+                             ipiv, c->d_flag);
+      }
       GW_CHECK_LAUNCH(c, "k_lu_panel");
     }
     {
@@ -707,7 +965,7 @@ gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
     if (rest > 0) {
       {
         ProfScope ps(c, "lu_trsm");
-        hipLaunchKernelGGL(k_trsm_block<false>, dim3((rest + 255) / 256, nfreq), dim3(256), 0,
+        hipLaunchKernelGGL(k_trsm_block<false>, dim3((rest + 15) / 16, nfreq), dim3(64), 0,
                            c->stream, LU, N, k, nbk, LU, k + nbk, rest);
         GW_CHECK_LAUNCH(c, "k_trsm_block");
       }
@@ -731,7 +989,7 @@ gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
     const int nbk = std::min(NB, N - kb);
     {
       ProfScope ps(c, "inv_trsm_lower");
-      hipLaunchKernelGGL(k_trsm_block<false>, dim3((N + 255) / 256, nfreq), dim3(256), 0,
+      hipLaunchKernelGGL(k_trsm_block<false>, dim3((N + 15) / 16, nfreq), dim3(64), 0,
                          c->stream, LU, N, kb, nbk, Y, 0, N);
       GW_CHECK_LAUNCH(c, "k_trsm_block");
     }
@@ -750,7 +1008,7 @@ gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
     const int nbk = std::min(NB, N - kb);
     {
       ProfScope ps(c, "inv_trsm_upper");
-      hipLaunchKernelGGL(k_trsm_block<true>, dim3((N + 255) / 256, nfreq), dim3(256), 0,
+      hipLaunchKernelGGL(k_trsm_block<true>, dim3((N + 15) / 16, nfreq), dim3(64), 0,
                          c->stream, LU, N, kb, nbk, Y, 0, N);
       GW_CHECK_LAUNCH(c, "k_trsm_block");
     }
