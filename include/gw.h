@@ -253,17 +253,17 @@ gw_status gw_epsinv_lu(gw_ctx* ctx, int neps, int nfreq, const double* chi0,
  * about a tenth of the spectrum).  With epst(w) = I - V^1/2 chi0(w) V^1/2 and U the
  * eigenvectors of epst(0) with the nb largest eigenvalues:
  *   epst^-1(w) ~= I + U ((U^H epst(w) U)^-1 - I) U^H,  eps^-1 = V^1/2 epst^-1 V^-1/2.
- * The eigenvectors come from a cyclic Jacobi method on the GPU (converged to an
- * off-diagonal norm of 1e-14 of the matrix's); nb = neps gives the exact inverse.
+ * The eigenvectors come from a Householder reduction and divide and conquer on the
+ * GPU (backward error of order neps 2^-53); nb = neps gives the exact inverse.
  *   chi0  (device) complex double[nfreq][neps][neps], Hermitian, frequency 0 first.
  *   vcoul (device) double[neps], every entry > 0.
  *   epsinv (device) out complex double[nfreq][neps][neps], not chi0.
  *   eigenvalues (device) out double[neps] of epst(0) in ascending order, or NULL.
- * Allocates its own buffers (about 16 (nfreq + 2) neps^2 bytes) and synchronises
+ * Allocates its own buffers (about 16 (nfreq + 2.5) neps^2 bytes) and synchronises
  * the context stream.
  * Errors: GW_EINVAL for negative sizes, nb outside 1..neps, neps > 8192, NULL
- * arrays, aliasing, vcoul <= 0, non-finite input; GW_ENOMEM; GW_ESINGULAR from
- * the small inverses.
+ * arrays, aliasing, vcoul <= 0, non-finite input, an epst(0) that is not Hermitian
+ * to rounding; GW_ENOMEM; GW_ESINGULAR from the small inverses.
  */
 gw_status gw_epsinv_lowrank(gw_ctx* ctx, int neps, int nfreq, const double* chi0,
                             const double* vcoul, int nb, double* epsinv, double* eigenvalues);
@@ -275,7 +275,7 @@ gw_status gw_epsinv_lowrank(gw_ctx* ctx, int neps, int nfreq, const double* chi0
  * gw_lowrank_basis -- U (device out complex double[neps][nb], columns the
  *   eigenvectors of epst(0) = I - V^1/2 chi0(0) V^1/2 with the nb largest
  *   eigenvalues, descending) from the static chi0 (device complex double
- *   [neps][neps], Hermitian) by the Jacobi method of gw_epsinv_lowrank;
+ *   [neps][neps], Hermitian) by the method of gw_epsinv_lowrank;
  *   eigenvalues (device out double[neps], ascending) or NULL.  Allocates its own
  *   buffers and synchronises the context stream.  GW_EINVAL for nb outside
  *   1..neps, neps > 8192, NULL arrays, vcoul <= 0, non-finite input.

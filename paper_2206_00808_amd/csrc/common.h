@@ -234,6 +234,9 @@ gw_status epsinv_run(gw_ctx* c, int neps, int nfreq, const double* chi0, const d
                      double* epsinv);
 gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
                              const double* vcoul, double* epsinv);
+// eigenvectors of the nb largest eigenvalues of a Hermitian matrix (eig.hip)
+gw_status herm_eig_top(gw_ctx* c, int N, int nb, cpx<double>* A, cpx<double>* U, cpx<double>* Uh,
+                       double* lam);
 // consumers of eps^-1 (lu.hip): W = eps^-1 v, and the static screened exchange
 gw_status screened_w(gw_ctx* c, int N, int nfreq, const double* epsinv, const double* vcoul,
                      double* w);
