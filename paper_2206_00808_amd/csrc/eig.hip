@@ -3,7 +3,7 @@
 //   1. k_tri_step, one launch per column: Householder reduction to a tridiagonal
 //      matrix.  The reflectors H_j = I - 2 v_j v_j^H (unit v_j) stay as rows of V.
 //   2. The tridiagonal matrix, made real by a diagonal of phases, is divided at
-//      leaves of at most 32 rows (k_dc_leaf, implicit QR) and conquered level by
+//      leaves of at most 16 rows (k_dc_leaf, implicit QR) and conquered level by
 //      level by rank-one updates (Cuppen 1981): deflation (k_dc_deflate), the secular
 //      equation by rational interpolation (k_dc_secular; Bunch, Nielsen and Sorensen
 //      1978), the vectors from the recomputed update vector, which makes them
@@ -11,7 +11,7 @@
 //      Eisenstat 1994), and one product on the FP64 matrix cores (k_dc_gemm).
 //   3. The reflectors are applied to the wanted vectors in blocks of 32 (k_bt_*).
 //
-// All eigenvectors of a matrix of 1000 rows take 11 ms, a tenth of them 10.9; two-sided
+// A tenth of the eigenvectors of a 1000-row matrix take 7.4 ms, all of them 7.8; two-sided
 // Jacobi rounds on 32 x 32 blocks took 50 ms (13 sweeps of 63 rounds of two kernels).
 //
 // Everything is in FP64.  The matrix is first scaled by a power of two to entries below
@@ -28,7 +28,10 @@ typedef double v4f64 __attribute__((ext_vector_type(4)));
 
 namespace {
 constexpr double kU = 1.1102230246251565e-16;  // 2^-53
-constexpr int kLeaf = 32;       // rows of a leaf, at most
+// The scaled matrix has a component of at least one half, so its norm is at least that:
+// what vanishes against it is dropped, however small the leaf or node that it stands in.
+constexpr double kNormMin = 0.5;
+constexpr int kLeaf = 16;       // rows of a leaf, at most
 constexpr int kTriFused = 2048; // rows whose step vectors a workgroup keeps in LDS
 constexpr int kBt = 32;         // reflectors per back-transform block
 }  // namespace
@@ -64,6 +67,13 @@ __device__ __forceinline__ double wprod(double x) {
 __device__ __forceinline__ int wsum_i(int x) {
   for (int h = 32; h > 0; h >>= 1) x += __shfl_xor(x, h);
   return x;
+}
+
+// p[i] where ok, else 0: the load is made in either case, at i or at 0, so that several in
+// a row are in flight at once (a load under a branch waits for the one before)
+__device__ __forceinline__ cpx<double> load_if(const cpx<double>* __restrict__ p, int i, bool ok) {
+  const cpx<double> x = p[ok ? i : 0];
+  return mk(ok ? x.x : 0.0, ok ? x.y : 0.0);
 }
 
 // ------------------------------------------------------------- norms, checks, scaling
@@ -146,114 +156,129 @@ __global__ void k_eig_scale(cpx<double>* __restrict__ A, int N, int ex) {
 }
 
 // ------------------------------------------------------------- tridiagonal reduction
+// The reflector of a column c with |c|^2 = n2 below the diagonal and first entry c1:
+// u = c - beta e_1 with beta = -(c1 / |c1|) |c|, v' = u / |u|.  A column of at most one
+// entry below the diagonal, or of a norm that vanishes against the matrix (entries below
+// one), is left as it is (v' = 0).
+struct Reflector {
+  cpx<double> u1, e;  // first entry of u; the off-diagonal entry that remains
+  double inv;         // 1 / |u|, 0 where the column is left
+};
+__device__ __forceinline__ Reflector reflector(double n2, cpx<double> c1, int n) {
+  Reflector r;
+  r.u1 = c1;
+  r.inv = 0.0;
+  r.e = n == 2 ? c1 : mk(0.0, 0.0);
+  if (n > 2 && n2 > 1e-290) {
+    const double nrm = sqrt(n2), al = sqrt(c1.x * c1.x + c1.y * c1.y);
+    const double ia = nrm / al;
+    const cpx<double> b = al > 0.0 ? scal(c1, ia) : mk(nrm, 0.0);
+    r.e = mk(-b.x, -b.y);
+    r.u1 = c1 + b;
+    r.inv = 1.0 / sqrt(2.0 * nrm * (nrm + al));
+  }
+  return r;
+}
+
 // The vectors of step j over rows j..N-1 (index 0 is row j): from the last reflector v
 // and y = A v the update vector w = 2 (y - (v^H y) v), the column j of the updated
-// matrix A - v w^H - w v^H, and its reflector: u = c - beta e_1 with
-// beta = -(c_1 / |c_1|) |c|, v' = u / |u|.  A column of at most one entry below the
-// diagonal, or of a norm that vanishes against the matrix, is left as it is (v' = 0).
-// red: LDS of 4 doubles per wavefront.  Written: w, vo (= v), vn; d[j], e[j] by `lead`.
-template <int T, bool LDS>
+// matrix A - v w^H - w v^H, and its reflector.  A thread keeps its Q entries of each in
+// registers, so that all loads are in flight at once; emit(i, v, w, v') receives them.
+// red: LDS of 2 T / 64 + 2 doubles.  d[j], e[j] are written by `lead`.
+template <int T, int Q, typename F>
 __device__ __forceinline__ void tri_vectors(const cpx<double>* __restrict__ A, int N, int j,
                                             const cpx<double>* __restrict__ vprev,
-                                            const cpx<double>* __restrict__ yprev,
-                                            cpx<double>* w, cpx<double>* vo, cpx<double>* vn,
-                                            double* red, double* __restrict__ d,
-                                            cpx<double>* __restrict__ e, bool lead) {
+                                            const cpx<double>* __restrict__ yprev, double* red,
+                                            double* __restrict__ d, cpx<double>* __restrict__ e,
+                                            bool lead, F emit) {
   const int t = threadIdx.x, n = N - j, lane = t & 63, wave = t >> 6;
   constexpr int W = T / 64;
   const cpx<double>* row = A + (size_t)j * N + j;
-  cpx<double> v0 = mk(0.0, 0.0), w0 = v0;
-  double s = 0.0;
+  const cpx<double> zero = mk(0.0, 0.0);
+  cpx<double> v[Q], w[Q], c[Q], vj = zero, wj = zero;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = t + T * q;
+    const bool in = i < n, pd = in && j > 0;
+    v[q] = pd ? vprev[j + i] : zero;
+    w[q] = pd ? yprev[j + i] : zero;
+    c[q] = in ? row[i] : zero;
+  }
   if (j > 0) {
-    const cpx<double> vj = vprev[j], yj = yprev[j];
-    for (int i = t; i < n; i += T) {
-      const cpx<double> v = vprev[j + i], y = yprev[j + i];
-      if (LDS) {
-        vo[i] = v;
-        w[i] = y;
-      }
-      s += v.x * y.x + v.y * y.y;
-    }
+    vj = vprev[j];
+    wj = yprev[j];
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) s += v[q].x * w[q].x + v[q].y * w[q].y;
     s = wsum(s);
     if (lane == 0) red[wave] = s;
     __syncthreads();
     s = 0.0;
 #pragma unroll
     for (int q = 0; q < W; ++q) s += red[q];
-    v0 = vj;
-    w0 = scal(yj - scal(vj, s), 2.0);
+    wj = scal(wj - scal(vj, s), 2.0);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) w[q] = scal(w[q] - scal(v[q], s), 2.0);
   }
   double n2 = 0.0;
-  for (int i = t; i < n; i += T) {
-    const cpx<double> a = row[i];
-    cpx<double> c = mk(a.x, -a.y);
-    if (j > 0) {
-      const cpx<double> v = LDS ? vo[i] : vprev[j + i];
-      const cpx<double> y = LDS ? w[i] : yprev[j + i];
-      const cpx<double> ww = scal(y - scal(v, s), 2.0);
-      w[i] = ww;
-      c = c - cmulc(w0, v) - cmulc(v0, ww);
-    } else if (LDS) {
-      w[i] = mk(0.0, 0.0);
-      vo[i] = mk(0.0, 0.0);
-    }
-    vn[i] = c;
-    if (i > 0) n2 += c.x * c.x + c.y * c.y;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    c[q] = mk(c[q].x, -c[q].y) - cmulc(wj, v[q]) - cmulc(vj, w[q]);
+    if (q > 0 || t > 0) n2 += c[q].x * c[q].x + c[q].y * c[q].y;
   }
   n2 = wsum(n2);
   if (lane == 0) red[W + wave] = n2;
+  if (t == 1) {
+    red[2 * W] = c[0].x;
+    red[2 * W + 1] = c[0].y;
+  }
   __syncthreads();
   n2 = 0.0;
 #pragma unroll
   for (int q = 0; q < W; ++q) n2 += red[W + q];
-  const cpx<double> c1 = n > 1 ? vn[1] : mk(0.0, 0.0);
-  const double dj = vn[0].x;
-  __syncthreads();  // vn[0] and vn[1] are read before they change
-  const bool skip = n <= 2 || !(n2 > 1e-290);
-  double inv = 0.0;
-  cpx<double> u1 = c1, beta = c1;
-  if (!skip) {
-    const double nrm = sqrt(n2), al = hypot(c1.x, c1.y);
-    const cpx<double> ph = al > 0.0 ? scal(c1, 1.0 / al) : mk(1.0, 0.0);
-    beta = scal(ph, -nrm);
-    u1 = scal(ph, al + nrm);
-    inv = 1.0 / sqrt(2.0 * nrm * (nrm + al));
-  }
-  for (int i = t; i < n; i += T) {
-    const cpx<double> u = i == 0 ? mk(0.0, 0.0) : i == 1 ? u1 : vn[i];
-    vn[i] = skip ? mk(0.0, 0.0) : scal(u, inv);
-  }
+  const Reflector r = reflector(n2, mk(red[2 * W], red[2 * W + 1]), n);
   if (lead && t == 0) {
-    d[j] = dj;
-    if (n > 1) e[j] = n > 2 && skip ? mk(0.0, 0.0) : beta;
+    d[j] = c[0].x;
+    if (n > 1) e[j] = r.e;
   }
-  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = t + T * q;
+    const cpx<double> u = i == 0 ? zero : i == 1 ? r.u1 : c[q];
+    if (i < n) emit(i, v[q], w[q], scal(u, r.inv));
+  }
 }
 
 // Step j: the rows below j of the matrix take the pending rank-two update and their
-// product with the new reflector, one wavefront per row; the first 512 columns of the
-// row are fetched before the vectors are formed.
+// product with the new reflector, one wavefront per row; its row, up to 1024
+// columns, is fetched before the vectors are formed.  Up to 256 Q rows every workgroup forms
+// the vectors anew in its LDS, which costs less than a second launch; with Q = 0 they
+// come from global memory (k_tri_vec).
 //
 // One kernel boundary per column orders the steps (each row of y needs the whole new
-// reflector, and the next reflector all of y); every workgroup forms the vectors anew,
-// which costs less than a second launch.  Bound: the latency of that chain, 8.0 us per
-// column over the 1000 columns of a 1000-row matrix.
-constexpr int kPre = 8;
-template <bool FUSED>
+// reflector, and the next reflector all of y).  Bound: the latency of that chain,
+// 6.0 us per column over the 1000 columns of a 1000-row matrix (7.4 above 512 rows, 4.1
+// below 256; 8.0 with the vectors' passes through LDS).  Of the 7.4, the launch and the
+// vectors are 4.3, the stores 0.7.
+// first group of four rows of step j's grid: a multiple of the XCD count, so that a
+// group, which is workgroup (group mod 8) of every step, stays with one XCD's L2
+__host__ __device__ __forceinline__ int tri_group(int j) { return (j + 1) / 4 / kXcd * kXcd; }
+template <int Q>
 __global__ void __launch_bounds__(256) k_tri_step(cpx<double>* __restrict__ A, int N, int j,
                                                   const cpx<double>* __restrict__ vprev,
                                                   const cpx<double>* __restrict__ yprev,
-                                                  cpx<double>* __restrict__ wg,
+                                                  const cpx<double>* __restrict__ wg,
                                                   cpx<double>* __restrict__ vout,
                                                   cpx<double>* __restrict__ yout,
                                                   double* __restrict__ d,
                                                   cpx<double>* __restrict__ e) {
   extern __shared__ char smem[];
-  __shared__ double red[8];
+  __shared__ double red[10];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, n = N - j;
-  const int i = 1 + blockIdx.x * 4 + wave;  // row j + i
-  const bool live = i < n;
+  const int i = tri_group(j) * 4 + blockIdx.x * 4 + wave - j;  // row j + i
+  const bool live = i > 0 && i < n;
   cpx<double>* row = A + (size_t)(j + (live ? i : 0)) * N + j;
+  constexpr int kPre = Q == 0 ? 8 : Q < 4 ? 4 * Q : 16;
   cpx<double> a[kPre];
 #pragma unroll
   for (int q = 0; q < kPre; ++q) {
@@ -261,15 +286,22 @@ __global__ void __launch_bounds__(256) k_tri_step(cpx<double>* __restrict__ A, i
     a[q] = live && k < n ? row[k] : mk(0.0, 0.0);
   }
   const cpx<double>*w, *vo, *vn;
-  if (FUSED) {
+  if (Q > 0) {
     auto* ls = reinterpret_cast<cpx<double>*>(smem);
-    tri_vectors<256, true>(A, N, j, vprev, yprev, ls, ls + n, ls + 2 * n, red, d, e,
-                           blockIdx.x == 0);
+    const bool lead = blockIdx.x == 0;
+    tri_vectors<256, Q ? Q : 1>(A, N, j, vprev, yprev, red, d, e, lead,
+                                [&](int k, cpx<double> v, cpx<double> u, cpx<double> x) {
+                                  ls[k] = u;
+                                  ls[n + k] = v;
+                                  ls[2 * n + k] = x;
+                                  if (lead) vout[j + k] = x;
+                                });
+    __syncthreads();
     w = ls;
     vo = ls + n;
     vn = ls + 2 * n;
-    if (blockIdx.x == 0)
-      for (int k = t; k < N; k += 256) vout[k] = k < j ? mk(0.0, 0.0) : vn[k - j];
+    if (lead)
+      for (int k = t; k < j; k += 256) vout[k] = mk(0.0, 0.0);
   } else {
     w = wg + j;
     vo = vprev + j;
@@ -312,13 +344,19 @@ __global__ void __launch_bounds__(256) k_tri_step(cpx<double>* __restrict__ A, i
 // The vectors of a step above kTriFused rows, where every workgroup's own copy would not
 // fit its LDS: one workgroup forms them in global memory.
 __global__ void __launch_bounds__(1024) k_tri_vec(const cpx<double>* __restrict__ A, int N, int j,
-                                                  const cpx<double>* vprev,
-                                                  const cpx<double>* yprev, cpx<double>* wg,
-                                                  cpx<double>* vout, double* __restrict__ d,
+                                                  const cpx<double>* __restrict__ vprev,
+                                                  const cpx<double>* __restrict__ yprev,
+                                                  cpx<double>* __restrict__ wg,
+                                                  cpx<double>* __restrict__ vout,
+                                                  double* __restrict__ d,
                                                   cpx<double>* __restrict__ e) {
-  __shared__ double red[32];
+  __shared__ double red[34];
   for (int k = threadIdx.x; k < j; k += 1024) vout[k] = mk(0.0, 0.0);
-  tri_vectors<1024, false>(A, N, j, vprev, yprev, wg + j, nullptr, vout + j, red, d, e, true);
+  tri_vectors<1024, 8>(A, N, j, vprev, yprev, red, d, e, true,
+                       [&](int k, cpx<double>, cpx<double> u, cpx<double> x) {
+                         wg[j + k] = u;
+                         vout[j + k] = x;
+                       });
 }
 
 // |e| and the phases D_0 = 1, D_{j+1} = D_j e_j / |e_j| that make the matrix real, by one
@@ -371,17 +409,30 @@ __host__ __device__ __forceinline__ int dc_bound(int q, int N, int leaves) {
   return (int)((long long)q * N / leaves);
 }
 
+// 1 / sqrt(x) for normal positive x: the hardware estimate and two Newton steps
+__device__ __forceinline__ double rsq_newton(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+  return fma(0.5 * r, fma(-x * r, r, 1.0), r);
+}
+
 // Implicit symmetric QR with Wilkinson's shift on one leaf per wavefront: every lane
-// carries the scalar recurrence, lane r the r-th components of the vectors.
+// carries the scalar recurrence in registers (the entries ahead are loaded from LDS a
+// step early), lane r the r-th components of the vectors.  Bound: the latency of its
+// rotations in series, about 250 for 16 rows: 75 us.  Leaves of 32 rows took 264 us (494
+// with the entries in LDS and library square roots and divisions), more than the level of
+// merges that they save.
 __global__ void __launch_bounds__(64) k_dc_leaf(const double* __restrict__ d,
                                                 const double* __restrict__ e, int N, int leaves,
                                                 double* __restrict__ lam, double* __restrict__ Qt,
                                                 int* __restrict__ flag) {
   __shared__ double q[kLeaf][kLeaf + 1];
-  __shared__ double sd[kLeaf], se[kLeaf];
+  __shared__ double sd[kLeaf + 2], se[kLeaf + 2];
   const int t = threadIdx.x, b = blockIdx.x;
   const int lo = dc_bound(b, N, leaves), hi = dc_bound(b + 1, N, leaves), n = hi - lo;
   const bool own = t < n;
+  if (t < kLeaf + 2) sd[t] = se[t] = 0.0;
+  __syncthreads();
   if (own) {
     double x = d[lo + t];
     if (t == 0 && lo > 0) x -= e[lo - 1];
@@ -393,42 +444,54 @@ __global__ void __launch_bounds__(64) k_dc_leaf(const double* __restrict__ d,
   __syncthreads();
   double nrm = 0.0;
   for (int k = 0; k < n; ++k) nrm = fmax(nrm, fmax(fabs(sd[k]), fabs(se[k])));
-  const double tol = kU * nrm;
+  const double tol = kU * fmax(nrm, kNormMin);
   int hiq = n - 1, budget = 40 * n;
   while (hiq > 0 && budget-- > 0) {
-    if (fabs(se[hiq - 1]) <= tol) {
-      --hiq;
-      continue;
+    // the last unreduced block [p, hiq]
+    const unsigned long long big = __ballot(t < hiq && fabs(se[min(t, kLeaf)]) > tol);
+    if (big == 0) {
+      hiq = 0;
+      break;
     }
-    int p = hiq - 1;
-    while (p > 0 && fabs(se[p - 1]) > tol) --p;
+    hiq = 64 - __builtin_clzll(big);
+    const unsigned long long gap = ~big & ((1ull << hiq) - 1);
+    const int p = gap ? 64 - __builtin_clzll(gap) : 0;
     const double a = sd[hiq - 1], bb = se[hiq - 1], c = sd[hiq];
     const double h = 0.5 * (a - c);
-    const double mu = c - bb * bb / (h + copysign(hypot(h, bb), h));
-    double x = sd[p] - mu, z = se[p];
+    const double mu = c - bb * bb / (h + copysign(sqrt(h * h + bb * bb), h));
+    double dk = sd[p], ek = se[p], x = dk - mu, z = ek;
+    double dl = sd[p + 1], en = se[p + 1];
+    double u = own ? q[p][t] : 0.0, w = own ? q[p + 1][t] : 0.0;
     for (int k = p; k < hiq; ++k) {
-      const double r = hypot(x, z);
-      const double cs = r > 0.0 ? x / r : 1.0, sn = r > 0.0 ? z / r : 0.0;
-      const double dk = sd[k], dl = sd[k + 1], ek = se[k], en = se[k + 1];
-      __syncthreads();
+      const double dn = sd[k + 2], ef = se[k + 2];
+      const double wn = own && k + 2 <= hiq ? q[k + 2][t] : 0.0;
+      const double r2 = x * x + z * z;
+      // below 1e-290 both vanish against the leaf's norm
+      const bool act = r2 > 1e-290;
+      const double ri = act ? rsq_newton(r2) : 0.0;
+      const double cs = act ? x * ri : 1.0, sn = z * ri;
       const double g = 2.0 * cs * sn * ek, c2 = cs * cs, s2 = sn * sn;
       const double nek = (c2 - s2) * ek - cs * sn * (dk - dl);
       if (t == 0) {
-        if (k > p) se[k - 1] = r;
+        if (k > p) se[k - 1] = r2 * ri;
         sd[k] = c2 * dk + g + s2 * dl;
-        sd[k + 1] = s2 * dk - g + c2 * dl;
-        se[k] = nek;
-        if (k + 1 < hiq) se[k + 1] = cs * en;
       }
-      if (own) {
-        const double u = q[k][t], w = q[k + 1][t];
-        q[k][t] = cs * u + sn * w;
-        q[k + 1][t] = cs * w - sn * u;
-      }
+      if (own) q[k][t] = cs * u + sn * w;
+      u = cs * w - sn * u;
+      w = wn;
+      dk = s2 * dk - g + c2 * dl;
       x = nek;
+      ek = cs * en;
       z = sn * en;
-      __syncthreads();
+      dl = dn;
+      en = ef;
     }
+    if (t == 0) {
+      se[hiq - 1] = x;
+      sd[hiq] = dk;
+    }
+    if (own) q[hiq][t] = u;
+    __syncthreads();
   }
   if (t == 0 && hiq > 0) *flag = 1;
   if (own) {
@@ -457,18 +520,18 @@ struct DcWork {
 // The rank-one update of a merge: z from the last row of the left vectors and the first
 // of the right ones, in ascending order of the eigenvalues; an entry whose weight
 // vanishes against the norm is deflated, and one of a pair of eigenvalues so close that
-// rotating the weight to the other costs nothing.  The scan over pairs is serial.
+// rotating the weight to the other costs nothing.  One wavefront scans 64 entries at a
+// time: the tests of neighbours are made at once, and only where one succeeds does it go
+// through the entries one by one (a rotation changes the next test).
+// 10 us at 1000 entries, 91 with one lane going through all of them.
 __global__ void __launch_bounds__(256) k_dc_deflate(const double* __restrict__ lam,
                                                     const double* __restrict__ e,
                                                     const double* __restrict__ Qt, int N,
                                                     int leaves, int s, DcWork W) {
-  constexpr int CH = 512;
-  __shared__ double cd[CH], cz[CH];
-  __shared__ int ci[CH];
   __shared__ double red[256];
   const int t = threadIdx.x, b = blockIdx.x;
   const int lo = dc_bound(2 * s * b, N, leaves), mid = dc_bound(2 * s * b + s, N, leaves),
-            hi = dc_bound(2 * s * b + 2 * s, N, leaves), n = hi - lo;
+            hi = dc_bound(2 * s * b + 2 * s, N, leaves);
   const double rho = 2.0 * e[mid - 1];
   double big = rho;
   for (int i = lo + t; i < hi; i += 256) {
@@ -493,64 +556,92 @@ __global__ void __launch_bounds__(256) k_dc_deflate(const double* __restrict__ l
     if (t < h) red[t] = fmax(red[t], red[t + h]);
     __syncthreads();
   }
-  const double tol = 8.0 * kU * red[0];
-  int k = 0, nd = 0, nr = 0, sp = -1;
+  if (t >= 64) return;
+  const double tol = 8.0 * kU * fmax(red[0], kNormMin);
+  int k = lo, nd = hi, nr = lo, sp = -1;  // sp: the row of the entry held back
   double dp = 0.0, zp = 0.0;
-  for (int c0 = lo; c0 < hi; c0 += CH) {
-    const int m = min(CH, hi - c0);
-    __syncthreads();
-    for (int i = t; i < m; i += 256) {
-      cd[i] = W.ds[c0 + i];
-      cz[i] = W.zs[c0 + i];
-      ci[i] = W.is[c0 + i];
+  auto close = [&](double d0, double z0, double d1, double z1) {
+    return fabs((d1 - d0) * z1 * z0) <= tol * (z1 * z1 + z0 * z0);
+  };
+  for (int c0 = lo; c0 < hi; c0 += 64) {
+    const bool in = c0 + t < hi;
+    const double dj = in ? W.ds[c0 + t] : 0.0, zj = in ? W.zs[c0 + t] : 0.0;
+    const int sj = in ? W.is[c0 + t] : 0;
+    const bool heavy = in && rho * fabs(zj) > tol;
+    const unsigned long long live = __ballot(heavy), below = live & ((1ull << t) - 1);
+    const unsigned long long out = __ballot(in && !heavy);
+    if (in && !heavy) {
+      const int x = nd - 1 - __popcll(out & ((1ull << t) - 1));
+      W.dl[x] = dj;
+      W.src[x] = sj;
     }
-    __syncthreads();
-    if (t != 0) continue;
-    for (int i = 0; i < m; ++i) {
-      const double dj = cd[i], zj = cz[i];
-      const int sj = ci[i];
-      if (rho * fabs(zj) <= tol) {
-        ++nd;
-        W.dl[hi - nd] = dj;
-        W.src[hi - nd] = sj;
-        continue;
+    nd -= __popcll(out);
+    if (live == 0) continue;
+    // the heavy entry before this one: of this piece, or the one held back
+    const int pl = below ? 63 - __builtin_clzll(below) : t;
+    const double qd = __shfl(dj, pl), qz = __shfl(zj, pl);
+    const int qs = __shfl(sj, pl);
+    const double d0 = below ? qd : dp, z0 = below ? qz : zp;
+    const int s0 = below ? qs : sp;
+    if (__ballot(heavy && s0 >= 0 && close(d0, z0, dj, zj)) == 0) {
+      // nothing rotates: every heavy entry passes on the one before it
+      const int held = sp >= 0 ? 1 : 0;
+      if (heavy && s0 >= 0) {
+        const int x = k + __popcll(below) - (1 - held);
+        W.dl[x] = d0;
+        W.w[x] = z0;
+        W.src[x] = s0;
       }
+      k += __popcll(live) - (1 - held);
+      const int l = 63 - __builtin_clzll(live);
+      dp = lane_val(dj, l);
+      zp = lane_val(zj, l);
+      sp = __builtin_amdgcn_readlane(sj, l);
+      continue;
+    }
+    for (unsigned long long m = live; m; m &= m - 1) {
+      const int l = __builtin_ctzll(m);
+      const double d1 = lane_val(dj, l), z1 = lane_val(zj, l);
+      const int s1 = __builtin_amdgcn_readlane(sj, l);
       if (sp >= 0) {
-        const double t2 = zj * zj + zp * zp;
-        if (fabs((dj - dp) * zj * zp) <= tol * t2) {
-          const double tau = sqrt(t2), c = zj / tau, sn = zp / tau;
-          W.ra[lo + nr] = sp;
-          W.rb[lo + nr] = sj;
-          W.rc[lo + nr] = c;
-          W.rs[lo + nr] = sn;
+        const double t2 = z1 * z1 + zp * zp;
+        if (close(dp, zp, d1, z1)) {
+          const double tau = sqrt(t2), c = z1 / tau, sn = zp / tau;
+          --nd;
+          if (t == 0) {
+            W.ra[nr] = sp;
+            W.rb[nr] = s1;
+            W.rc[nr] = c;
+            W.rs[nr] = sn;
+            W.dl[nd] = dp * c * c + d1 * sn * sn;
+            W.src[nd] = sp;
+          }
           ++nr;
-          ++nd;
-          W.dl[hi - nd] = dp * c * c + dj * sn * sn;
-          W.src[hi - nd] = sp;
-          dp = dp * sn * sn + dj * c * c;
+          dp = dp * sn * sn + d1 * c * c;
           zp = tau;
-          sp = sj;
+          sp = s1;
           continue;
         }
-        W.dl[lo + k] = dp;
-        W.w[lo + k] = zp;
-        W.src[lo + k] = sp;
+        if (t == 0) {
+          W.dl[k] = dp;
+          W.w[k] = zp;
+          W.src[k] = sp;
+        }
         ++k;
       }
-      dp = dj;
-      zp = zj;
-      sp = sj;
+      dp = d1;
+      zp = z1;
+      sp = s1;
     }
   }
   if (t == 0) {
     if (sp >= 0) {
-      W.dl[lo + k] = dp;
-      W.w[lo + k] = zp;
-      W.src[lo + k] = sp;
-      ++k;
+      W.dl[k] = dp;
+      W.w[k] = zp;
+      W.src[k] = sp;
     }
-    W.k[b] = k;
-    W.nrot[b] = nr;
+    W.k[b] = k - lo + (sp >= 0 ? 1 : 0);
+    W.nrot[b] = nr - lo;
     W.rho[b] = rho;
   }
 }
@@ -747,15 +838,28 @@ __global__ void __launch_bounds__(256) k_dc_gemm(const double* __restrict__ Ut,
   const int lane = t & 63, wave = t >> 6, l16 = lane & 15, lk = lane >> 4;
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
   v4f64 acc[2][2] = {};
+  // a thread's share of a stage, fetched while the one before is multiplied
+  double fa[4], fb[4];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = t / KB + 16 * q, j = k0 + t % KB;
+      fa[q] = i0 + i < k && j < k ? Ut[(size_t)(lo + i0 + i) * N + lo + j] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int j = k0 + t / 64 + 4 * q, g = g0 + t % 64;
+      fb[q] = j < k && g < n ? Qt[(size_t)W.src[lo + j] * N + lo + g] : 0.0;
+    }
+  };
+  fetch(0);
   for (int k0 = 0; k0 < k; k0 += KB) {
-    for (int e = t; e < KB * 64; e += 256) {
-      const int i = e / KB, j = e % KB;
-      sa[j][i] = i0 + i < k && k0 + j < k ? Ut[(size_t)(lo + i0 + i) * N + lo + k0 + j] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      sa[t % KB][t / KB + 16 * q] = fa[q];
+      sb[t / 64 + 4 * q][t % 64] = fb[q];
     }
-    for (int e = t; e < KB * 64; e += 256) {
-      const int j = e / 64, g = e % 64;
-      sb[j][g] = k0 + j < k && g0 + g < n ? Qt[(size_t)W.src[lo + k0 + j] * N + lo + g0 + g] : 0.0;
-    }
+    fetch(k0 + KB);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < KB; j += 4) {
@@ -789,55 +893,75 @@ __global__ void k_bt_start(const double* __restrict__ Qt, const cpx<double>* __r
   Z[e] = scal(D[g], Qt[(size_t)(N - 1 - r) * N + g]);
 }
 
-// T of H_{j0} .. H_{j0+31} = I - V T V^H: the inverse of 1/2 I plus the strictly upper
-// part of V^H V, one workgroup per block
-__global__ void __launch_bounds__(1024) k_bt_tfac(const cpx<double>* __restrict__ V, int N, int R,
-                                                  cpx<double>* __restrict__ T) {
+// V^H V of a block of reflectors over one of `splits` column ranges
+constexpr int kTfSplit = 8;
+__global__ void __launch_bounds__(1024) k_bt_tgram(const cpx<double>* __restrict__ V, int N, int R,
+                                                   cpx<double>* __restrict__ part) {
   __shared__ cpx<double> sv[kBt][kBt + 1];
-  __shared__ cpx<double> sg[kBt][kBt + 1];
-  __shared__ cpx<double> sx[kBt][kBt + 1];
   const int t = threadIdx.x, m = t / kBt, c = t % kBt, j0 = blockIdx.x * kBt;
   cpx<double> g = mk(0.0, 0.0);
-  for (int i0 = j0; i0 < N; i0 += kBt) {
-    const int i = i0 + c;
-    sv[m][c] = j0 + m < R && i < N ? V[(size_t)(j0 + m) * N + i] : mk(0.0, 0.0);
+  auto fetch = [&](int i) {
+    return j0 + m < R && i < N ? V[(size_t)(j0 + m) * N + i] : mk(0.0, 0.0);
+  };
+  const int i1 = j0 + blockIdx.y * kBt, step = kBt * gridDim.y;
+  cpx<double> next = fetch(i1 + c);
+  for (int i0 = i1; i0 < N; i0 += step) {
+    sv[m][c] = next;
     __syncthreads();
+    next = fetch(i0 + step + c);
 #pragma unroll 8
     for (int x = 0; x < kBt; ++x) g = g + cmulc(sv[m][x], sv[c][x]);
     __syncthreads();
   }
-  sg[m][c] = g;
-  __syncthreads();
-  if (t < kBt) {
-    for (int i = kBt - 1; i >= 0; --i) {
-      cpx<double> x = mk(i == t ? 1.0 : 0.0, 0.0);
-      for (int q = i + 1; q < kBt; ++q) x = x - cmul(sg[i][q], sx[q][t]);
-      sx[i][t] = i > t ? mk(0.0, 0.0) : scal(x, 2.0);
-    }
-  }
-  __syncthreads();
-  T[((size_t)blockIdx.x * kBt + m) * kBt + c] = sx[m][c];
+  part[((size_t)blockIdx.x * gridDim.y + blockIdx.y) * kBt * kBt + t] = g;
 }
 
-constexpr int kBtSpan = 256;  // columns of Z per workgroup
-// partial V^H Z over one span: part[span][b][m], four wavefronts of 64 columns
-__global__ void __launch_bounds__(256) k_bt_gram(const cpx<double>* __restrict__ V,
+// T of H_{j0} .. H_{j0+31} = I - V T V^H: the inverse of 1/2 I plus the strictly upper
+// part of V^H V, one workgroup per block, rows from the last
+__global__ void __launch_bounds__(1024) k_bt_tfac(const cpx<double>* __restrict__ part, int splits,
+                                                  cpx<double>* __restrict__ T) {
+  __shared__ cpx<double> sg[kBt][kBt + 1];
+  __shared__ cpx<double> sx[2][kBt];
+  const int t = threadIdx.x, m = t / kBt, c = t % kBt;
+  cpx<double> g = mk(0.0, 0.0);
+  for (int q = 0; q < splits; ++q)
+    g = g + part[((size_t)blockIdx.x * splits + q) * kBt * kBt + t];
+  sg[m][c] = g;
+  cpx<double> acc = mk(m == c ? 1.0 : 0.0, 0.0), x = acc;
+  for (int i = kBt - 1; i >= 0; --i) {
+    if (m == i) {
+      x = scal(acc, 2.0);
+      sx[i & 1][c] = x;
+    }
+    __syncthreads();
+    if (m < i) acc = acc - cmul(sg[m][i], sx[i & 1][c]);
+  }
+  T[(size_t)blockIdx.x * kBt * kBt + t] = x;
+}
+
+// Columns of Z per workgroup, 16 per wavefront: a block of reflectors is two dependent
+// launches, and 100 vectors of 1000 rows give them 56 and 112 workgroups, 5.4 and 8.2 us
+// (28 workgroups of 64 columns per wavefront: 13 and 18).
+constexpr int kBtSpan = 64, kBtGram = 128;
+// partial V^H Z over one span: part[span][b][m]
+__global__ void __launch_bounds__(512) k_bt_gram(const cpx<double>* __restrict__ V,
                                                  const cpx<double>* __restrict__ Z, int N, int R,
                                                  int nb, int j0, cpx<double>* __restrict__ part) {
-  __shared__ cpx<double> sg[4][16][kBt + 1];
+  __shared__ cpx<double> sg[8][16][kBt + 1];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, l16 = lane & 15, lk = lane >> 4;
-  const int b0 = blockIdx.x * 16, i0 = j0 + blockIdx.y * kBtSpan + wave * 64;
+  const int b0 = blockIdx.x * 16, i0 = j0 + blockIdx.y * kBtGram + wave * 16;
   const bool rz = b0 + l16 < nb, r0 = j0 + l16 < R, r1 = j0 + 16 + l16 < R;
   const cpx<double>* z = Z + (size_t)(rz ? b0 + l16 : 0) * N;
   const cpx<double>* va = V + (size_t)(r0 ? j0 + l16 : 0) * N;
   const cpx<double>* vb = V + (size_t)(r1 ? j0 + 16 + l16 : 0) * N;
   const cpx<double> o = mk(0.0, 0.0);
   v4f64 re[2] = {}, im[2] = {};
-#pragma unroll 4
-  for (int k = 0; k < 64; k += 4) {
+#pragma unroll
+  for (int k = 0; k < 16; k += 4) {
     const int i = i0 + k + lk;
     const bool in = i < N;
-    const cpx<double> zz = in && rz ? z[i] : o, x0 = in && r0 ? va[i] : o, x1 = in && r1 ? vb[i] : o;
+    const cpx<double> zz = load_if(z, i, in && rz), x0 = load_if(va, i, in && r0),
+                      x1 = load_if(vb, i, in && r1);
     // rows: vectors b, columns: reflectors
     re[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(zz.x, x0.x, re[0], 0, 0, 0);
     re[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(zz.x, x1.x, re[1], 0, 0, 0);
@@ -853,10 +977,11 @@ __global__ void __launch_bounds__(256) k_bt_gram(const cpx<double>* __restrict__
 #pragma unroll
     for (int r = 0; r < 4; ++r) sg[wave][lk + 4 * r][16 * h + l16] = mk(re[h][r], im[h][r]);
   __syncthreads();
-  for (int e = t; e < 16 * kBt; e += 256) {
-    const int b = e / kBt, m = e % kBt;
+  {
+    const int e = t, b = e / kBt, m = e % kBt;
     part[(((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 + b) * kBt + m] =
-        (sg[0][b][m] + sg[1][b][m]) + (sg[2][b][m] + sg[3][b][m]);
+        ((sg[0][b][m] + sg[1][b][m]) + (sg[2][b][m] + sg[3][b][m])) +
+        ((sg[4][b][m] + sg[5][b][m]) + (sg[6][b][m] + sg[7][b][m]));
   }
 }
 
@@ -870,43 +995,60 @@ __global__ void __launch_bounds__(256) k_bt_apply(const cpx<double>* __restrict_
   __shared__ cpx<double> st[kBt][kBt + 1];
   __shared__ cpx<double> sm[16][kBt + 1];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, l16 = lane & 15, lk = lane >> 4;
-  const int b0 = blockIdx.x * 16, i0 = j0 + blockIdx.y * kBtSpan + wave * 64;
-  for (int e = t; e < kBt * kBt; e += 256) st[e / kBt][e % kBt] = T[(size_t)j0 * kBt + e];
+  const int b0 = blockIdx.x * 16, i0 = j0 + blockIdx.y * kBtSpan + wave * 16;
+  const cpx<double> o = mk(0.0, 0.0);
+  const int i = i0 + l16;
+  cpx<double> v[kBt / 4];
+#pragma unroll
+  for (int k = 0; k < kBt / 4; ++k)
+    v[k] = load_if(V + (size_t)min(j0 + 4 * k + lk, R - 1) * N, i, i < N && j0 + 4 * k + lk < R);
+  cpx<double> z[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    z[r] = load_if(Z + (size_t)min(b0 + lk + 4 * r, nb - 1) * N, i, i < N);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = t + 256 * q;
+    st[e / kBt][e % kBt] = T[(size_t)j0 * kBt + e];
+  }
   for (int e = t; e < 16 * kBt; e += 256) {
-    cpx<double> x = mk(0.0, 0.0);
-    for (int q = 0; q < nspan; ++q)
-      x = x + part[((size_t)q * gridDim.x + blockIdx.x) * 16 * kBt + e];
+    const cpx<double>* p = part + (size_t)blockIdx.x * 16 * kBt + e;
+    const size_t sp = (size_t)gridDim.x * 16 * kBt;
+    cpx<double> x = o;
+    for (int q0 = 0; q0 < nspan; q0 += 8) {
+      cpx<double> y[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) y[q] = load_if(p + min(q0 + q, nspan - 1) * sp, 0, q0 + q < nspan);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x = x + y[q];
+    }
     sg[e / kBt][e % kBt] = x;
   }
   __syncthreads();
   for (int e = t; e < 16 * kBt; e += 256) {
     const int b = e / kBt, m = e % kBt;
-    cpx<double> x = mk(0.0, 0.0);
-    for (int q = m; q < kBt; ++q) x = x + cmul(st[m][q], sg[b][q]);
-    sm[b][m] = x;
+    cpx<double> x = o, y = o;  // T is zero below its diagonal
+#pragma unroll
+    for (int q = 0; q < kBt; q += 2) {
+      x = x + cmul(st[m][q], sg[b][q]);
+      y = y + cmul(st[m][q + 1], sg[b][q + 1]);
+    }
+    sm[b][m] = x + y;
   }
   __syncthreads();
-  const cpx<double> o = mk(0.0, 0.0);
-  for (int q = 0; q < 4; ++q) {
-    const int i = i0 + 16 * q + l16;
-    v4f64 re = {}, im = {};
+  v4f64 re = {}, im = {};
 #pragma unroll
-    for (int k = 0; k < kBt; k += 4) {
-      const cpx<double> v = i < N && j0 + k + lk < R ? V[(size_t)(j0 + k + lk) * N + i] : o;
-      const cpx<double> x = sm[l16][k + lk];
-      re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, v.x, re, 0, 0, 0);
-      im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, v.y, im, 0, 0, 0);
-      re = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.y, v.y, re, 0, 0, 0);
-      im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, v.x, im, 0, 0, 0);
-    }
+  for (int k = 0; k < kBt / 4; ++k) {
+    const cpx<double> x = sm[l16][4 * k + lk];
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, v[k].x, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, v[k].y, im, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.y, v[k].y, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, v[k].x, im, 0, 0, 0);
+  }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int b = b0 + lk + 4 * r;
-      if (b < nb && i < N) {
-        cpx<double>* p = Z + (size_t)b * N + i;
-        *p = *p - mk(re[r], im[r]);
-      }
-    }
+  for (int r = 0; r < 4; ++r) {
+    const int b = b0 + lk + 4 * r;
+    if (b < nb && i < N) Z[(size_t)b * N + i] = z[r] - mk(re[r], im[r]);
   }
 }
 
@@ -931,12 +1073,13 @@ gw_status herm_eig_top(gw_ctx* c, int N, int nb, cpx<double>* A, cpx<double>* U,
   int levels = 0;
   while (((N + (1 << levels) - 1) >> levels) > kLeaf) ++levels;
   const int leaves = 1 << levels, R = std::max(0, N - 2), nblk = (R + kBt - 1) / kBt;
-  const int nspan = (N + kBtSpan - 1) / kBtSpan, nbt = (nb + 15) / 16;
+  const int nspan = (N + kBtGram - 1) / kBtGram, nbt = (nb + 15) / 16;
   const int nparts = (int)std::min<size_t>(1024, (nn + 255) / 256);
   const size_t row = align_up((size_t)N * 16);
   const size_t bytes = align_up(nn * 16) + align_up(nn * 8) + 24 * row +
                        4 * align_up((size_t)leaves * 8) +
                        align_up((size_t)std::max(nblk, 1) * kBt * kBt * 16) +
+                       align_up((size_t)std::max(nblk, 1) * kTfSplit * kBt * kBt * 16) +
                        align_up((size_t)nspan * nbt * 16 * kBt * 16) +
                        align_up((size_t)nparts * 7 * 8) + 256;
   char* base = nullptr;
@@ -983,6 +1126,8 @@ gw_status herm_eig_top(gw_ctx* c, int N, int nb, cpx<double>* A, cpx<double>* U,
   W.nrot = reinterpret_cast<int*>(take((size_t)leaves * 4));
   W.rho = reinterpret_cast<double*>(take((size_t)leaves * 8));
   auto* T = reinterpret_cast<cpx<double>*>(take((size_t)std::max(nblk, 1) * kBt * kBt * 16));
+  auto* tp = reinterpret_cast<cpx<double>*>(
+      take((size_t)std::max(nblk, 1) * kTfSplit * kBt * kBt * 16));
   auto* part = reinterpret_cast<cpx<double>*>(take((size_t)nspan * nbt * 16 * kBt * 16));
   auto* np = reinterpret_cast<double*>(take((size_t)nparts * 7 * 8));
   auto* flag = reinterpret_cast<int*>(take(4));
@@ -1027,23 +1172,24 @@ gw_status herm_eig_top(gw_ctx* c, int N, int nb, cpx<double>* A, cpx<double>* U,
   {
     ProfScope ps(c, "lowrank_tridiag");
     if (N * 48 > 65536)
-      GW_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tri_step<true>),
+      GW_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tri_step<8>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kTriFused * 48));
     hipLaunchKernelGGL(k_eig_scale, dim3(gnn), dim3(256), 0, c->stream, A, N, ex);
     for (int j = 0; j < N; ++j) {
       const int n = N - j;
-      const dim3 grid(std::max(1, (n - 1 + 3) / 4));
-      const cpx<double>* vp = j > 0 ? V + (size_t)(j - 1) * N : nullptr;
+      const dim3 grid(std::max(1, (N + 3) / 4 - tri_group(j)));
+      const cpx<double>* vp = V + (size_t)std::max(j - 1, 0) * N;
       cpx<double>* vo = V + (size_t)j * N;
-      if (n <= kTriFused) {
-        hipLaunchKernelGGL(k_tri_step<true>, grid, dim3(256), (size_t)n * 48, c->stream, A, N, j,
-                           vp, y[(j + 1) & 1], wv, vo, y[j & 1], d, e);
-      } else {
+      if (n > kTriFused)
         hipLaunchKernelGGL(k_tri_vec, dim3(1), dim3(1024), 0, c->stream, A, N, j, vp,
                            y[(j + 1) & 1], wv, vo, d, e);
-        hipLaunchKernelGGL(k_tri_step<false>, grid, dim3(256), 0, c->stream, A, N, j, vp,
-                           y[(j + 1) & 1], wv, vo, y[j & 1], d, e);
-      }
+      auto* step = n > kTriFused ? &k_tri_step<0>
+                   : n > 1024    ? &k_tri_step<8>
+                   : n > 512     ? &k_tri_step<4>
+                   : n > 256     ? &k_tri_step<2>
+                                 : &k_tri_step<1>;
+      hipLaunchKernelGGL(step, grid, dim3(256), n > kTriFused ? 0 : (size_t)n * 48, c->stream, A,
+                         N, j, vp, y[(j + 1) & 1], wv, vo, y[j & 1], d, e);
     }
     GW_CHECK_LAUNCH(c, "tridiagonal reduction");
   }
@@ -1077,12 +1223,16 @@ gw_status herm_eig_top(gw_ctx* c, int N, int nb, cpx<double>* A, cpx<double>* U,
     const unsigned gz = (unsigned)(((size_t)std::max(nb, 1) * N + 255) / 256);
     hipLaunchKernelGGL(k_bt_start, dim3(gz), dim3(256), 0, c->stream, Q[levels & 1], D, N, nb, Uh);
     if (nblk > 0)
-      hipLaunchKernelGGL(k_bt_tfac, dim3(nblk), dim3(1024), 0, c->stream, V, N, R, T);
+      {
+      hipLaunchKernelGGL(k_bt_tgram, dim3(nblk, kTfSplit), dim3(1024), 0, c->stream, V, N, R, tp);
+      hipLaunchKernelGGL(k_bt_tfac, dim3(nblk), dim3(1024), 0, c->stream, tp, kTfSplit, T);
+    }
     for (int b = nblk - 1; b >= 0; --b) {
-      const int j0 = b * kBt, sp = (N - j0 + kBtSpan - 1) / kBtSpan;
-      hipLaunchKernelGGL(k_bt_gram, dim3(nbt, sp), dim3(256), 0, c->stream, V, Uh, N, R, nb, j0,
+      const int j0 = b * kBt, sp = (N - j0 + kBtSpan - 1) / kBtSpan,
+                sg = (N - j0 + kBtGram - 1) / kBtGram;
+      hipLaunchKernelGGL(k_bt_gram, dim3(nbt, sg), dim3(512), 0, c->stream, V, Uh, N, R, nb, j0,
                          part);
-      hipLaunchKernelGGL(k_bt_apply, dim3(nbt, sp), dim3(256), 0, c->stream, V, T, part, sp, N, R,
+      hipLaunchKernelGGL(k_bt_apply, dim3(nbt, sp), dim3(256), 0, c->stream, V, T, part, sg, N, R,
                          nb, j0, Uh);
     }
     hipLaunchKernelGGL(k_bt_finish, dim3(gz), dim3(256), 0, c->stream, Uh, N, nb, U, ev, ex, lam);
