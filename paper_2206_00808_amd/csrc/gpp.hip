@@ -14,13 +14,16 @@
 // Sigma_n(E) = -sum_{n'' occ} m^H [SX v] m + sum_{n''} m^H [COH v] m, m = M_{n''n}.
 // Modes with |delta - eps^-1| <= 1e-10 or Re wt^2 <= 0 carry no pole (A = 0).
 //
-// k_sigma_gpp keeps a 16 x 64 tile of (A, wt) in registers (four rows of one
-// column per thread) and streams every n'' past it: the work per element and
-// energy is one reciprocal (two for occupied n'') and about a dozen FP64
-// operations, so the kernel is bound by the vector ALUs, not by memory.
-// conj(M(G)) A is formed once per element and n'' and reused for every energy.
-// Each thread sums its rows, then its column's v M(G'), over all n'' before a
-// single reduction per band.
+// k_sigma_gpp keeps a 16 x 64 tile of wt in registers (four rows of one column per
+// thread) and streams every n'' past it.  A factors out of the sum over n'': each
+// element and energy accumulates S = sum conj(M(G)) M(G') / (d - wt), and A v S is
+// formed once at the end.
+// Bound: FP64 vector instructions (the ALUs issue 96% of the time).  An element and
+// energy of an empty n'' takes 9 of them, and its share of M M* with three energies 2
+// more: 11.1 of 11.7 issued.  8 bands, 816 states, 3 energies, 1000 vectors: 8.9 ms;
+// 10.9 ms with conj(M(G)) A summed over the thread's rows and multiplied by v M(G') for
+// every n'' (14.5 FP64 instructions).  Two wavefronts per SIMD, because at three the
+// accumulators move between registers (34 of 190 instructions; 9.9 ms).
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -32,7 +35,6 @@ namespace gw {
 namespace {
 constexpr double kGppDropTol = 1e-10;
 constexpr int kTR = 16, kTC = 64, kRows = 4, kChunk = 32;
-constexpr int kRB = 4;  // rows sharing one reciprocal (kRows / kRB reciprocals per energy set)
 }  // namespace
 
 __global__ void k_gpp_modes(const double* __restrict__ qg, const int* __restrict__ g, int N,
@@ -83,166 +85,165 @@ __device__ __forceinline__ double rcp_nr(double x) {
 }
 
 template <typename Tin, int NE>
-__global__ void __launch_bounds__(256, 3) k_sigma_gpp(
+__global__ void __launch_bounds__(256, 2) k_sigma_gpp(
     const cpx<Tin>* __restrict__ m, int nn, int nocc, int nband, int N, int b0,
     const double* __restrict__ en, const double* __restrict__ v,
     const cpx<double>* __restrict__ amp, const cpx<double>* __restrict__ wt,
     const double* __restrict__ energies, int ntc, cpx<double>* __restrict__ part) {
+  // rows sharing one reciprocal: at most 12 squares are multiplied, so that their product
+  // stays in range while every |d - wt| is between 1e-12 and 1e12
+  constexpr int kRB = NE <= 3 ? 4 : 2;
   __shared__ cpx<double> mrow[kChunk][kTR];
-  __shared__ cpx<double> wcol[kChunk][kTC];
+  __shared__ cpx<double> mcol[kChunk][kTC];
+  __shared__ double dst[kChunk][NE];
   __shared__ double red[4][4 * NE];
   const int tile = blockIdx.x, n = b0 + blockIdx.y;
   const int ti = tile / ntc, tj = tile % ntc;
   const int t = threadIdx.x, c = t % kTC, rg = t / kTC;
   const int col = tj * kTC + c;
   const int row0 = ti * kTR + rg * kRows;
-  cpx<double> A[kRows], W[kRows];
+  double wx[kRows], wy[kRows], wy2[kRows];
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
     const int row = row0 + r;
-    const bool in = row < N && col < N;
-    A[r] = in ? amp[(size_t)row * N + col] : mk(0.0, 0.0);
-    W[r] = in ? wt[(size_t)row * N + col] : mk(1.0, 0.0);
+    // outside the matrix M is zero, and no energy meets this pole
+    const cpx<double> w = row < N && col < N ? wt[(size_t)row * N + col] : mk(1.0, 1.0);
+    wx[r] = w.x;
+    wy[r] = w.y;
+    wy2[r] = w.y * w.y;
   }
   const int diag = (col >= row0 && col < row0 + kRows && col < N) ? col - row0 : -1;
-  double WY2[kRows];
+  cpx<double> S[kRows][NE];
 #pragma unroll
-  for (int r = 0; r < kRows; ++r) WY2[r] = W[r].y * W[r].y;
-  double E[NE];
+  for (int r = 0; r < kRows; ++r)
 #pragma unroll
-  for (int k = 0; k < NE; ++k) E[k] = energies[(size_t)n * NE + k];
-  cpx<double> acoh[NE], asx[NE];
-#pragma unroll
-  for (int k = 0; k < NE; ++k) acoh[k] = asx[k] = mk(0.0, 0.0);
+    for (int k = 0; k < NE; ++k) S[r][k] = mk(0.0, 0.0);
 
-  for (int a0 = 0; a0 < nn; a0 += kChunk) {
-    const int na = nn - a0 < kChunk ? nn - a0 : kChunk;
+  // M rows, M columns and d of the next n'' chunk
+  auto stage = [&](int a0, int na) {
     __syncthreads();
-    // stage conj-ready M rows and v M columns of the next n'' chunk
-    for (int idx = t; idx < kChunk * (kTR + kTC); idx += 256) {
+    for (int idx = t; idx < na * (kTR + kTC); idx += 256) {
       const int s = idx / (kTR + kTC), o = idx % (kTR + kTC);
+      const int gg = o < kTR ? ti * kTR + o : tj * kTC + (o - kTR);
       cpx<double> val = mk(0.0, 0.0);
-      if (s < na) {
-        const size_t base = ((size_t)(a0 + s) * nband + n) * N;
-        if (o < kTR) {
-          const int gg = ti * kTR + o;
-          if (gg < N) {
-            const cpx<Tin> x = m[base + gg];
-            val = mk((double)x.x, (double)x.y);
+      if (gg < N) {
+        const cpx<Tin> x = m[((size_t)(a0 + s) * nband + n) * N + gg];
+        val = mk((double)x.x, (double)x.y);
+      }
+      if (o < kTR) mrow[s][o] = val;
+      else mcol[s][o - kTR] = val;
+    }
+    for (int idx = t; idx < na * NE; idx += 256)
+      dst[idx / NE][idx % NE] = energies[(size_t)n * NE + idx % NE] - en[a0 + idx / NE];
+    __syncthreads();
+  };
+
+  cpx<double> acoh[NE], asx[NE];
+  // occupied n'': COH and SX; a row's reciprocals come from one of their product
+  {
+    cpx<double> D[kRows][NE], own = mk(0.0, 0.0);
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+#pragma unroll
+      for (int k = 0; k < NE; ++k) D[r][k] = mk(0.0, 0.0);
+    for (int a0 = 0; a0 < nocc; a0 += kChunk) {
+      const int na = min(kChunk, nocc - a0);
+      stage(a0, na);
+      for (int s = 0; s < na; ++s) {
+        const cpx<double> mc = mcol[s][c];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+          const cpx<double> C = cmulc(mrow[s][rg * kRows + r], mc);
+          if (r == diag) own = own + C;
+          const double cyw = C.y * wy[r], cxw = C.x * wy[r];
+          double z1[NE], z2[NE], x[2 * NE], pre[2 * NE];
+#pragma unroll
+          for (int k = 0; k < NE; ++k) {
+            const double d = dst[s][k];
+            z1[k] = d - wx[r];
+            z2[k] = d + wx[r];
+            x[2 * k] = fma(z1[k], z1[k], wy2[r]);
+            x[2 * k + 1] = fma(z2[k], z2[k], wy2[r]);
+            pre[2 * k] = k == 0 ? x[0] : pre[2 * k - 1] * x[2 * k];
+            pre[2 * k + 1] = pre[2 * k] * x[2 * k + 1];
           }
-          mrow[s][o] = val;
-        } else {
-          const int gg = tj * kTC + (o - kTR);
-          if (gg < N) {
-            const cpx<Tin> x = m[base + gg];
-            val = mk(v[gg] * (double)x.x, v[gg] * (double)x.y);
+          double rr = rcp_nr(pre[2 * NE - 1]);
+#pragma unroll
+          for (int k = NE - 1; k >= 0; --k) {
+            const double y2 = rr * pre[2 * k];
+            rr *= x[2 * k + 1];
+            const double y1 = k == 0 ? rr : rr * pre[2 * k - 1];
+            if (k > 0) rr *= x[2 * k];
+            // C / (d - wt) and C / (d - wt) - C / (d + wt)
+            const cpx<double> r1 = mk(y1 * fma(C.x, z1[k], -cyw), y1 * fma(C.y, z1[k], cxw));
+            S[r][k] = S[r][k] + r1;
+            D[r][k] = D[r][k] + mk(fma(-y2, fma(C.x, z2[k], cyw), r1.x),
+                                   fma(-y2, fma(C.y, z2[k], -cxw), r1.y));
           }
-          wcol[s][o - kTR] = val;
         }
       }
     }
-    __syncthreads();
+    const double vc = col < N ? v[col] : 0.0;
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+      cpx<double> x = own;
+#pragma unroll
+      for (int r = 0; r < kRows; ++r)
+        if (row0 + r < N && col < N)
+          x = x + scal(cmul(amp[(size_t)(row0 + r) * N + col], D[r][k]), 0.5);
+      asx[k] = scal(x, vc);
+    }
+  }
+  // empty n'': COH only.  The reciprocals of |d - wt|^2 for kRB rows and every energy come
+  // from one hardware reciprocal of their product (prefix products, then
+  // back-substitution)
+  for (int a0 = nocc; a0 < nn; a0 += kChunk) {
+    const int na = min(kChunk, nn - a0);
+    stage(a0, na);
     for (int s = 0; s < na; ++s) {
-      const int a = a0 + s;
-      const double ea = en[a];
-      const bool occ = a < nocc;
-      const cpx<double> wc = wcol[s][c];
-      cpx<double> tc[NE], ts[NE];
+      const cpx<double> mc = mcol[s][c];
+      double d[NE];
 #pragma unroll
-      for (int k = 0; k < NE; ++k) tc[k] = ts[k] = mk(0.0, 0.0);
-      if (!occ && NE <= 3) {
-        // empty n'': COH only.  The reciprocals of |d - wt|^2 for kRB rows and every
-        // energy come from one hardware reciprocal of their product (prefix
-        // products, then back-substitution)
+      for (int k = 0; k < NE; ++k) d[k] = dst[s][k];
 #pragma unroll
-        for (int g0 = 0; g0 < kRows; g0 += kRB) {
-          double z1[kRB][NE], x[kRB][NE], pre[kRB * NE];
+      for (int g0 = 0; g0 < kRows; g0 += kRB) {
+        double z[kRB][NE], x[kRB][NE], pre[kRB * NE];
 #pragma unroll
-          for (int r = 0; r < kRB; ++r)
-#pragma unroll
-            for (int k = 0; k < NE; ++k) {
-              z1[r][k] = (E[k] - ea) - W[g0 + r].x;
-              x[r][k] = fma(z1[r][k], z1[r][k], WY2[g0 + r]);
-              const int i = r * NE + k;
-              pre[i] = i == 0 ? x[0][0] : pre[i - 1] * x[r][k];
-            }
-          double rr = rcp_nr(pre[kRB * NE - 1]);
-#pragma unroll
-          for (int r = kRB - 1; r >= 0; --r) {
-            const cpx<double> mr = mrow[s][rg * kRows + g0 + r];
-            // conj(M(G)) A conj(d - wt) / |d - wt|^2 = A conj(M) / (d - wt); the
-            // products of B with Im wt are the same for every energy
-            const cpx<double> B = cmulc(mr, A[g0 + r]);
-            const double byw = B.y * W[g0 + r].y, bxw = B.x * W[g0 + r].y;
-#pragma unroll
-            for (int k = NE - 1; k >= 0; --k) {
-              const int i = r * NE + k;
-              const double inv = i == 0 ? rr : rr * pre[i - 1];
-              rr *= x[r][k];
-              const cpx<double> b1 = mk(fma(B.x, z1[r][k], -byw), fma(B.y, z1[r][k], bxw));
-              tc[k] = mk(fma(inv, b1.x, tc[k].x), fma(inv, b1.y, tc[k].y));
-            }
-          }
-        }
-      } else if (!occ) {
-        // empty n'', four energies: the NE reciprocals of |d - wt|^2 come from one
-        // hardware reciprocal of their product (prefix products, then back-substitution)
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-          const cpx<double> mr = mrow[s][rg * kRows + r];
-          // conj(M(G)) A is the same for every energy; A/(d - wt) = A conj(d - wt) / |d - wt|^2
-          const cpx<double> B = cmulc(mr, A[r]);
-          const double wx = W[r].x, wy = W[r].y, wy2 = wy * wy;
-          double z1[NE], x[NE], pre[NE], inv[NE];
+        for (int r = 0; r < kRB; ++r)
 #pragma unroll
           for (int k = 0; k < NE; ++k) {
-            z1[k] = (E[k] - ea) - wx;
-            x[k] = fma(z1[k], z1[k], wy2);
-            pre[k] = k == 0 ? x[0] : pre[k - 1] * x[k];
+            z[r][k] = d[k] - wx[g0 + r];
+            x[r][k] = fma(z[r][k], z[r][k], wy2[g0 + r]);
+            const int i = r * NE + k;
+            pre[i] = i == 0 ? x[0][0] : pre[i - 1] * x[r][k];
           }
-          double rr = rcp_nr(pre[NE - 1]);
+        double rr = rcp_nr(pre[kRB * NE - 1]);
 #pragma unroll
-          for (int k = NE - 1; k > 0; --k) {
-            inv[k] = rr * pre[k - 1];
-            rr *= x[k];
-          }
-          inv[0] = rr;
+        for (int r = kRB - 1; r >= 0; --r) {
+          // C conj(d - wt) / |d - wt|^2; C Im wt is the same for every energy
+          const cpx<double> C = cmulc(mrow[s][rg * kRows + g0 + r], mc);
+          const double cyw = C.y * wy[g0 + r], cxw = C.x * wy[g0 + r];
 #pragma unroll
-          for (int k = 0; k < NE; ++k) {
-            // B (z1 + i wy) = B conj(d - wt)
-            const cpx<double> b1 = mk(fma(B.x, z1[k], -B.y * wy), fma(B.x, wy, B.y * z1[k]));
-            tc[k] = mk(fma(inv[k], b1.x, tc[k].x), fma(inv[k], b1.y, tc[k].y));
-          }
-        }
-      } else {
-        // occupied n'': COH and SX, one refined reciprocal per denominator
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-          const cpx<double> mr = mrow[s][rg * kRows + r];
-          const cpx<double> B = cmulc(mr, A[r]);
-          const double wx = W[r].x, wy = W[r].y;
-#pragma unroll
-          for (int k = 0; k < NE; ++k) {
-            const double d = E[k] - ea;
-            const double z1 = d - wx;
-            const double y1 = rcp_nr(fma(z1, z1, wy * wy));
-            const cpx<double> b1 = mk(fma(B.x, z1, -B.y * wy), fma(B.x, wy, B.y * z1));
-            tc[k] = mk(fma(y1, b1.x, tc[k].x), fma(y1, b1.y, tc[k].y));
-            const double z2 = d + wx;
-            const double y2 = rcp_nr(fma(z2, z2, wy * wy));
-            // B conj(d + wt) = B (z2 - i wy)
-            const cpx<double> b2 = mk(fma(B.x, z2, B.y * wy), fma(B.y, z2, -B.x * wy));
-            cpx<double> f = mk(0.5 * fma(y1, b1.x, -y2 * b2.x), 0.5 * fma(y1, b1.y, -y2 * b2.y));
-            if (r == diag) f = f + mk(mr.x, -mr.y);
-            ts[k] = ts[k] + f;
+          for (int k = NE - 1; k >= 0; --k) {
+            const int i = r * NE + k;
+            const double inv = i == 0 ? rr : rr * pre[i - 1];
+            if (i > 0) rr *= x[r][k];
+            cpx<double>& q = S[g0 + r][k];
+            q = mk(fma(inv, fma(C.x, z[r][k], -cyw), q.x), fma(inv, fma(C.y, z[r][k], cxw), q.y));
           }
         }
       }
+    }
+  }
+  {
+    const double vc = col < N ? v[col] : 0.0;
 #pragma unroll
-      for (int k = 0; k < NE; ++k) {
-        acoh[k] = acoh[k] + cmul(tc[k], wc);
-        asx[k] = asx[k] + cmul(ts[k], wc);
-      }
+    for (int k = 0; k < NE; ++k) {
+      cpx<double> x = mk(0.0, 0.0);
+#pragma unroll
+      for (int r = 0; r < kRows; ++r)
+        if (row0 + r < N && col < N) x = x + cmul(amp[(size_t)(row0 + r) * N + col], S[r][k]);
+      acoh[k] = scal(x, vc);
     }
   }
   // one reduction per band: 64-lane butterflies, then the four wavefronts in order
