@@ -20,7 +20,7 @@
 //   update : A22 -= L21 U12 on the FP64 matrix cores
 // then eps^-1 = U^-1 L^-1 P by blocked forward/back substitution on P*I.
 #include "common.h"
-#include "tiles.h"
+#include "gj.h"
 
 #include <climits>
 
@@ -444,8 +444,6 @@ __global__ void k_perm_identity(const int* __restrict__ perm, int N, cpx<double>
 
 
 // ---------------------------------------------------------------- Gauss-Jordan path
-constexpr int GB = 64;  // Gauss-Jordan block width
-
 __global__ void k_fill_int(int* p, int n, int v) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = v;
 }
@@ -454,6 +452,7 @@ __global__ void k_fill_int(int* p, int n, int v) {
 // epst = I - S chi0 S with S = diag(sqrt(v)), one 32x32 tile per workgroup
 // (grid: tiles x tiles x nfreq). flag[1] = 1 if some v <= 0 or non-finite;
 // flag[4] = 1 if some chi0 entry is not finite;
+// flag[5] = 1 if chi0 is not exactly Hermitian;
 // flag[3] = 1 if chi0 is not Hermitian: |chi_ij - conj(chi_ji)| above
 // kHermRel (|chi_ij| + |chi_ji|) for some pair, checked against the mirror
 // tile staged through LDS. The Gauss-Jordan pivot test alone cannot tell a
@@ -477,7 +476,7 @@ __global__ void __launch_bounds__(256) k_epst_build(const cpx<double>* __restric
     if (i < N && j < N) mir[c][r] = chi[(size_t)i * N + j];
   }
   __syncthreads();
-  bool bad = false, nonfinite = false;
+  bool bad = false, nonfinite = false, inexact = false;
   for (int r = r0; r < ET; r += 256 / ET) {
     const int i = ti * ET + r, j = tj * ET + c;
     if (i >= N || j >= N) continue;
@@ -487,6 +486,7 @@ __global__ void __launch_bounds__(256) k_epst_build(const cpx<double>* __restric
     const cpx<double> y = mir[r][c];  // chi[j][i]
     const double dr = x.x - y.x, di = x.y + y.y;
     const double lim = kHermRel * (fabs(x.x) + fabs(x.y) + fabs(y.x) + fabs(y.y));
+    inexact = inexact || !(dr == 0.0 && di == 0.0);
     nonfinite = nonfinite || !(fabs(x.x) < INFINITY && fabs(x.y) < INFINITY);
     bad = bad || !(fabs(dr) <= lim && fabs(di) <= lim);
     const double s = sqrt(vi) * sqrt(vj);
@@ -494,305 +494,7 @@ __global__ void __launch_bounds__(256) k_epst_build(const cpx<double>* __restric
   }
   if (bad) flag[3] = 1;
   if (nonfinite) flag[4] = 1;
-}
-
-// Inverse of the diagonal block D = A[K][K] (nbk <= GB = 64) by Gauss-Jordan
-// without pivoting, register resident (gj_invert_64); the block of frequency f
-// is src[f * sstride + i * ld + j] and its inverse goes to Dw[f]. A pivot that
-// is not real and >= 1/2 sets flag[2].
-__global__ void __launch_bounds__(1024) k_gj_diag(const cpx<double>* __restrict__ src, int ld,
-                                                  size_t sstride, int nbk,
-                                                  cpx<double>* __restrict__ Dw,
-                                                  int* __restrict__ flag) {
-  static_assert(GB == 64, "gj_invert_64 holds a 64x64 block");
-  __shared__ cpx<double> rowb[2][GB], colb[2][GB];
-  const int f = blockIdx.x;
-  src += (size_t)f * sstride;
-  Dw += (size_t)f * GB * GB;
-  const int tid = threadIdx.x, ti = tid / 32, tj = tid % 32;
-  cpx<double> d[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int i = ti + 32 * a, j = tj + 32 * b;
-      d[a][b] = (i < nbk && j < nbk) ? src[(size_t)i * ld + j] : mk(i == j ? 1.0 : 0.0, 0.0);
-    }
-  if (gj_invert_64<32>(d, nbk, rowb, colb)) flag[2] = 1;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int i = ti + 32 * a, j = tj + 32 * b;
-      if (i < nbk && j < nbk) Dw[i * GB + j] = d[a][b];
-    }
-}
-
-// The one launch between the row panel and the rank update of step K (block
-// k, width nbk):
-//   - row block of the previous step (kp, nbp; none when nbp is 0) <- Rp outside
-//     its columns and Dp inside, its Gauss-Jordan value;
-//   - Cb[i][t] = A[i][k+t], the rows of the previous block taking those values;
-//   - R[t][k+j] = delta_tj + D[t][j]; with R in the K columns set this way,
-//     A[:,K] - Cb R leaves -Cb D in the column block, its Gauss-Jordan value.
-// No entry is both read and written: the previous block's rows are taken from
-// Rp and Dp.
-__global__ void k_gj_step(cpx<double>* __restrict__ A, int N, int k, int nbk,
-                          cpx<double>* __restrict__ Cb, cpx<double>* __restrict__ R,
-                          const cpx<double>* __restrict__ D, int kp, int nbp,
-                          const cpx<double>* __restrict__ Rp, const cpx<double>* __restrict__ Dp) {
-  const size_t f = blockIdx.y;
-  A += f * (size_t)N * N;
-  Cb += f * (size_t)N * GB;
-  R += f * (size_t)GB * N;
-  Rp += f * (size_t)GB * N;
-  D += f * (size_t)GB * GB;
-  Dp += f * (size_t)GB * GB;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  auto fixed = [&](int t, int j) {
-    return (j >= kp && j < kp + nbp) ? Dp[t * GB + (j - kp)] : Rp[(size_t)t * N + j];
-  };
-  if (e < nbp * N) {
-    const int t = e / N, j = e % N;
-    A[(size_t)(kp + t) * N + j] = fixed(t, j);
-  }
-  if (e < N * nbk) {
-    const int i = e / nbk, t = e % nbk;
-    Cb[(size_t)i * GB + t] = (i >= kp && i < kp + nbp) ? fixed(i - kp, k + t)
-                                                       : A[(size_t)i * N + k + t];
-  }
-  if (e < nbk * nbk) {
-    const int t = e / nbk, j = e % nbk;
-    const cpx<double> dv = D[t * GB + j];
-    R[(size_t)t * N + k + j] = mk(dv.x + (t == j ? 1.0 : 0.0), dv.y);
-  }
-}
-
-// Row block K <- R outside the K columns and Dinv inside.
-__global__ void k_gj_fix(cpx<double>* __restrict__ A, int N, int k, int nbk,
-                         const cpx<double>* __restrict__ R, const cpx<double>* __restrict__ Dw) {
-  const size_t f = blockIdx.y;
-  A += f * (size_t)N * N;
-  R += f * (size_t)GB * N;
-  Dw += f * (size_t)GB * GB;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nbk * N) return;
-  const int t = e / N, j = e % N;
-  A[(size_t)(k + t) * N + j] = (j >= k && j < k + nbk) ? Dw[t * GB + (j - k)] : R[(size_t)t * N + j];
-}
-
-// The rank-nbk update A -= Cb R of every row and column (one matrix per
-// frequency), the bulk of each Gauss-Jordan step, with the next step's
-// diagonal inverse in the same launch.
-//   - Update tiles: with K at most GB the product per output is short and the C
-//     tile streams through once, so there is no LDS staging and no barrier.
-//     Each wavefront computes a 32x32 block (2x2 v_mfma_f64_16x16x4_f64, three
-//     real products per complex one) with its fragments loaded straight from
-//     Cb (N x GB) and R (GB x N), which stay in L2; the next four K are loaded
-//     while the current ones feed the matrix cores. C is read in the epilogue;
-//     three workgroups per CU cover that latency with the other wavefronts'
-//     products. From N = 2048 the operands pass through LDS instead
-//     (gj_update_tile_lds), which loads each fragment once per workgroup.
-//     Tiles of 64x64 are numbered frequency, row band, column band and
-//     renumbered per XCD, so one XCD's L2 holds the panels of its tiles.
-//   - Look-ahead (nb2 > 0): the first nfreq workgroups each form the next
-//     diagonal block Dn = A[K'][K'] - Cb[K'] R[:, K'] with the same tile code,
-//     invert it in registers (gj_invert_64, 16x16 threads holding 4x4 entries)
-//     and write the inverse to Dw. The update skips tile (K', K'): that block
-//     is only ever read into values that a later step overwrites (the next
-//     panel's K' columns and row block K', which the step after rewrites from
-//     R and Dinv), so no workgroup writes what another reads.
-constexpr int UT = 64;  // workgroup tile (2x2 wavefronts of 32x32)
-
-// A -= product on a wavefront's 32x32 block at (ia, ja): Re = t1 - t2, Im = t3 -
-// t1 - t2 (f64 16x16x4 D layout: row lk + 4r, column l16). The 8 entries of
-// each row block are loaded (at clamped, always valid addresses) before any is
-// stored, so the loads are in flight together: with a load, a wait and a store
-// per entry, each of the 16 entries cost a full memory round trip.
-__device__ __forceinline__ void gj_epilogue(const d4 (&t1)[2][2], const d4 (&t2)[2][2],
-                                            const d4 (&t3)[2][2], cpx<double>* A, int N, int ia,
-                                            int ja) {
-  const int lane = threadIdx.x & 63, l16 = lane & 15, lk = lane >> 4;
-#pragma unroll
-  for (int a = 0; a < 2; ++a) {
-    cpx<double> v[2][4];
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = min(ia + a * 16 + lk + 4 * r, N - 1), j = min(ja + b * 16 + l16, N - 1);
-        v[b][r] = A[(size_t)i * N + j];
-      }
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = ia + a * 16 + lk + 4 * r, j = ja + b * 16 + l16;
-        if (i < N && j < N)
-          A[(size_t)i * N + j] = mk(v[b][r].x - (t1[a][b][r] - t2[a][b][r]),
-                                    v[b][r].y - ((t3[a][b][r] - t1[a][b][r]) - t2[a][b][r]));
-      }
-  }
-}
-
-// A -= Cb R on the 64x64 tile at (i0, j0) (rows and columns below N) with the
-// operands staged in LDS: Cb[i0 .. i0 + 63][K] and R[K][j0 .. j0 + 63] pass in
-// chunks of 8 K through two 16 KiB buffers, loaded by global_load_lds, so each
-// fragment comes from L2 once per workgroup, where the 2x2 wavefronts loading
-// their fragments directly fetch each twice.
-//   - Cb chunk [64 rows][8 k of 16 B]: k stored at slot k ^ (row & 7). A
-//     fragment read (16 rows, one k per group of 16 lanes) then takes as many
-//     LDS cycles as a contiguous 1 KiB read, by the bank-conflict counter;
-//     (row & 7) ^ ((row >> 3) & 1) took twice as many. R chunk [8 k][64
-//     columns]: a fragment read is 256 contiguous bytes per k.
-//   - K past kdim is read clamped and zeroed at the fragment (stale panel
-//     entries may hold anything); rows and columns past N are clamped and
-//     feed outputs that are not stored.
-//   - Products as in gj_update_tile: 2x2 v_mfma_f64_16x16x4_f64 blocks per
-//     wavefront, three real products per complex one, A read in the epilogue.
-__device__ __forceinline__ void gj_update_tile_lds(const cpx<double>* __restrict__ Cb,
-                                                   const cpx<double>* __restrict__ R,
-                                                   cpx<double>* A, int N, int kdim, int i0,
-                                                   int j0) {
-  __shared__ __align__(16) cpx<double> Cs0[UT * 8], Rs0[8 * UT], Cs1[UT * 8], Rs1[8 * UT];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l16 = lane & 15, lk = lane >> 4;
-  const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
-  d4 t1[2][2], t2[2][2], t3[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      t1[a][b] = (d4){0, 0, 0, 0};
-      t2[a][b] = (d4){0, 0, 0, 0};
-      t3[a][b] = (d4){0, 0, 0, 0};
-    }
-  // chunk at K offset kc: 16 row blocks of 1 KiB (8 of Cb, 8 rows each; 8 of
-  // R, one k each), 4 per wavefront
-  auto issue = [&](cpx<double>* Cs, cpx<double>* Rs, int kc) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int idx = wave * 4 + u;
-      const int row = (idx & 7) * 8 + (lane >> 3);
-      const int kb = (lane & 7) ^ (lane >> 3);  // row & 7 = lane >> 3
-      const cpx<double>* sa = Cb + (size_t)min(i0 + row, N - 1) * GB + min(kc + kb, kdim - 1);
-      const cpx<double>* sr = R + (size_t)min(kc + (idx & 7), kdim - 1) * N + min(j0 + lane, N - 1);
-      if (idx < 8)
-        __builtin_amdgcn_global_load_lds((const void*)sa, (lds_void*)(Cs + idx * 64), 16, 0, 0);
-      else
-        __builtin_amdgcn_global_load_lds((const void*)sr, (lds_void*)(Rs + (idx - 8) * 64), 16,
-                                         0, 0);
-    }
-  };
-  auto compute = [&](const cpx<double>* Cs, const cpx<double>* Rs, int kc) {
-#pragma unroll
-    for (int kk = 0; kk < 8; kk += 4) {
-      const int k = kk + lk;
-      const bool ok = kc + k < kdim;
-      cpx<double> fa[2], fb[2];
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        const int row = wi + a * 16 + l16;
-        const cpx<double> v = Cs[row * 8 + (k ^ (l16 & 7))];
-        fa[a] = ok ? v : mk(0.0, 0.0);
-      }
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const cpx<double> v = Rs[k * UT + wj + b * 16 + l16];
-        fb[b] = ok ? v : mk(0.0, 0.0);
-      }
-      double sa[2], sb[2];
-#pragma unroll
-      for (int a = 0; a < 2; ++a) sa[a] = fa[a].x + fa[a].y;
-#pragma unroll
-      for (int b = 0; b < 2; ++b) sb[b] = fb[b].x + fb[b].y;
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          t1[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a].x, fb[b].x, t1[a][b], 0, 0, 0);
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          t2[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a].y, fb[b].y, t2[a][b], 0, 0, 0);
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          t3[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[a], sb[b], t3[a][b], 0, 0, 0);
-    }
-  };
-  const int nch = (kdim + 7) / 8;
-  issue(Cs0, Rs0, 0);
-  __syncthreads();  // (its fence waits for the loads)
-  for (int c = 0; c < nch; c += 2) {
-    if (c + 1 < nch) issue(Cs1, Rs1, (c + 1) * 8);
-    compute(Cs0, Rs0, c * 8);
-    __syncthreads();
-    if (c + 1 < nch) {
-      if (c + 2 < nch) issue(Cs0, Rs0, (c + 2) * 8);
-      compute(Cs1, Rs1, (c + 1) * 8);
-      __syncthreads();
-    }
-  }
-  gj_epilogue(t1, t2, t3, A, N, i0 + wi, j0 + wj);
-}
-
-template <bool kLds>
-__global__ void __launch_bounds__(256, 3) k_gj_update(cpx<double>* __restrict__ A, int N,
-                                                      int kdim, const cpx<double>* __restrict__ Cb,
-                                                      const cpx<double>* __restrict__ R,
-                                                      int nfreq, int k2, int nb2,
-                                                      cpx<double>* __restrict__ Dn,
-                                                      cpx<double>* __restrict__ Dw,
-                                                      int* __restrict__ flag) {
-  const int nt = (N + UT - 1) / UT;
-  const int wave = threadIdx.x >> 6;
-  const int ndiag = nb2 > 0 ? nfreq : 0;
-  if ((int)blockIdx.x < ndiag) {
-    static_assert(GB == 64 && UT == GB, "the look-ahead block is one 64x64 tile");
-    __shared__ cpx<double> rowb[2][GB], colb[2][GB];
-    const int f = blockIdx.x;
-    A += (size_t)f * N * N;
-    Dn += (size_t)f * GB * GB;
-    Dw += (size_t)f * GB * GB;
-    gj_update_tile(Cb + (size_t)f * N * GB, GB, R + (size_t)f * GB * N, A, N, kdim,
-                   k2 + (wave >> 1) * 32, k2 + (wave & 1) * 32, k2 + nb2, Dn, GB, k2);
-    __syncthreads();  // Dn complete and visible to the workgroup
-    constexpr int TG = 16, TE = GB / TG;
-    const int ti = threadIdx.x / TG, tj = threadIdx.x % TG;
-    cpx<double> d[TE][TE];
-#pragma unroll
-    for (int a = 0; a < TE; ++a)
-#pragma unroll
-      for (int b = 0; b < TE; ++b) {
-        const int i = ti + TG * a, j = tj + TG * b;
-        d[a][b] = (i < nb2 && j < nb2) ? Dn[i * GB + j] : mk(i == j ? 1.0 : 0.0, 0.0);
-      }
-    if (gj_invert_64<TG>(d, nb2, rowb, colb)) flag[2] = 1;
-#pragma unroll
-    for (int a = 0; a < TE; ++a)
-#pragma unroll
-      for (int b = 0; b < TE; ++b) {
-        const int i = ti + TG * a, j = tj + TG * b;
-        if (i < nb2 && j < nb2) Dw[i * GB + j] = d[a][b];
-      }
-    return;
-  }
-  const long long lin = xcd_linear(blockIdx.x - ndiag, (long long)nt * nt * nfreq);
-  if (lin < 0) return;
-  const int f = (int)(lin / ((long long)nt * nt));
-  const int rem = (int)(lin % ((long long)nt * nt));
-  const int ti = rem / nt, tj = rem % nt;
-  if (nb2 > 0 && ti == k2 / UT && tj == k2 / UT) return;
-  A += (size_t)f * N * N;
-  if constexpr (kLds)
-    gj_update_tile_lds(Cb + (size_t)f * N * GB, R + (size_t)f * GB * N, A, N, kdim, ti * UT,
-                       tj * UT);
-  else
-    gj_update_tile(Cb + (size_t)f * N * GB, GB, R + (size_t)f * GB * N, A, N, kdim,
-                   ti * UT + (wave >> 1) * 32, tj * UT + (wave & 1) * 32, N, A, N, 0);
+  if (inexact) flag[5] = 1;
 }
 
 // ---------------------------------------------------------------- consumers of eps^-1
@@ -896,17 +598,6 @@ gw_status sigma_sx_static(gw_ctx* c, int nocc, int nband, int N, const void* mtx
                        reinterpret_cast<cpx<double>*>(sigma));
   GW_CHECK_LAUNCH(c, "k_sx_reduce");
   return GW_OK;
-}
-
-// eps^-1 = S epst^-1 S^-1, in place.
-__global__ void k_unscale(cpx<double>* __restrict__ A, const double* __restrict__ v, int N) {
-  const size_t nn = (size_t)N * N;
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= nn) return;
-  const int i = (int)(idx / N), j = (int)(idx % N);
-  const double s = sqrt(v[i]) / sqrt(v[j]);
-  cpx<double>* a = A + (size_t)blockIdx.y * nn + idx;
-  *a = scal(*a, s);
 }
 
 gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
@@ -1027,18 +718,23 @@ gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
 
 static gw_status epsinv_gauss_jordan(gw_ctx* c, int N, int nfreq, const double* chi0,
                                      const double* vcoul, double* epsinv) {
-  const size_t nn = (size_t)N * N;
   const size_t nR = (size_t)nfreq * GB * N, nC = (size_t)nfreq * N * GB, nD = (size_t)nfreq * GB * GB;
   gw_status st = ws_begin(c, 2 * align_up(nR * 16) + align_up(nC * 16) + 3 * align_up(nD * 16));
   if (st != GW_OK) return st;
-  cpx<double>* Rw[2] = {static_cast<cpx<double>*>(ws_take(c, nR * 16)),
-                        static_cast<cpx<double>*>(ws_take(c, nR * 16))};
-  cpx<double>* Cb = static_cast<cpx<double>*>(ws_take(c, nC * 16));
-  cpx<double>* Dw[2] = {static_cast<cpx<double>*>(ws_take(c, nD * 16)),
-                        static_cast<cpx<double>*>(ws_take(c, nD * 16))};
-  cpx<double>* Dn = static_cast<cpx<double>*>(ws_take(c, nD * 16));
-  cpx<double>* A = reinterpret_cast<cpx<double>*>(epsinv);
-  const double* Ad = epsinv;
+  GjStrided g;
+  g.m.A = reinterpret_cast<cpx<double>*>(epsinv);
+  g.m.chi = reinterpret_cast<const cpx<double>*>(chi0);
+  g.m.v = vcoul;
+  g.m.R0 = static_cast<cpx<double>*>(ws_take(c, nR * 16));
+  g.m.R1 = static_cast<cpx<double>*>(ws_take(c, nR * 16));
+  g.m.Cb = static_cast<cpx<double>*>(ws_take(c, nC * 16));
+  g.m.D0 = static_cast<cpx<double>*>(ws_take(c, nD * 16));
+  g.m.D1 = static_cast<cpx<double>*>(ws_take(c, nD * 16));
+  g.m.Dn = static_cast<cpx<double>*>(ws_take(c, nD * 16));
+  g.m.bad = c->d_flag + 2;
+  g.m.full = c->d_flag + 5;
+  g.m.N = N;
+  g.m.pad = 0;
   {
     ProfScope ps(c, "flags_clear");
     hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, c->stream, c->d_flag, 16, 0);
@@ -1048,71 +744,10 @@ static gw_status epsinv_gauss_jordan(gw_ctx* c, int N, int nfreq, const double* 
     ProfScope ps(c, "eps_build");
     const unsigned nt = (unsigned)((N + ET - 1) / ET);
     hipLaunchKernelGGL(k_epst_build, dim3(nt, nt, nfreq), dim3(256), 0, c->stream,
-                       reinterpret_cast<const cpx<double>*>(chi0), vcoul, A, N, c->d_flag);
+                       g.m.chi, vcoul, g.m.A, N, c->d_flag);
     GW_CHECK_LAUNCH(c, "k_epst_build");
   }
-  {
-    ProfScope ps(c, "gj_diag");
-    hipLaunchKernelGGL(k_gj_diag, dim3(nfreq), dim3(1024), 0, c->stream, A, N, nn,
-                       std::min(GB, N), Dw[0], c->d_flag);
-    GW_CHECK_LAUNCH(c, "k_gj_diag");
-  }
-  const size_t ext = (size_t)nfreq * nn;
-  // Per step K: the row panel R = Dinv A[K][:], one small kernel, and the rank
-  // update, whose launch also forms and inverts the next diagonal block (the
-  // look-ahead) on its first workgroups. The panels R and the diagonal inverses
-  // alternate between two buffers by step parity.
-  int kp = 0, nbp = 0;
-  for (int k = 0, s = 0; k < N; k += GB, ++s) {
-    const int nbk = std::min(GB, N - k);
-    cpx<double>* D = Dw[s & 1];
-    cpx<double>* R = Rw[s & 1];
-    // R = Dinv A[K][:] (rows nbk.. of R are never read)
-    st = zgemm_nn(c, nbk, N, nbk, 1.0, reinterpret_cast<const double*>(D), 0, GB, GB * GB, Ad,
-                  (size_t)k * N, N, (long long)nn, reinterpret_cast<double*>(R), 0, N,
-                  (long long)GB * N, nfreq, nD, ext, nR, 0.0);
-    if (st != GW_OK) return st;
-    {
-      ProfScope ps(c, "gj_small");
-      hipLaunchKernelGGL(k_gj_step, dim3((N * GB + 255) / 256, nfreq), dim3(256), 0, c->stream,
-                         A, N, k, nbk, Cb, R, D, kp, nbp, Rw[(s + 1) & 1], Dw[(s + 1) & 1]);
-      GW_CHECK_LAUNCH(c, "k_gj_step");
-    }
-    // A -= Cb R over the whole matrix: every row outside K is final, including
-    // its K columns; row block K is rewritten by the next step's small kernel
-    const int k2 = k + GB, nb2 = std::max(0, std::min(GB, N - k2));
-    {
-      ProfScope ps(c, "gj_update");
-      const int nt = (N + UT - 1) / UT;
-      const long long tiles = (long long)nt * nt * nfreq;
-      const long long grid = (nb2 > 0 ? nfreq : 0) + ((tiles + kXcd - 1) / kXcd) * kXcd;
-      // operands staged in LDS from N = 2048 (C3, N = 4000: 8.8 vs 9.7 ms per step);
-      // below, fragments straight from L2 (C2, N = 1000: 1.68 vs 1.84 ms)
-      if (N >= 2048)
-        hipLaunchKernelGGL(k_gj_update<true>, dim3((unsigned)grid), dim3(256), 0, c->stream, A,
-                           N, nbk, Cb, R, nfreq, k2, nb2, Dn, Dw[(s + 1) & 1], c->d_flag);
-      else
-        hipLaunchKernelGGL(k_gj_update<false>, dim3((unsigned)grid), dim3(256), 0, c->stream, A,
-                           N, nbk, Cb, R, nfreq, k2, nb2, Dn, Dw[(s + 1) & 1], c->d_flag);
-      GW_CHECK_LAUNCH(c, "k_gj_update");
-    }
-    kp = k;
-    nbp = nbk;
-  }
-  {
-    ProfScope ps(c, "gj_small");
-    const int s_last = (N + GB - 1) / GB - 1;
-    hipLaunchKernelGGL(k_gj_fix, dim3((N * nbp + 255) / 256, nfreq), dim3(256), 0, c->stream,
-                       A, N, kp, nbp, Rw[s_last & 1], Dw[s_last & 1]);
-    GW_CHECK_LAUNCH(c, "k_gj_fix");
-  }
-  {
-    ProfScope ps(c, "eps_unscale");
-    hipLaunchKernelGGL(k_unscale, dim3((unsigned)((nn + 255) / 256), nfreq), dim3(256), 0,
-                       c->stream, A, vcoul, N);
-    GW_CHECK_LAUNCH(c, "k_unscale");
-  }
-  return GW_OK;
+  return gj_steps(c, g, nfreq, N, "gj_diag", "gj_small", "gj_update", "eps_unscale");
 }
 
 // rmax[f] = max_ij |R_f[i][j] - delta_ij| (|re| + |im|), one workgroup per

@@ -23,8 +23,8 @@
 #include <sstream>
 #include <tuple>
 
+#include "gj.h"
 #include "mtxel_mm.h"
-#include "tiles.h"
 
 namespace gw {
 
@@ -36,18 +36,6 @@ struct ChiQ {
   double* chi;
   int P, neps, skip, pad;
 };
-
-struct GjM {
-  cpx<double>* A;          // eps~ in place, then eps^-1 (the caller's epsinv slice)
-  const cpx<double>* chi;  // chi0 slice
-  const double* v;         // v(q+G)
-  cpx<double>* R;          // [PB][N]
-  cpx<double>* Cb;         // [N][PB]
-  cpx<double>* D;          // [PB][PB]
-  int N, pad;
-};
-
-constexpr int PB = 64;  // Gauss-Jordan block width of the batched inversion
 
 // ------------------------------------------------------------------ batched contraction
 template <int WM, int BF16, typename Tin>
@@ -81,109 +69,29 @@ __global__ void k_zero_i32(int* p, int n) {
 }
 
 // ------------------------------------------------------------------ batched Gauss-Jordan
-// flags[m] = 1: some v <= 0 or a pivot that is not real and >= 1/2 (eps~ >= I).
-__global__ void k_gjb_build(const GjM* __restrict__ ms, int* __restrict__ flags) {
-  const GjM m = ms[blockIdx.y];
-  const size_t nn = (size_t)m.N * m.N;
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= nn) return;
-  const int i = (int)(idx / m.N), j = (int)(idx % m.N);
-  const double vi = m.v[i], vj = m.v[j];
-  if (!(vi > 0.0) || !(vi < INFINITY)) flags[blockIdx.y] = 1;
-  const double s = sqrt(vi) * sqrt(vj);
-  const cpx<double> x = m.chi[idx];
-  m.A[idx] = mk((i == j ? 1.0 : 0.0) - s * x.x, -s * x.y);
-}
-
-// Inverse of the diagonal block, register resident (gj_invert_64), as in the
-// single-matrix inversion; a ragged block is padded with the identity.
-__global__ void __launch_bounds__(1024) k_gjb_diag(const GjM* __restrict__ ms, int k,
-                                                   int* __restrict__ flags) {
-  static_assert(PB == 64, "gj_invert_64 holds a 64x64 block");
-  const GjM m = ms[blockIdx.x];
-  if (k >= m.N) return;
-  const int N = m.N, nbk = min(PB, N - k);
-  __shared__ cpx<double> rowb[2][PB], colb[2][PB];
-  const int tid = threadIdx.x, ti = tid / 32, tj = tid % 32;
-  cpx<double> d[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int i = ti + 32 * a, j = tj + 32 * b;
-      d[a][b] = (i < nbk && j < nbk) ? m.A[(size_t)(k + i) * N + k + j]
-                                     : mk(i == j ? 1.0 : 0.0, 0.0);
-    }
-  if (gj_invert_64<32>(d, nbk, rowb, colb)) flags[blockIdx.x] = 1;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int i = ti + 32 * a, j = tj + 32 * b;
-      if (i < nbk && j < nbk) m.D[i * PB + j] = d[a][b];
-    }
-}
-
-// R = Dinv A[K, :] (rows nbk.. of R are never read)
-__global__ void __launch_bounds__(256, 2) k_gjb_rpanel(const GjM* __restrict__ ms, int k) {
+// m.bad: some v <= 0; m.full: chi0 not exactly Hermitian, found against the mirror tile
+// through LDS (grid: tiles x tiles x matrices of 32 x 32)
+__global__ void __launch_bounds__(256) k_gjb_build(const GjM* __restrict__ ms) {
+  __shared__ cpx<double> mir[32][33];
   const GjM m = ms[blockIdx.z];
-  if (k >= m.N) return;
-  const int N = m.N, nbk = min(PB, N - k);
-  const int j0 = blockIdx.x * ZTM;
-  if (j0 >= N) return;
-  zgemm_tile(nbk, N, nbk, 1.0, 0.0, m.D, PB, m.A + (size_t)k * N, N, m.R, N, 0, j0);
-}
-
-// Cb = A[:, K]; R[:, K] = I + Dinv, so that A - Cb R leaves -Cb Dinv in the
-// column block (its Gauss-Jordan value)
-__global__ void k_gjb_prep(const GjM* __restrict__ ms, int k) {
-  const GjM m = ms[blockIdx.y];
-  if (k >= m.N) return;
-  const int N = m.N, nbk = min(PB, N - k);
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < N * nbk) {
-    const int i = e / nbk, t = e % nbk;
-    m.Cb[(size_t)i * PB + t] = m.A[(size_t)i * N + k + t];
-  }
-  if (e < nbk * nbk) {
-    const int t = e / nbk, j = e % nbk;
-    const cpx<double> dv = m.D[t * PB + j];
-    m.R[(size_t)t * N + k + j] = mk(dv.x + (t == j ? 1.0 : 0.0), dv.y);
-  }
-}
-
-// A -= Cb R over the whole matrix (the LDS-free rank-update tile)
-__global__ void __launch_bounds__(256, 3) k_gjb_update(const GjM* __restrict__ ms, int k) {
-  static_assert(PB == 64, "one 64x64 tile per workgroup");
-  const GjM m = ms[blockIdx.z];
-  if (k >= m.N) return;
-  const int N = m.N, nbk = min(PB, N - k);
-  const int i0 = blockIdx.y * PB, j0 = blockIdx.x * PB;
+  const int N = m.N, i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
   if (i0 >= N || j0 >= N) return;
-  const int wave = threadIdx.x >> 6;
-  gj_update_tile(m.Cb, PB, m.R, m.A, N, nbk, i0 + (wave >> 1) * 32, j0 + (wave & 1) * 32, N,
-                 m.A, N, 0);
-}
-
-// row block K <- R outside the K columns and Dinv inside
-__global__ void k_gjb_fix(const GjM* __restrict__ ms, int k) {
-  const GjM m = ms[blockIdx.y];
-  if (k >= m.N) return;
-  const int N = m.N, nbk = min(PB, N - k);
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nbk * N) return;
-  const int t = e / N, j = e % N;
-  m.A[(size_t)(k + t) * N + j] =
-      (j >= k && j < k + nbk) ? m.D[t * PB + (j - k)] : m.R[(size_t)t * N + j];
-}
-
-__global__ void k_gjb_unscale(const GjM* __restrict__ ms) {
-  const GjM m = ms[blockIdx.y];
-  const size_t nn = (size_t)m.N * m.N;
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= nn) return;
-  const int i = (int)(idx / m.N), j = (int)(idx % m.N);
-  m.A[idx] = scal(m.A[idx], sqrt(m.v[i]) / sqrt(m.v[j]));
+  const int c = threadIdx.x % 32, r0 = threadIdx.x / 32;
+  for (int r = r0; r < 32; r += 8)
+    if (j0 + r < N && i0 + c < N) mir[c][r] = m.chi[(size_t)(j0 + r) * N + i0 + c];
+  __syncthreads();
+  bool inexact = false;
+  for (int r = r0; r < 32; r += 8) {
+    const int i = i0 + r, j = j0 + c;
+    if (i >= N || j >= N) continue;
+    const double vi = m.v[i], vj = m.v[j];
+    if (j == 0 && (!(vi > 0.0) || !(vi < INFINITY))) *m.bad = 1;
+    const double s = sqrt(vi) * sqrt(vj);
+    const cpx<double> x = m.chi[(size_t)i * N + j], y = mir[r][c];
+    inexact = inexact || !(x.x == y.x && x.y == -y.y);
+    m.A[(size_t)i * N + j] = mk((i == j ? 1.0 : 0.0) - s * x.x, -s * x.y);
+  }
+  if (inexact) *m.full = 1;
 }
 
 }  // namespace gw
@@ -402,50 +310,15 @@ static gw_status enqueue_back(gw_plan* p) {
   // batched Gauss-Jordan over every (q, omega)
   {
     ProfScope ps(c, "plan_gj_build");
-    hipLaunchKernelGGL(k_zero_i32, dim3((p->nmat + 255) / 256), dim3(256), 0, c->stream, p->d_flags,
-                       p->nmat);
+    hipLaunchKernelGGL(k_zero_i32, dim3((2 * p->nmat + 255) / 256), dim3(256), 0, c->stream,
+                       p->d_flags, 2 * p->nmat);
     GW_CHECK_LAUNCH(c, "k_zero_i32");
-    const size_t nn = (size_t)p->nmax * p->nmax;
-    hipLaunchKernelGGL(k_gjb_build, dim3((unsigned)((nn + 255) / 256), p->nmat), dim3(256), 0,
-                       c->stream, p->d_gj, p->d_flags);
+    const unsigned nt = (unsigned)((p->nmax + 31) / 32);
+    hipLaunchKernelGGL(k_gjb_build, dim3(nt, nt, p->nmat), dim3(256), 0, c->stream, p->d_gj);
     GW_CHECK_LAUNCH(c, "k_gjb_build");
   }
-  const int tiles = (p->nmax + ZTM - 1) / ZTM;
-  for (int k = 0; k < p->nmax; k += PB) {
-    {
-      ProfScope ps(c, "plan_gj_small");
-      hipLaunchKernelGGL(k_gjb_diag, dim3(p->nmat), dim3(1024), 0, c->stream, p->d_gj, k,
-                         p->d_flags);
-      GW_CHECK_LAUNCH(c, "k_gjb_diag");
-      hipLaunchKernelGGL(k_gjb_rpanel, dim3(tiles, 1, p->nmat), dim3(256), 0, c->stream,
-                         p->d_gj, k);
-      GW_CHECK_LAUNCH(c, "k_gjb_rpanel");
-      hipLaunchKernelGGL(k_gjb_prep, dim3((PB * p->nmax + 255) / 256, p->nmat), dim3(256), 0,
-                         c->stream, p->d_gj, k);
-      GW_CHECK_LAUNCH(c, "k_gjb_prep");
-    }
-    {
-      ProfScope ps(c, "plan_gj_update");
-      hipLaunchKernelGGL(k_gjb_update, dim3(tiles, tiles, p->nmat), dim3(256), 0, c->stream,
-                         p->d_gj, k);
-      GW_CHECK_LAUNCH(c, "k_gjb_update");
-    }
-    {
-      ProfScope ps(c, "plan_gj_small");
-      hipLaunchKernelGGL(k_gjb_fix, dim3((PB * p->nmax + 255) / 256, p->nmat), dim3(256), 0,
-                         c->stream, p->d_gj, k);
-      GW_CHECK_LAUNCH(c, "k_gjb_fix");
-    }
-  }
-  {
-    ProfScope ps(c, "plan_gj_build");
-    const size_t nn = (size_t)p->nmax * p->nmax;
-    hipLaunchKernelGGL(k_gjb_unscale, dim3((unsigned)((nn + 255) / 256), p->nmat), dim3(256), 0,
-                       c->stream, p->d_gj);
-    GW_CHECK_LAUNCH(c, "k_gjb_unscale");
-  }
-  (void)st;
-  return GW_OK;
+  return gj_steps(c, GjTable{p->d_gj}, p->nmat, p->nmax, "plan_gj_small", "plan_gj_small",
+                  "plan_gj_update", "plan_gj_build");
 }
 
 static gw_status enqueue_all(gw_plan* p, int nbins) {
@@ -650,8 +523,8 @@ gw_status gw_plan_compile(gw_plan* p) {
   parts.push_back({reinterpret_cast<void**>(&p->d_items), (size_t)p->nitems * sizeof(int4)});
   parts.push_back({reinterpret_cast<void**>(&p->d_bins), ((size_t)p->nbins + 1) * sizeof(int)});
   parts.push_back({reinterpret_cast<void**>(&p->d_gj), (size_t)p->nmat * sizeof(GjM)});
-  parts.push_back({reinterpret_cast<void**>(&p->d_flags), (size_t)p->nmat * sizeof(int)});
-  std::vector<void*> gjR(p->nmat), gjC(p->nmat), gjD(p->nmat);
+  parts.push_back({reinterpret_cast<void**>(&p->d_flags), 2 * (size_t)p->nmat * sizeof(int)});
+  std::vector<void*> gjR(p->nmat), gjC(p->nmat), gjD(p->nmat);  // R twice, Cb, three blocks
   for (auto& q : p->q) {
     parts.push_back({&q.M, (size_t)q.P * q.d.neps * elem});
     parts.push_back({reinterpret_cast<void**>(&q.wts), (size_t)p->nfreq * q.P * sizeof(double)});
@@ -666,9 +539,9 @@ gw_status gw_plan_compile(gw_plan* p) {
     for (int f = 0; f < p->nfreq; ++f) {
       const int m = iq * p->nfreq + f;
       const size_t N = p->q[iq].d.neps;
-      parts.push_back({&gjR[m], PB * N * 16});
-      parts.push_back({&gjC[m], N * PB * 16});
-      parts.push_back({&gjD[m], PB * PB * 16});
+      parts.push_back({&gjR[m], 2 * GB * N * 16});
+      parts.push_back({&gjC[m], N * GB * 16});
+      parts.push_back({&gjD[m], 3 * GB * GB * 16});
     }
   size_t total = 0;
   for (auto& pt : parts) total += align_up(pt.second);
@@ -712,9 +585,14 @@ gw_status gw_plan_compile(gw_plan* p) {
       g.A = reinterpret_cast<cpx<double>*>(d.epsinv) + f * nn;
       g.chi = reinterpret_cast<const cpx<double>*>(d.chi0) + f * nn;
       g.v = d.vcoul;
-      g.R = static_cast<cpx<double>*>(gjR[m]);
+      g.R0 = static_cast<cpx<double>*>(gjR[m]);
+      g.R1 = g.R0 + (size_t)GB * d.neps;
       g.Cb = static_cast<cpx<double>*>(gjC[m]);
-      g.D = static_cast<cpx<double>*>(gjD[m]);
+      g.D0 = static_cast<cpx<double>*>(gjD[m]);
+      g.D1 = g.D0 + GB * GB;
+      g.Dn = g.D1 + GB * GB;
+      g.bad = p->d_flags + m;
+      g.full = p->d_flags + p->nmat + m;
       g.N = d.neps;
       g.pad = 0;
       p->h_gj[m] = g;
