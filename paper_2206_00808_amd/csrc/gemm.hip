@@ -403,7 +403,7 @@ gw_status chi0_splitbf16(gw_ctx* c, int P, int neps, const void* mtxel, int nfre
 
 // ---------------------------------------------------------------- generic ZGEMM
 // C[i][j] += alpha * sum_k A[i][k] B[k][j], complex double, row-major, batched on z.
-__global__ void __launch_bounds__(256) k_zgemm_nn(int m, int n, int kdim, double alpha,
+__global__ void __launch_bounds__(256, 2) k_zgemm_nn(int m, int n, int kdim, double alpha,
                                                   double beta,
                                                   const cpx<double>* __restrict__ A, int lda,
                                                   long long sA, const cpx<double>* __restrict__ B,
