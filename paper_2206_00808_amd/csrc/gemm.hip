@@ -277,6 +277,11 @@ static gw_status tile_order(gw_ctx* c, int nt, int GR, int GC, const int2** out)
   return GW_OK;
 }
 
+static int range_len(int P, int split) {
+  int pc = (P + split - 1) / split;
+  return (pc + BK - 1) / BK * BK;  // whole MFMA K steps; the last range is the short one
+}
+
 int chi0_split(gw_ctx* c, int P, int neps, int nfreq, gw_prec prec, gw_dtype dt) {
   if (prec == GW_PREC_SPLITBF16) return chi0_split_w(c, P, neps, nfreq);
   const int nt = (neps + kChiTM - 1) / kChiTM;
@@ -295,6 +300,24 @@ int chi0_split(gw_ctx* c, int P, int neps, int nfreq, gw_prec prec, gw_dtype dt)
     return r / std::ceil(r);
   };
   int best = 1;
+  if (b1 < c->cus) {
+    // Fewer tiles than CUs: the ranges put the idle ones to work.  A workgroup alone on its
+    // CU takes about 0.135 us per pair, one of k 0.1 k, and 6 us for its start and epilogue;
+    // the extra pass takes 5 us and its bytes.  59 vectors, 256 pairs: 52 us in one range,
+    // 32 in eight; 100 vectors, 12800 pairs: 1398 in four, 68 in 64.  Three frequencies of
+    // 700 vectors, 800 pairs, stay in one (123 us; 132 in two, which share the CUs).
+    const double mat = (double)nfreq * neps * neps * 16.0;
+    double bt = 0.0;
+    for (int s = 1; s <= 64; ++s) {
+      if (s > 1 && (P / s < 32 || (s - 1) * mat > 268435456.0)) break;
+      const long long share = (b1 * s + c->cus - 1) / c->cus;  // workgroups per CU
+      const double t = (share == 1 ? 0.135 : 0.1 * share) * range_len(P, s) + 6.0 +
+                       (s > 1 ? 5.0 + (s + 2) * mat / 4e6 : 0.0);
+      if ((long long)range_len(P, s) * (s - 1) >= P) continue;  // an empty last range
+      if (s == 1 || t < 0.95 * bt) { best = s; bt = t; }
+    }
+    return best;
+  }
   double bf = fill(b1);
   for (int s = 2; s <= 4; ++s) {
     if (P / s < 1024) break;  // keep each range long against its epilogue and the extra pass
@@ -304,10 +327,6 @@ int chi0_split(gw_ctx* c, int P, int neps, int nfreq, gw_prec prec, gw_dtype dt)
   return best;
 }
 
-static int range_len(int P, int split) {
-  int pc = (P + split - 1) / split;
-  return (pc + BK - 1) / BK * BK;  // whole MFMA K steps; the last range is the short one
-}
 
 static gw_status chi0_reduce(gw_ctx* c, int neps, int nfreq, double* chi0, int split,
                              const double* part) {
