@@ -11,7 +11,7 @@
 //      Eisenstat 1994), and one product on the FP64 matrix cores (k_dc_gemm).
 //   3. The reflectors are applied to the wanted vectors in blocks of 32 (k_bt_*).
 //
-// A tenth of the eigenvectors of a 1000-row matrix take 7.4 ms, all of them 7.8; two-sided
+// A tenth of the eigenvectors of a 1000-row matrix take 6.9 ms, all of them 7.3; two-sided
 // Jacobi rounds on 32 x 32 blocks took 50 ms (13 sweeps of 63 rounds of two kernels).
 //
 // Everything is in FP64.  The matrix is first scaled by a power of two to entries below
@@ -250,21 +250,24 @@ __device__ __forceinline__ void tri_vectors(const cpx<double>* __restrict__ A, i
 }
 
 // Step j: the rows below j of the matrix take the pending rank-two update and their
-// product with the new reflector, one wavefront per row; its row, up to 1024
-// columns, is fetched before the vectors are formed.  Up to 256 Q rows every workgroup forms
-// the vectors anew in its LDS, which costs less than a second launch; with Q = 0 they
-// come from global memory (k_tri_vec).
+// product with the new reflector, S wavefronts per row; a row, up to 1024 columns, is
+// fetched before the vectors are formed.  Up to T Q rows every workgroup forms the vectors
+// anew in its LDS, which costs less than a second launch; with Q = 0 they come from global
+// memory (k_tri_vec).
 //
 // One kernel boundary per column orders the steps (each row of y needs the whole new
-// reflector, and the next reflector all of y).  Bound: the latency of that chain,
-// 6.0 us per column over the 1000 columns of a 1000-row matrix (7.4 above 512 rows, 4.1
-// below 256; 8.0 with the vectors' passes through LDS).  Of the 7.4, the launch and the
-// vectors are 4.3, the stores 0.7.
-// first group of four rows of step j's grid: a multiple of the XCD count, so that a
-// group, which is workgroup (group mod 8) of every step, stays with one XCD's L2
-__host__ __device__ __forceinline__ int tri_group(int j) { return (j + 1) / 4 / kXcd * kXcd; }
-template <int Q>
-__global__ void __launch_bounds__(256) k_tri_step(cpx<double>* __restrict__ A, int N, int j,
+// reflector, and the next reflector all of y).  Bound: the latency of that chain, 5.9 us
+// per column over the 1000 columns of a 1000-row matrix (7.2 above 512 rows, 4.1 below
+// 256; 8.0 with the vectors' passes through LDS).  Of the 7.2, the launch and the vectors
+// are about 4.  Above 256 rows two wavefronts share a row: 7.2 us above 512 rows, 7.4 with
+// one, 7.7 with four (and 8.2 with one each for eight rows per workgroup).
+// first group of `rows` rows (a workgroup's) of step j's grid: a multiple of the XCD count,
+// so that a group, which is workgroup (group mod 8) of every step, stays with one XCD's L2
+__host__ __device__ __forceinline__ int tri_group(int j, int rows) {
+  return (j + 1) / rows / kXcd * kXcd;
+}
+template <int Q, int T, int S>
+__global__ void __launch_bounds__(T) k_tri_step(cpx<double>* __restrict__ A, int N, int j,
                                                   const cpx<double>* __restrict__ vprev,
                                                   const cpx<double>* __restrict__ yprev,
                                                   const cpx<double>* __restrict__ wg,
@@ -273,23 +276,26 @@ __global__ void __launch_bounds__(256) k_tri_step(cpx<double>* __restrict__ A, i
                                                   double* __restrict__ d,
                                                   cpx<double>* __restrict__ e) {
   extern __shared__ char smem[];
-  __shared__ double red[10];
+  __shared__ double red[2 * (T / 64) + 2];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, n = N - j;
-  const int i = tri_group(j) * 4 + blockIdx.x * 4 + wave - j;  // row j + i
+  constexpr int rows = T / 64 / S;
+  __shared__ cpx<double> ysum[T / 64];
+  const int first = 1 + lane + 64 * (wave % S);  // this wavefront's columns: first + 64 S q
+  const int i = (tri_group(j, rows) + blockIdx.x) * rows + wave / S - j;  // row j + i
   const bool live = i > 0 && i < n;
   cpx<double>* row = A + (size_t)(j + (live ? i : 0)) * N + j;
-  constexpr int kPre = Q == 0 ? 8 : Q < 4 ? 4 * Q : 16;
+  constexpr int kPre = Q == 0 ? 8 : Q * T / 64 / S < 16 / S ? Q * T / 64 / S : 16 / S;
   cpx<double> a[kPre];
 #pragma unroll
   for (int q = 0; q < kPre; ++q) {
-    const int k = 1 + lane + 64 * q;
+    const int k = first + 64 * S * q;
     a[q] = live && k < n ? row[k] : mk(0.0, 0.0);
   }
   const cpx<double>*w, *vo, *vn;
   if (Q > 0) {
     auto* ls = reinterpret_cast<cpx<double>*>(smem);
     const bool lead = blockIdx.x == 0;
-    tri_vectors<256, Q ? Q : 1>(A, N, j, vprev, yprev, red, d, e, lead,
+    tri_vectors<T, Q ? Q : 1>(A, N, j, vprev, yprev, red, d, e, lead,
                                 [&](int k, cpx<double> v, cpx<double> u, cpx<double> x) {
                                   ls[k] = u;
                                   ls[n + k] = v;
@@ -301,15 +307,15 @@ __global__ void __launch_bounds__(256) k_tri_step(cpx<double>* __restrict__ A, i
     vo = ls + n;
     vn = ls + 2 * n;
     if (lead)
-      for (int k = t; k < j; k += 256) vout[k] = mk(0.0, 0.0);
+      for (int k = t; k < j; k += T) vout[k] = mk(0.0, 0.0);
   } else {
     w = wg + j;
     vo = vprev + j;
     vn = vout + j;
   }
-  if (!live) return;
   const bool pend = j > 0;
-  const cpx<double> vi = pend ? vo[i] : mk(0.0, 0.0), wi = pend ? w[i] : mk(0.0, 0.0);
+  const cpx<double> vi = pend && live ? vo[i] : mk(0.0, 0.0),
+                    wi = pend && live ? w[i] : mk(0.0, 0.0);
   cpx<double> acc = mk(0.0, 0.0);
   auto one = [&](int k, cpx<double> x) {
     if (pend) {
@@ -322,23 +328,34 @@ __global__ void __launch_bounds__(256) k_tri_step(cpx<double>* __restrict__ A, i
   };
 #pragma unroll
   for (int q = 0; q < kPre; ++q) {
-    const int k = 1 + lane + 64 * q;
-    if (k < n) one(k, a[q]);
+    const int k = first + 64 * S * q;
+    if (live && k < n) one(k, a[q]);
   }
-  for (int k0 = 1 + 64 * kPre; k0 < n; k0 += 64 * kPre) {
+  for (int k0 = first + 64 * S * kPre; live && k0 < n; k0 += 64 * S * kPre) {
 #pragma unroll
     for (int q = 0; q < kPre; ++q) {
-      const int k = k0 + lane + 64 * q;
+      const int k = k0 + 64 * S * q;
       if (k < n) a[q] = row[k];
     }
 #pragma unroll
     for (int q = 0; q < kPre; ++q) {
-      const int k = k0 + lane + 64 * q;
-      if (k < n) one(k, a[q]);
+      const int k = k0 + 64 * S * q;
+      if (live && k < n) one(k, a[q]);
     }
   }
   const double yr = wsum(acc.x), yi = wsum(acc.y);
-  if (lane == 0) yout[j + i] = mk(yr, yi);
+  if (S == 1) {
+    if (live && lane == 0) yout[j + i] = mk(yr, yi);
+    return;
+  }
+  if (lane == 0) ysum[wave] = mk(yr, yi);
+  __syncthreads();
+  if (live && lane == 0 && wave % S == 0) {
+    cpx<double> y = ysum[wave];
+#pragma unroll
+    for (int q = 1; q < S; ++q) y = y + ysum[wave + q];
+    yout[j + i] = y;
+  }
 }
 
 // The vectors of a step above kTriFused rows, where every workgroup's own copy would not
@@ -1172,23 +1189,24 @@ gw_status herm_eig_top(gw_ctx* c, int N, int nb, cpx<double>* A, cpx<double>* U,
   {
     ProfScope ps(c, "lowrank_tridiag");
     if (N * 48 > 65536)
-      GW_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tri_step<8>),
+      GW_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tri_step<4, 512, 2>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kTriFused * 48));
     hipLaunchKernelGGL(k_eig_scale, dim3(gnn), dim3(256), 0, c->stream, A, N, ex);
     for (int j = 0; j < N; ++j) {
       const int n = N - j;
-      const dim3 grid(std::max(1, (N + 3) / 4 - tri_group(j)));
+      const int T = n > 256 && n <= kTriFused ? 512 : 256, rows = 4;
+      const dim3 grid(std::max(1, (N + rows - 1) / rows - tri_group(j, rows)));
       const cpx<double>* vp = V + (size_t)std::max(j - 1, 0) * N;
       cpx<double>* vo = V + (size_t)j * N;
       if (n > kTriFused)
         hipLaunchKernelGGL(k_tri_vec, dim3(1), dim3(1024), 0, c->stream, A, N, j, vp,
                            y[(j + 1) & 1], wv, vo, d, e);
-      auto* step = n > kTriFused ? &k_tri_step<0>
-                   : n > 1024    ? &k_tri_step<8>
-                   : n > 512     ? &k_tri_step<4>
-                   : n > 256     ? &k_tri_step<2>
-                                 : &k_tri_step<1>;
-      hipLaunchKernelGGL(step, grid, dim3(256), n > kTriFused ? 0 : (size_t)n * 48, c->stream, A,
+      auto* step = n > kTriFused ? &k_tri_step<0, 256, 1>
+                   : n > 1024    ? &k_tri_step<4, 512, 2>
+                   : n > 512     ? &k_tri_step<2, 512, 2>
+                   : n > 256     ? &k_tri_step<1, 512, 2>
+                                 : &k_tri_step<1, 256, 1>;
+      hipLaunchKernelGGL(step, grid, dim3(T), n > kTriFused ? 0 : (size_t)n * 48, c->stream, A,
                          N, j, vp, y[(j + 1) & 1], wv, vo, y[j & 1], d, e);
     }
     GW_CHECK_LAUNCH(c, "tridiagonal reduction");
