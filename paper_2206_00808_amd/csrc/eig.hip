@@ -159,7 +159,8 @@ __global__ void k_eig_scale(cpx<double>* __restrict__ A, int N, int ex) {
 // The reflector of a column c with |c|^2 = n2 below the diagonal and first entry c1:
 // u = c - beta e_1 with beta = -(c1 / |c1|) |c|, v' = u / |u|.  A column of at most one
 // entry below the diagonal, or of a norm that vanishes against the matrix (entries below
-// one), is left as it is (v' = 0).
+// one), is left as it is (v' = 0).  |c1| is not taken from a square that is subnormal or
+// zero: u must have |u|^2 = 2 |c| (|c| + |c1|) to working precision for H to be unitary.
 struct Reflector {
   cpx<double> u1, e;  // first entry of u; the off-diagonal entry that remains
   double inv;         // 1 / |u|, 0 where the column is left
@@ -170,9 +171,11 @@ __device__ __forceinline__ Reflector reflector(double n2, cpx<double> c1, int n)
   r.inv = 0.0;
   r.e = n == 2 ? c1 : mk(0.0, 0.0);
   if (n > 2 && n2 > 1e-290) {
-    const double nrm = sqrt(n2), al = sqrt(c1.x * c1.x + c1.y * c1.y);
+    const double nrm = sqrt(n2), a2 = c1.x * c1.x + c1.y * c1.y;
+    const double al = a2 > 1e-280 ? sqrt(a2) : hypot(c1.x, c1.y);
     const double ia = nrm / al;
-    const cpx<double> b = al > 0.0 ? scal(c1, ia) : mk(nrm, 0.0);
+    // below 1e-290 of a norm of at least 1e-145 c1 vanishes, and its phase is free
+    const cpx<double> b = al > 1e-290 ? scal(c1, ia) : mk(nrm, 0.0);
     r.e = mk(-b.x, -b.y);
     r.u1 = c1 + b;
     r.inv = 1.0 / sqrt(2.0 * nrm * (nrm + al));
