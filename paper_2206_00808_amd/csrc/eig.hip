@@ -390,7 +390,8 @@ __global__ void __launch_bounds__(1024) k_tri_phase(const cpx<double>* __restric
     const cpx<double> x = e[j];
     const double m = hypot(x.x, x.y);
     *mag = m;
-    return m > 0.0 ? mk(x.x / m, x.y / m) : mk(1.0, 0.0);
+    // an entry so small vanishes against the norm, and a subnormal m gives no unit vector
+    return m > 1e-290 ? mk(x.x / m, x.y / m) : mk(1.0, 0.0);
   };
   auto norm1 = [](cpx<double> z) { return scal(z, 1.0 / hypot(z.x, z.y)); };
   cpx<double> p = mk(1.0, 0.0);

@@ -59,6 +59,11 @@ def test_subdiagonal_entry_whose_square_underflows(n, x):
     _check(h, n)
 
 
+@pytest.mark.parametrize("x", [1e-160, 1e-310, 3e-324])
+def test_two_rows_with_a_vanishing_entry(x):
+    _check(np.array([[2.0, x * (1 - 1j)], [x * (1 + 1j), -1.0]]), 2)
+
+
 @pytest.mark.parametrize("n", [15, 16, 17, 34, 35])
 @pytest.mark.parametrize("kind", ["random", "rank", "fourfold", "graded"])
 def test_edges_of_leaves_and_blocks(kind, n):
