@@ -39,6 +39,20 @@ __global__ void k_eps_build(const cpx<double>* __restrict__ chi, const double* _
   A[off] = mk((i == j ? 1.0 : 0.0) - v[i] * x.x, -v[i] * x.y);
 }
 
+// 1 / p of a pivot whose square leaves the normal range (a subnormal square loses the
+// pivot's digits and has no reciprocal): p is scaled by a power of two to order one first.
+// The back substitution raises flag[1] at such a pivot, and the matrix is factored again
+// with this inverse: any test in the panels' chain of columns cost 1.4% of them.
+__device__ __forceinline__ cpx<double> scaled_inverse(cpx<double> p) {
+  int e = 0;
+  (void)frexp(fmax(fabs(p.x), fabs(p.y)), &e);
+  const double x = ldexp(p.x, -e), y = ldexp(p.y, -e), den = x * x + y * y;
+  return mk(ldexp(x / den, -e), ldexp(-y / den, -e));
+}
+__device__ __forceinline__ bool square_in_range(double abs1) {
+  return abs1 > 1e-140 && abs1 < 1e140;
+}
+
 __global__ void __launch_bounds__(1024) k_lu_panel(cpx<double>* __restrict__ A, int N, int k,
                                                    int nbk, int* __restrict__ ipiv,
                                                    int* __restrict__ flag) {
@@ -87,7 +101,8 @@ __global__ void __launch_bounds__(1024) k_lu_panel(cpx<double>* __restrict__ A, 
     if (pm > 0.0) {
       const cpx<double> piv = prow[jj];
       const double den = piv.x * piv.x + piv.y * piv.y;
-      const cpx<double> inv = mk(piv.x / den, -piv.y / den);
+      const cpx<double> inv =
+          square_in_range(pm) ? mk(piv.x / den, -piv.y / den) : scaled_inverse(piv);
       for (int i = j + 1 + tid; i < N; i += nt) {
         cpx<double>* row = A + (size_t)i * N + k;
         const cpx<double> l = cmul(row[jj], inv);
@@ -117,7 +132,7 @@ __global__ void __launch_bounds__(1024) k_lu_panel(cpx<double>* __restrict__ A, 
 constexpr int SW = 8;           // sub-panel width
 constexpr int kPanelT = 256;    // threads: one wavefront per SIMD, up to 12 rows each
 
-// 1 / x: the hardware estimate and two Newton steps
+// 1 / x for normal x: the hardware estimate and two Newton steps
 __device__ __forceinline__ double rcp_newton(double x) {
   double r = __builtin_amdgcn_rcp(x);
   r = fma(fma(-x, r, 1.0), r, r);
@@ -369,10 +384,10 @@ __device__ __forceinline__ double quad_get(double v, int from) {
   }
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
-template <bool UPPER>
+template <bool UPPER, bool SCALED>
 __global__ void __launch_bounds__(64) k_trsm_block(const cpx<double>* __restrict__ LU, int N,
                                                    int kb, int nbk, cpx<double>* __restrict__ X,
-                                                   int c0, int ncols) {
+                                                   int c0, int ncols, int* __restrict__ flag) {
   __shared__ cpx<double> T[NB][NB + 1];  // T[column][row]: the rows a column is taken out of
   __shared__ cpx<double> dinv[NB];
   LU += (size_t)blockIdx.y * N * N;
@@ -392,7 +407,13 @@ __global__ void __launch_bounds__(64) k_trsm_block(const cpx<double>* __restrict
     T[cc][r] = (UPPER ? r < cc : r > cc) ? t : mk(0.0, 0.0);
     if (UPPER && r == cc) {
       const double den = t.x * t.x + t.y * t.y;
-      dinv[r] = in ? mk(t.x / den, -t.y / den) : mk(0.0, 0.0);
+      cpx<double> inv = mk(t.x / den, -t.y / den);
+      const double abs1 = fabs(t.x) + fabs(t.y);
+      if (in && !square_in_range(abs1)) {
+        if (SCALED) inv = scaled_inverse(t);
+        else if (abs1 != 0.0) flag[1] = 1;
+      }
+      dinv[r] = in ? inv : mk(0.0, 0.0);
     }
   }
   __syncthreads();
@@ -600,8 +621,10 @@ gw_status sigma_sx_static(gw_ctx* c, int nocc, int nband, int N, const void* mtx
   return GW_OK;
 }
 
-gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
-                             const double* vcoul, double* epsinv) {
+// one factorisation and its substitutions; *again: a pivot's square left the normal range
+// and `scaled` was not set
+static gw_status epsinv_pivoted(gw_ctx* c, int N, int nfreq, const double* chi0,
+                                const double* vcoul, double* epsinv, bool scaled, bool* again) {
   const size_t nn = (size_t)N * N;
   const size_t bytes = align_up(nfreq * nn * 16) + 2 * align_up((size_t)nfreq * N * 4) +
                        align_up((size_t)nfreq * N * NB * 16);
@@ -631,7 +654,7 @@ gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
     {
       ProfScope ps(c, "lu_panel");
       // rows per thread that fit the registers; more rows stay in global memory
-      switch ((N - k + kPanelT - 1) / kPanelT) {
+      switch (scaled ? 0 : (N - k + kPanelT - 1) / kPanelT) {
 #define GW_PANEL(R)                                                                          \
   case R:                                                                                    \
     hipLaunchKernelGGL(k_lu_panel_reg<R>, dim3(nfreq), dim3(kPanelT), 0, c->stream, LU, N, k, \
@@ -656,8 +679,8 @@ gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
     if (rest > 0) {
       {
         ProfScope ps(c, "lu_trsm");
-        hipLaunchKernelGGL(k_trsm_block<false>, dim3((rest + 15) / 16, nfreq), dim3(64), 0,
-                           c->stream, LU, N, k, nbk, LU, k + nbk, rest);
+        hipLaunchKernelGGL((k_trsm_block<false, false>), dim3((rest + 15) / 16, nfreq), dim3(64), 0,
+                           c->stream, LU, N, k, nbk, LU, k + nbk, rest, c->d_flag);
         GW_CHECK_LAUNCH(c, "k_trsm_block");
       }
       st = zgemm_nn(c, rest, rest, nbk, -1.0, LUd, (size_t)(k + nbk) * N + k, N, s2, LUd,
@@ -680,8 +703,8 @@ gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
     const int nbk = std::min(NB, N - kb);
     {
       ProfScope ps(c, "inv_trsm_lower");
-      hipLaunchKernelGGL(k_trsm_block<false>, dim3((N + 15) / 16, nfreq), dim3(64), 0,
-                         c->stream, LU, N, kb, nbk, Y, 0, N);
+      hipLaunchKernelGGL((k_trsm_block<false, false>), dim3((N + 15) / 16, nfreq), dim3(64), 0,
+                         c->stream, LU, N, kb, nbk, Y, 0, N, c->d_flag);
       GW_CHECK_LAUNCH(c, "k_trsm_block");
     }
     const int below = N - kb - nbk;
@@ -699,8 +722,9 @@ gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
     const int nbk = std::min(NB, N - kb);
     {
       ProfScope ps(c, "inv_trsm_upper");
-      hipLaunchKernelGGL(k_trsm_block<true>, dim3((N + 15) / 16, nfreq), dim3(64), 0,
-                         c->stream, LU, N, kb, nbk, Y, 0, N);
+      auto* solve = scaled ? &k_trsm_block<true, true> : &k_trsm_block<true, false>;
+      hipLaunchKernelGGL(solve, dim3((N + 15) / 16, nfreq), dim3(64), 0, c->stream, LU, N, kb, nbk,
+                         Y, 0, N, c->d_flag);
       GW_CHECK_LAUNCH(c, "k_trsm_block");
     }
     if (kb > 0) {
@@ -709,11 +733,22 @@ gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
       if (st != GW_OK) return st;
     }
   }
-  int flag = 0;
-  GW_HIP(c, hipMemcpyAsync(&flag, c->d_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+  int flag[2] = {0, 0};
+  GW_HIP(c, hipMemcpyAsync(flag, c->d_flag, sizeof flag, hipMemcpyDeviceToHost, c->stream));
   GW_HIP(c, hipStreamSynchronize(c->stream));
-  if (flag) return fail(c, GW_ESINGULAR, "eps has a zero pivot (singular dielectric matrix)");
+  // what follows such a pivot is not finite, so it comes before the zero pivots
+  *again = flag[1] && !scaled;
+  if (flag[0] && !*again)
+    return fail(c, GW_ESINGULAR, "eps has a zero pivot (singular dielectric matrix)");
   return GW_OK;
+}
+
+gw_status epsinv_pivoted_one(gw_ctx* c, int N, int nfreq, const double* chi0,
+                             const double* vcoul, double* epsinv) {
+  bool again = false;
+  gw_status st = epsinv_pivoted(c, N, nfreq, chi0, vcoul, epsinv, false, &again);
+  if (st == GW_OK && again) st = epsinv_pivoted(c, N, nfreq, chi0, vcoul, epsinv, true, &again);
+  return st;
 }
 
 static gw_status epsinv_gauss_jordan(gw_ctx* c, int N, int nfreq, const double* chi0,
