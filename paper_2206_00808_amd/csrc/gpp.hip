@@ -92,7 +92,7 @@ __global__ void __launch_bounds__(256, 2) k_sigma_gpp(
     const double* __restrict__ energies, int ntc, cpx<double>* __restrict__ part) {
   // rows sharing one reciprocal: at most 12 squares are multiplied, so that their product
   // stays in range while every |d - wt| is between 1e-12 and 1e12
-  constexpr int kRB = NE <= 3 ? 4 : 2;
+  constexpr int kRB = NE <= 3 ? 4 : 1;
   __shared__ cpx<double> mrow[kChunk][kTR];
   __shared__ cpx<double> mcol[kChunk][kTC];
   __shared__ double dst[kChunk][NE];
@@ -139,7 +139,9 @@ __global__ void __launch_bounds__(256, 2) k_sigma_gpp(
   };
 
   cpx<double> acoh[NE], asx[NE];
-  // occupied n'': COH and SX; a row's reciprocals come from one of their product
+  // occupied n'': COH and SX.  The rows of one energy and sign share a reciprocal, as they
+  // go into the same sum: a pole met exactly at one energy, or an energy that is not
+  // finite, leaves the others alone, and one of d + wt leaves COH alone
   {
     cpx<double> D[kRows][NE], own = mk(0.0, 0.0);
 #pragma unroll
@@ -151,34 +153,42 @@ __global__ void __launch_bounds__(256, 2) k_sigma_gpp(
       stage(a0, na);
       for (int s = 0; s < na; ++s) {
         const cpx<double> mc = mcol[s][c];
+        cpx<double> C[kRows];
+        double cyw[kRows], cxw[kRows];
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
-          const cpx<double> C = cmulc(mrow[s][rg * kRows + r], mc);
-          if (r == diag) own = own + C;
-          const double cyw = C.y * wy[r], cxw = C.x * wy[r];
-          double z1[NE], z2[NE], x[2 * NE], pre[2 * NE];
+          C[r] = cmulc(mrow[s][rg * kRows + r], mc);
+          if (r == diag) own = own + C[r];
+          cyw[r] = C[r].y * wy[r];
+          cxw[r] = C[r].x * wy[r];
+        }
 #pragma unroll
-          for (int k = 0; k < NE; ++k) {
-            const double d = dst[s][k];
-            z1[k] = d - wx[r];
-            z2[k] = d + wx[r];
-            x[2 * k] = fma(z1[k], z1[k], wy2[r]);
-            x[2 * k + 1] = fma(z2[k], z2[k], wy2[r]);
-            pre[2 * k] = k == 0 ? x[0] : pre[2 * k - 1] * x[2 * k];
-            pre[2 * k + 1] = pre[2 * k] * x[2 * k + 1];
+        for (int k = 0; k < NE; ++k) {
+          const double d = dst[s][k];
+          double z1[kRows], z2[kRows], x1[kRows], x2[kRows], p1[kRows], p2[kRows];
+#pragma unroll
+          for (int r = 0; r < kRows; ++r) {
+            z1[r] = d - wx[r];
+            z2[r] = d + wx[r];
+            x1[r] = fma(z1[r], z1[r], wy2[r]);
+            x2[r] = fma(z2[r], z2[r], wy2[r]);
+            p1[r] = r == 0 ? x1[0] : p1[r - 1] * x1[r];
+            p2[r] = r == 0 ? x2[0] : p2[r - 1] * x2[r];
           }
-          double rr = rcp_nr(pre[2 * NE - 1]);
+          double q1 = rcp_nr(p1[kRows - 1]), q2 = rcp_nr(p2[kRows - 1]);
 #pragma unroll
-          for (int k = NE - 1; k >= 0; --k) {
-            const double y2 = rr * pre[2 * k];
-            rr *= x[2 * k + 1];
-            const double y1 = k == 0 ? rr : rr * pre[2 * k - 1];
-            if (k > 0) rr *= x[2 * k];
+          for (int r = kRows - 1; r >= 0; --r) {
+            const double y1 = r == 0 ? q1 : q1 * p1[r - 1], y2 = r == 0 ? q2 : q2 * p2[r - 1];
+            if (r > 0) {
+              q1 *= x1[r];
+              q2 *= x2[r];
+            }
             // C / (d - wt) and C / (d - wt) - C / (d + wt)
-            const cpx<double> r1 = mk(y1 * fma(C.x, z1[k], -cyw), y1 * fma(C.y, z1[k], cxw));
+            const cpx<double> r1 =
+                mk(y1 * fma(C[r].x, z1[r], -cyw[r]), y1 * fma(C[r].y, z1[r], cxw[r]));
             S[r][k] = S[r][k] + r1;
-            D[r][k] = D[r][k] + mk(fma(-y2, fma(C.x, z2[k], cyw), r1.x),
-                                   fma(-y2, fma(C.y, z2[k], -cxw), r1.y));
+            D[r][k] = D[r][k] + mk(fma(-y2, fma(C[r].x, z2[r], cyw[r]), r1.x),
+                                   fma(-y2, fma(C[r].y, z2[r], -cxw[r]), r1.y));
           }
         }
       }

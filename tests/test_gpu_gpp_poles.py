@@ -1,0 +1,66 @@
+"""GPU plasmon-pole self-energy where one of a band's energies meets a pole exactly or is
+not finite: the band's other energies, and the other sums, keep their values."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _run(P, m, en, nocc, v, amp, wt, ee):
+    nn, nb, n = m.shape
+    ctx = P.Context(0)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    sx = torch.zeros((nb, ee.shape[1]), dtype=torch.complex128, device="cuda")
+    coh = torch.zeros_like(sx)
+    P.gw_sigma_gpp(ctx, nn, nocc, nb, n, dev(m), dev(en), dev(v), dev(amp), dev(wt), dev(ee), 0.7,
+                   sx, coh)
+    ctx.close()
+    return sx.cpu().numpy(), coh.cpu().numpy()
+
+
+def _case(n, nn, ne):
+    rng = np.random.default_rng(100 * n + 10 * nn + ne)
+    m = rng.standard_normal((nn, 2, n)) + 1j * rng.standard_normal((nn, 2, n))
+    wt = rng.uniform(0.8, 3.0, (n, n)) + 1j * rng.uniform(0.05, 0.3, (n, n))
+    amp = rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))
+    # energies and poles in eighths, so that a pole can be met exactly
+    en = np.round(8 * rng.uniform(-4, 4, nn)) / 8 + 1 / 16
+    ee = rng.uniform(-0.2, 0.2, (2, ne))
+    return m, en, rng.uniform(0.1, 3.0, n), amp, wt, ee
+
+
+@pytest.mark.parametrize("n,nn", [(5, 3), (70, 40)])
+@pytest.mark.parametrize("ne", [2, 3, 4])
+@pytest.mark.parametrize("what", ["d=wt", "d=-wt", "nan", "inf"])
+def test_one_energy_of_occupied_states(what, ne, n, nn):
+    import paper_2206_00808_amd as P
+    m, en, v, amp, wt, ee = _case(n, nn, ne)
+    wt[2, 3] = 1.5  # a real pole; no other energy is near it
+    sx0, coh0 = _run(P, m, en, nn, v, amp, wt, ee)
+    assert np.isfinite(sx0).all() and np.isfinite(coh0).all()
+    hit = ee.copy()
+    hit[1, 1] = {"d=wt": en[2] + 1.5, "d=-wt": en[2] - 1.5, "nan": np.nan, "inf": np.inf}[what]
+    sx, coh = _run(P, m, en, nn, v, amp, wt, hit)
+    keep = np.ones_like(ee, dtype=bool)
+    keep[1, 1] = False
+    assert np.array_equal(sx[keep], sx0[keep]) and np.array_equal(coh[keep], coh0[keep])
+    if what == "d=-wt":
+        # COH has no such pole: the sum at that energy, each term to a few ulp, with every
+        # other pole at least 0.05 away
+        d = (hit[1, 1] - en)[:, None, None]
+        if (d == 1.5).any():
+            return  # another state meets + wt at this energy
+        h = 0.35 * np.conj(m[:, 1, :, None]) * m[:, 1, None, :] * v * amp / (d - wt)
+        assert abs(coh[1, 1] - h.sum()) <= 1e-14 * np.abs(h).sum() * np.log2(4 + nn * n)
+
+
+def test_four_energies_far_poles():
+    import paper_2206_00808_amd as P
+    m, en, v, amp, wt, ee = _case(20, 7, 4)
+    ref = _run(P, m, en, 3, v, np.where(np.arange(20)[:, None] == 6, 0, amp), wt, ee)
+    wt[6] = 1e25  # the terms of these poles vanish
+    got = _run(P, m, en, 3, v, np.where(np.arange(20)[:, None] == 6, 0, amp), wt, ee)
+    for a, b in zip(got, ref):
+        # the other rows' terms in a product with other rows' reciprocals: a few ulp of the sum
+        assert np.all(np.abs(a - b) <= 1e-13 * np.abs(b).max())
