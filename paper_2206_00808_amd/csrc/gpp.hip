@@ -199,7 +199,7 @@ __global__ void __launch_bounds__(256, 2) k_sigma_gpp(
       cpx<double> x = own;
 #pragma unroll
       for (int r = 0; r < kRows; ++r)
-        if (row0 + r < N && col < N)
+        if (nocc > 0 && row0 + r < N && col < N)
           x = x + scal(cmul(amp[(size_t)(row0 + r) * N + col], D[r][k]), 0.5);
       asx[k] = scal(x, vc);
     }

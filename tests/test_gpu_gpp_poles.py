@@ -55,6 +55,15 @@ def test_one_energy_of_occupied_states(what, ne, n, nn):
         assert abs(coh[1, 1] - h.sum()) <= 1e-14 * np.abs(h).sum() * np.log2(4 + nn * n)
 
 
+@pytest.mark.parametrize("ne", [1, 4])
+def test_no_occupied_state_leaves_sx(ne):
+    import paper_2206_00808_amd as P
+    m, en, v, amp, wt, ee = _case(20, 7, ne)
+    amp[3, 4] = np.inf
+    sx, _ = _run(P, m, en, 0, v, amp, wt, ee)
+    assert not sx.any()
+
+
 def test_four_energies_far_poles():
     import paper_2206_00808_amd as P
     m, en, v, amp, wt, ee = _case(20, 7, 4)
