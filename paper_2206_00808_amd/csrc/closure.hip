@@ -312,16 +312,18 @@ __global__ void __launch_bounds__(256, 2) k_cl_wgrad(ClWg W, long long rows, int
 #pragma unroll
       for (int i = 0; i < 32; ++i) v[i] = 0.f;
     }
+    float slab = 0.f;  // 32 rows at a time: a chain over all rows would round each at its sum
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       f8 t;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         t[k] = v[8 * i + k];
-        csum += t[k];
+        slab += t[k];
       }
       *reinterpret_cast<bf8*>(&S[buf][tid][8 * i]) = __builtin_convertvector(t, bf8);
     }
+    csum += slab;
     __syncthreads();
     if (r + 32 < r1) fetch(r + 32);
     if (work) {
@@ -565,10 +567,13 @@ struct ClBufs {
 // Row splits of the weight gradients: a multiple of the XCDs.  64 splits of the 12
 // tiles of a 256-wide, 3-deep network are 768 workgroups, and their partials
 // (35 MB) stay below a tenth of the operands' bytes from 60 k rows on.  Larger
-// networks have more tiles and take fewer splits: the partials stay within 256 MB
-// until the smallest number of splits is reached.
-static int cl_splits(size_t count) {
-  return (int)std::max<size_t>(kXcd, std::min<size_t>(64, ((64u << 20) / count) / kXcd * kXcd));
+// networks have more tiles and take fewer splits, so that the partials stay within
+// 256 MB, but not fewer than 32 of many rows: each split is a chain of sums in single
+// precision, and rows / 32 / splits terms and the splits together are never more than
+// with 32.
+static int cl_splits(size_t count, long long npad) {
+  const long long fit = std::min<long long>(64, (long long)((64u << 20) / count) / kXcd * kXcd);
+  return (int)std::max(fit, std::min<long long>(32, (npad + 8191) / 8192 * kXcd));
 }
 static constexpr int kRelBlocks = 256;  // workgroups of the fixed-order rel_F reduction
 
@@ -586,7 +591,7 @@ static gw_status cl_buffers(gw_mlp* net, int N, long long npad, bool train, ClBu
   add(&b->Y, (size_t)npad * CL_NOUT * 4);
   add(&b->dY, (size_t)npad * CL_NOUT * 4);
   add(&b->T, (size_t)npad * CL_NOUT * 4);
-  add(&b->part, train ? (size_t)cl_splits(net->count) * net->count * 4 : 0);
+  add(&b->part, train ? (size_t)cl_splits(net->count, npad) * net->count * 4 : 0);
   add(&b->wo, CL_NOUT * w * 4);
   add(&b->wb, net->count * 2);
   add(&b->wt, net->count * 2);
@@ -712,7 +717,7 @@ static gw_status cl_backward(gw_mlp* net, long long npad, ClBufs& b) {
     y.tile0 = W.tiles;
     W.tiles += y.tn * ((y.dout + WG_T - 1) / WG_T);
   }
-  const int splits = cl_splits(net->count);
+  const int splits = cl_splits(net->count, npad);
   const long long rchunk = ((npad + splits - 1) / splits + 31) / 32 * 32;
   ProfScope ps(c, "closure_wgrad");
   hipLaunchKernelGGL(k_cl_wgrad, dim3((unsigned)(W.tiles * splits)), dim3(256), 0, c->stream, W,
@@ -996,9 +1001,8 @@ gw_status gw_chi0_closure(gw_ctx* c, gw_mlp* net, int mode, int N, const double*
     {
       ProfScope ps(c, "closure_adam");
       hipLaunchKernelGGL(k_adam, dim3((unsigned)((net->count + 255) / 256)), dim3(256), 0,
-                         c->stream, net->p, b.part, cl_splits(net->count), net->m, net->v, net->count, lr, b1,
-                         b2, 1e-8f,
-                         bc1, bc2);
+                         c->stream, net->p, b.part, cl_splits(net->count, npad), net->m, net->v,
+                         net->count, lr, b1, b2, 1e-8f, bc1, bc2);
       GW_CHECK_LAUNCH(c, "k_adam");
     }
     net->ready = true;
