@@ -285,6 +285,7 @@ gw_status gw_ctx_destroy(gw_ctx* c) {
   }
   for (auto& kv : c->twiddles) (void)hipFree(kv.second);
   for (auto& kv : c->tile_orders) (void)hipFree(kv.second);
+  if (c->up) (void)hipStreamDestroy(c->up);
   if (c->ws) (void)hipFree(c->ws);
   if (c->d_flag) (void)hipFree(c->d_flag);
   pin_release(c);

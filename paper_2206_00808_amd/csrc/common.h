@@ -3,13 +3,13 @@
 
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <cstdint>
 #include <cstdio>
 #include <map>
 #include <memory>
 #include <set>
 #include <string>
-#include <tuple>
 #include <vector>
 
 #include "../../include/gw.h"
@@ -88,7 +88,10 @@ struct PinRec {
   hipEvent_t ev;   // recorded after that copy
 };
 
-struct MmTables;  // mtxel_mm.h
+// mtxel_mm.h
+struct MmTables;
+struct MmEps;
+using MmGridKey = std::array<int, 10>;
 
 }  // namespace gw
 
@@ -103,10 +106,13 @@ struct gw_ctx {
   size_t ws_used = 0;
   // cached device tables
   std::map<std::string, gw::SphereMap> spheres;
-  // transform tables per (valence, conduction, eps) sphere, spinor count and type; null
-  // where no dense-transform kernel is built for the sizes
-  std::map<std::tuple<const gw::SphereMap*, const gw::SphereMap*, const gw::SphereMap*, int, bool>,
-           std::shared_ptr<gw::MmTables>> mm;
+  // dense-transform tables: by the spheres' largest |g|, spinor count and type (null where
+  // no kernel is built for the sizes), and by eps sphere and axis order
+  std::map<gw::MmGridKey, std::shared_ptr<gw::MmTables>> mm_grid;
+  std::map<std::pair<const gw::SphereMap*, int>, std::shared_ptr<gw::MmEps>> mm_eps;
+  size_t mm_grid_bytes = 0, mm_eps_bytes = 0;
+  std::set<std::shared_ptr<void>> mm_held;        // those that captured graphs read
+  hipStream_t up = nullptr;                       // uploads of those tables
   std::map<std::pair<int, int>, void*> twiddles;  // (n, is_double) -> device table
   std::map<long long, void*> tile_orders;         // (tiles, block shape) -> chi0 tile order (int2)
   int* d_flag = nullptr;                          // device status flags

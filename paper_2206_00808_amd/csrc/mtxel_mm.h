@@ -8,6 +8,21 @@
 
 namespace gw {
 
+// One device allocation
+struct DevBuf {
+  char* p = nullptr;
+  size_t bytes = 0;
+  ~DevBuf();
+};
+
+// What depends on the eps sphere and the axis order alone: kept (|g1|, |g2|) quads and
+// the compact index map of the last transform.
+struct MmEps {
+  DevBuf dev;
+  int nq = 0, nq4 = 0;                  // quads, padded to 4
+  size_t o_qpos = 0, o_tab = 0;
+};
+
 // Spheres, grid and tables of one triple.  Axes are internal: 0 the planes' axis, 1
 // the rows of a plane, 2 the entries of a row; perm[a] is the caller's axis.
 struct MmTables {
@@ -22,19 +37,19 @@ struct MmTables {
   int rt = 1, ks = 1, jt = 1;           // row tiles of 16, K steps of 4, groups of 16 entries
   int ncz = 1, nry = 1, nx = 1;         // tiles of 8 kept |g| per axis 2, 1, 0
   int kx = 1;                           // K steps of the last transform
-  int nq = 0, nq4 = 0;                  // kept (|g1|, |g2|) quads, padded to 4
   size_t plane = 0;                     // elements of a plane of one band, all spinor components
-  char* dev = nullptr;                  // one allocation
-  size_t o_zc = 0, o_yc = 0, o_xc = 0, o_qpos = 0, o_tab = 0;
+  size_t o_zc = 0, o_yc = 0, o_xc = 0;
   struct Band {
     int kx, ky, ntz, ncol;              // K steps over axes 0 and 1, tiles over axis 2, columns
     size_t bx, by, bz;                  // coefficient tables
   } bv{}, bc{};
-  ~MmTables();
+  std::shared_ptr<DevBuf> grid;         // coefficients: they depend on the largest |g| alone
+  std::shared_ptr<MmEps> eps;
 };
 
-// Tables for the triple, from the context's cache or new; null when no kernel is
-// built for these sizes.  Allocates on first use; geps is read during the call.
+// Tables for the triple, from the context's caches or new; null when no kernel is
+// built for these sizes.  Allocates when an extent of the spheres or an eps sphere is
+// first met, also while the stream is captured; geps is read during the call.
 gw_status mm_tables(gw_ctx* c, const SphereMap* sv, const SphereMap* sc, const SphereMap* se,
                     const int32_t* geps, int nspinor, bool dbl, std::shared_ptr<MmTables>* out);
 size_t mm_workspace(const MmTables& t, int nv, int nc);

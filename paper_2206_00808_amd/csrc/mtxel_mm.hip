@@ -642,7 +642,7 @@ struct MmSizes {
 };
 MmSizes mm_sizes(const MmTables& t, int nv, int nc) {
   const size_t el = t.dbl ? 16 : 8;
-  const size_t t2_band = (size_t)nv * t.n[0] * t.nq4 * 4 * el;
+  const size_t t2_band = (size_t)nv * t.n[0] * t.eps->nq4 * 4 * el;
   const size_t u_band = (size_t)t.n[0] * t.plane * el;
   const size_t t1_c = (size_t)t.nspinor * t.n[0] * t.bc.ncol * el;
   const size_t t1_v = (size_t)t.nspinor * t.n[0] * t.bv.ncol * el;
@@ -671,7 +671,7 @@ BandSet<T> band_set(const MmTables& t, bool val, int nb, int ng, const cpx<T>* c
   const int* g = val ? t.gv : t.gc;
   const long long* st = val ? t.sv : t.sc;
   const MmTables::Band& b = val ? t.bv : t.bc;
-  auto tab = [&](size_t o) { return reinterpret_cast<const double*>(t.dev + o); };
+  auto tab = [&](size_t o) { return reinterpret_cast<const double*>(t.grid->p + o); };
   return BandSet<T>{coef, val ? t.cube_v : t.cube_c, st[0], st[1], st[2], ng, nb * t.nspinor, g[0],
                     g[1], g[2], b.kx, b.ky, b.ntz, tab(b.bx), tab(b.by), tab(b.bz), t1, u};
 }
@@ -716,9 +716,9 @@ gw_status launch_pair(gw_ctx* c, const MmTables& t, const cpx<T>* uv, const cpx<
   const long long tot = base * nvs;
   hipLaunchKernelGGL(k, dim3((unsigned)((tot + kXcd - 1) / kXcd * kXcd)), dim3(256), lds,
                      c->stream, uv, uc, t.plane, nv, nct, nvs, t.n[0], t.n[1], t.ncz, t.nry,
-                     reinterpret_cast<const T*>(t.dev + t.o_zc),
-                     reinterpret_cast<const T*>(t.dev + t.o_yc),
-                     reinterpret_cast<const int*>(t.dev + t.o_qpos), t.ge[1], t.ge[2], t.nq4, t2);
+                     reinterpret_cast<const T*>(t.grid->p + t.o_zc),
+                     reinterpret_cast<const T*>(t.grid->p + t.o_yc),
+                     reinterpret_cast<const int*>(t.eps->dev.p + t.eps->o_qpos), t.ge[1], t.ge[2], t.eps->nq4, t2);
   GW_CHECK_LAUNCH(c, "k_mm_pair");
   return GW_OK;
 }
@@ -773,7 +773,7 @@ gw_status run_mtxel(gw_ctx* c, const MmTables& t, int nv, int ngv, const cpx<T>*
       if (st != GW_OK) return st;
     }
     ProfScope ps(c, "pair_xpass");
-    const long long tasks = (long long)nv * nct * (t.nq4 / 4), blocks = (tasks + 3) / 4;
+    const long long tasks = (long long)nv * nct * (t.eps->nq4 / 4), blocks = (tasks + 3) / 4;
     const dim3 gr((unsigned)((blocks + kXcd - 1) / kXcd * kXcd)), bl(256);
     const T invN = (T)(1.0 / ((double)t.n[0] * t.n[1] * t.n[2]));
     for (int i0 = 0; i0 < t.nx; i0 += kMaxNx) {
@@ -782,9 +782,9 @@ gw_status run_mtxel(gw_ctx* c, const MmTables& t, int nv, int ngv, const cpx<T>*
 #define GW_MM_PX(N)                                                                              \
   if (nx == N) {                                                                                 \
     if (!c->capturing) GW_HIP(c, allow(c, k_mm_pair_x<T, N>, xl));                               \
-    hipLaunchKernelGGL((k_mm_pair_x<T, N>), gr, bl, xl, c->stream, t2, t.n[0], t.nq4, t.kx, i0,   \
-                       t.nx, reinterpret_cast<const T*>(t.dev + t.o_xc),                         \
-                       reinterpret_cast<const int*>(t.dev + t.o_tab), invN, nv, c0, nc, t.neps,  \
+    hipLaunchKernelGGL((k_mm_pair_x<T, N>), gr, bl, xl, c->stream, t2, t.n[0], t.eps->nq4, t.kx, i0,   \
+                       t.nx, reinterpret_cast<const T*>(t.grid->p + t.o_xc),                         \
+                       reinterpret_cast<const int*>(t.eps->dev.p + t.eps->o_tab), invN, nv, c0, nc, t.neps,  \
                        tasks, M);                                                                \
   }
       GW_MM_PX(1) GW_MM_PX(2) GW_MM_PX(3) GW_MM_PX(4)
@@ -797,20 +797,52 @@ gw_status run_mtxel(gw_ctx* c, const MmTables& t, int nv, int ngv, const cpx<T>*
 
 }  // namespace
 
-MmTables::~MmTables() {
-  if (dev) (void)hipFree(dev);
+DevBuf::~DevBuf() {
+  if (p) (void)hipFree(p);
 }
 
-gw_status mm_tables(gw_ctx* c, const SphereMap* sv, const SphereMap* sc, const SphereMap* se,
-                    const int32_t* geps, int nspinor, bool dbl, std::shared_ptr<MmTables>* out) {
-  out->reset();
-  // sphere maps are the context's, one per set of G vectors, for its lifetime
-  const auto key = std::make_tuple(sv, sc, se, nspinor, dbl);
-  auto it = c->mm.find(key);
-  if (it != c->mm.end()) {
-    *out = it->second;
-    return GW_OK;
+// Host memory to a new allocation, on a stream of its own: neither waits for the
+// context's stream nor ends a capture of it.
+static gw_status upload(gw_ctx* c, const std::vector<char>& h, DevBuf* out) {
+  struct Relaxed {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  } relaxed;
+  if (!c->up) GW_HIP(c, hipStreamCreateWithFlags(&c->up, hipStreamNonBlocking));
+  void* d = nullptr;
+  GW_HIP(c, hipMalloc(&d, h.size()));
+  out->p = static_cast<char*>(d);
+  out->bytes = h.size();
+  GW_HIP(c, hipMemcpyAsync(d, h.data(), h.size(), hipMemcpyHostToDevice, c->up));
+  GW_HIP(c, hipStreamSynchronize(c->up));
+  return GW_OK;
+}
+
+static bool being_captured(gw_ctx* c) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  return c->stream && hipStreamIsCapturing(c->stream, &cap) == hipSuccess &&
+         cap != hipStreamCaptureStatusNone;
+}
+
+// Bounded caches: their entries are given back when they pass kCacheBytes together
+// (freeing waits for the device), but not during a capture.  What a plan or a captured
+// graph reads is held elsewhere too.
+constexpr size_t kCacheBytes = 256u << 20;
+template <typename M>
+static void bound_cache(M* cache, size_t* bytes, size_t more, bool capture) {
+  if (*bytes + more > kCacheBytes && !capture) {
+    cache->clear();
+    *bytes = 0;
   }
+  *bytes += more;
+}
+
+// Axis order and coefficient tables for the spheres' largest |g|; null when no kernel is
+// built for them.
+static gw_status grid_tables(gw_ctx* c, const SphereMap* sv, const SphereMap* sc,
+                             const SphereMap* se, int nspinor, bool dbl,
+                             std::shared_ptr<MmTables>* out) {
   // the axis order with the least matrix-core time and intermediate traffic per pair
   // among those the kernels are built for
   auto t = std::make_shared<MmTables>();
@@ -862,74 +894,114 @@ gw_status mm_tables(gw_ctx* c, const SphereMap* sv, const SphereMap* sc, const S
       }
     }
   }
-  if (best < INFINITY) {
-    t->cube_v = sv->d_cube;
-    t->cube_c = sc->d_cube;
-    t->neps = se->n;
-    t->plane = (size_t)nspinor * t->rt * t->ks * 64;
-    const int G0 = t->ge[0], G1 = t->ge[1], G2 = t->ge[2];
-    Blob b;
-    t->o_zc = b.begin();
-    for (int ct = 0; ct < t->ncz; ++ct)
-      for (int s = 0; s < t->ks; ++s)
-        for (int l = 0; l < 64; ++l) {
-          const int z = 4 * s + (l >> 4), g = ct * 8 + ((l & 15) >> 1);
-          b.put(z < t->n[2] && g <= G2 ? trig(l & 1, (long long)g * z, t->n[2]) : 0.0, dbl);
-        }
-    t->o_yc = b.begin();
-    put_out_rows(b, dbl, t->nry, t->rt * 4, G1, t->n[1]);
-    t->o_xc = b.begin();
-    put_out_rows(b, dbl, t->nx, t->kx, G0, t->n[0]);
-    put_band(b, *t, t->gv, &t->bv);
-    put_band(b, *t, t->gc, &t->bc);
-    // quads (|g1|, |g2|) with a point of the eps sphere, and its compact index map
-    const int e1 = 2 * G1 + 1, e2 = 2 * G2 + 1;
-    std::vector<int> map((size_t)(2 * G0 + 1) * e1 * e2, -1), qpos((size_t)(G1 + 1) * (G2 + 1), -1);
-    std::vector<std::pair<int, int>> quads;
-    for (int i = 0; i < se->n; ++i) {
-      const int g0 = geps[3 * i + t->perm[0]], g1 = geps[3 * i + t->perm[1]],
-                g2 = geps[3 * i + t->perm[2]];
-      map[((size_t)(g0 + G0) * e1 + g1 + G1) * e2 + g2 + G2] = i;
-      qpos[(size_t)std::abs(g1) * (G2 + 1) + std::abs(g2)] = 0;
-    }
-    for (int g1 = 0; g1 <= G1; ++g1)
-      for (int g2 = 0; g2 <= G2; ++g2) {
-        int& q = qpos[(size_t)g1 * (G2 + 1) + g2];
-        if (q < 0) continue;
-        q = (int)quads.size();
-        quads.push_back({g1, g2});
+  if (best == INFINITY) return GW_OK;
+  t->plane = (size_t)nspinor * t->rt * t->ks * 64;
+  const int G0 = t->ge[0], G1 = t->ge[1], G2 = t->ge[2];
+  Blob b;
+  t->o_zc = b.begin();
+  for (int ct = 0; ct < t->ncz; ++ct)
+    for (int s = 0; s < t->ks; ++s)
+      for (int l = 0; l < 64; ++l) {
+        const int z = 4 * s + (l >> 4), g = ct * 8 + ((l & 15) >> 1);
+        b.put(z < t->n[2] && g <= G2 ? trig(l & 1, (long long)g * z, t->n[2]) : 0.0, dbl);
       }
-    t->nq = (int)quads.size();
-    t->nq4 = (t->nq + 3) / 4 * 4;
-    t->o_qpos = b.begin();
-    for (int q : qpos) b.put_int(q);
-    t->o_tab = b.begin();
-    for (int tile = 0; tile < t->nq4 / 4; ++tile)
-      for (int g = 0; g < 8 * t->nx; ++g)
-        for (int sg = 0; sg < 2; ++sg)
-          for (int l = 0; l < 16; ++l) {
-            const int q = tile * 4 + l / 4, s1 = (l >> 1) & 1, s2 = l & 1;
-            int idx = -1;
-            if (q < t->nq && g <= G0) {
-              const int g1 = quads[q].first, g2 = quads[q].second;
-              if (!(sg && !g) && !(s1 && !g1) && !(s2 && !g2))
-                idx = map[((size_t)((sg ? -g : g) + G0) * e1 + (s1 ? -g1 : g1) + G1) * e2 +
-                          (s2 ? -g2 : g2) + G2];
-            }
-            b.put_int(idx);
-          }
-    void* d = nullptr;
-    const size_t bytes = b.begin();
-    GW_HIP(c, hipMalloc(&d, bytes));
-    t->dev = static_cast<char*>(d);
-    GW_HIP(c, hipMemcpy(d, b.h.data(), bytes, hipMemcpyHostToDevice));
-  } else {
-    t.reset();
+  t->o_yc = b.begin();
+  put_out_rows(b, dbl, t->nry, t->rt * 4, G1, t->n[1]);
+  t->o_xc = b.begin();
+  put_out_rows(b, dbl, t->nx, t->kx, G0, t->n[0]);
+  put_band(b, *t, t->gv, &t->bv);
+  put_band(b, *t, t->gc, &t->bc);
+  t->grid = std::make_shared<DevBuf>();
+  gw_status st = upload(c, b.h, t->grid.get());
+  if (st == GW_OK) *out = t;
+  return st;
+}
+
+static gw_status eps_tables(gw_ctx* c, const MmTables& t, const SphereMap* se,
+                            const int32_t* geps, std::shared_ptr<MmEps>* out) {
+  const int G0 = t.ge[0], G1 = t.ge[1], G2 = t.ge[2];
+  auto x = std::make_shared<MmEps>();
+  Blob b;
+  // quads (|g1|, |g2|) with a point of the eps sphere, and its compact index map
+  const int e1 = 2 * G1 + 1, e2 = 2 * G2 + 1;
+  std::vector<int> map((size_t)(2 * G0 + 1) * e1 * e2, -1), qpos((size_t)(G1 + 1) * (G2 + 1), -1);
+  std::vector<std::pair<int, int>> quads;
+  for (int i = 0; i < se->n; ++i) {
+    const int g0 = geps[3 * i + t.perm[0]], g1 = geps[3 * i + t.perm[1]],
+              g2 = geps[3 * i + t.perm[2]];
+    map[((size_t)(g0 + G0) * e1 + g1 + G1) * e2 + g2 + G2] = i;
+    qpos[(size_t)std::abs(g1) * (G2 + 1) + std::abs(g2)] = 0;
   }
-  // bounded: the tables of earlier spheres are given back (freeing waits for the
-  // device; a plan keeps the ones its graph reads)
-  if (c->mm.size() >= 256) c->mm.clear();
-  c->mm.emplace(key, t);
+  for (int g1 = 0; g1 <= G1; ++g1)
+    for (int g2 = 0; g2 <= G2; ++g2) {
+      int& q = qpos[(size_t)g1 * (G2 + 1) + g2];
+      if (q < 0) continue;
+      q = (int)quads.size();
+      quads.push_back({g1, g2});
+    }
+  x->nq = (int)quads.size();
+  x->nq4 = (x->nq + 3) / 4 * 4;
+  x->o_qpos = b.begin();
+  for (int q : qpos) b.put_int(q);
+  x->o_tab = b.begin();
+  for (int tile = 0; tile < x->nq4 / 4; ++tile)
+    for (int g = 0; g < 8 * t.nx; ++g)
+      for (int sg = 0; sg < 2; ++sg)
+        for (int l = 0; l < 16; ++l) {
+          const int q = tile * 4 + l / 4, s1 = (l >> 1) & 1, s2 = l & 1;
+          int idx = -1;
+          if (q < x->nq && g <= G0) {
+            const int g1 = quads[q].first, g2 = quads[q].second;
+            if (!(sg && !g) && !(s1 && !g1) && !(s2 && !g2))
+              idx = map[((size_t)((sg ? -g : g) + G0) * e1 + (s1 ? -g1 : g1) + G1) * e2 +
+                        (s2 ? -g2 : g2) + G2];
+          }
+          b.put_int(idx);
+        }
+  gw_status st = upload(c, b.h, &x->dev);
+  if (st == GW_OK) *out = x;
+  return st;
+}
+
+gw_status mm_tables(gw_ctx* c, const SphereMap* sv, const SphereMap* sc, const SphereMap* se,
+                    const int32_t* geps, int nspinor, bool dbl, std::shared_ptr<MmTables>* out) {
+  out->reset();
+  const bool capture = being_captured(c);
+  MmGridKey key{};
+  for (int a = 0; a < 3; ++a) {
+    key[a] = sv->gmax[a];
+    key[3 + a] = sc->gmax[a];
+    key[6 + a] = se->gmax[a];
+  }
+  key[9] = 2 * nspinor + dbl;
+  auto it = c->mm_grid.find(key);
+  if (it == c->mm_grid.end()) {
+    std::shared_ptr<MmTables> t;
+    gw_status st = grid_tables(c, sv, sc, se, nspinor, dbl, &t);
+    if (st != GW_OK) return st;
+    bound_cache(&c->mm_grid, &c->mm_grid_bytes, t ? t->grid->bytes : 256, capture);
+    it = c->mm_grid.emplace(key, t).first;
+  }
+  if (!it->second) return GW_OK;
+  auto t = std::make_shared<MmTables>(*it->second);
+  t->cube_v = sv->d_cube;
+  t->cube_c = sc->d_cube;
+  t->neps = se->n;
+  // sphere maps are the context's, one per set of G vectors, for its lifetime
+  const auto ek = std::make_pair(se, 9 * t->perm[0] + 3 * t->perm[1] + t->perm[2]);
+  auto ie = c->mm_eps.find(ek);
+  if (ie == c->mm_eps.end()) {
+    std::shared_ptr<MmEps> e;
+    gw_status st = eps_tables(c, *t, se, geps, &e);
+    if (st != GW_OK) return st;
+    bound_cache(&c->mm_eps, &c->mm_eps_bytes, e->dev.bytes, capture);
+    ie = c->mm_eps.emplace(ek, e).first;
+  }
+  t->eps = ie->second;
+  if (capture) {
+    c->mm_held.insert(t->grid);
+    c->mm_held.insert(t->eps);
+  }
   *out = t;
   return GW_OK;
 }

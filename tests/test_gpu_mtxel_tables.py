@@ -1,0 +1,80 @@
+"""GPU matrix elements of spheres that are known one by one but not together: under
+capture, and over more sets than any cache of whole sets would hold."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _sphere(rng, gmax, n):
+    g = np.array([(x, y, z) for x in range(-gmax, gmax + 1) for y in range(-gmax, gmax + 1)
+                  for z in range(-gmax, gmax + 1) if x * x + y * y + z * z <= gmax * gmax + 1],
+                 dtype=np.int32)
+    ends = np.array([s * gmax * np.eye(3, dtype=np.int32)[a] for a in range(3) for s in (-1, 1)],
+                    dtype=np.int32)
+    return np.unique(np.concatenate([ends, g[rng.permutation(len(g))[:n]]]), axis=0)
+
+
+def _bands(rng, nb, g, dtype):
+    c = rng.normal(size=(nb, 2, len(g))) + 1j * rng.normal(size=(nb, 2, len(g)))
+    return torch.from_numpy(c.astype(dtype)).cuda()
+
+
+@pytest.mark.parametrize("dtype", [np.complex128, np.complex64])
+@pytest.mark.parametrize("gv,gc,ge", [(3, 3, 2), (3, 4, 2), (4, 3, 1)])
+def test_new_set_of_known_spheres_under_capture(gv, gc, ge, dtype):
+    import paper_2206_00808_amd as P
+    rng = np.random.default_rng(gv + 10 * gc + 100 * ge)
+    box = (16, 15, 18)
+    a, b = _sphere(rng, gv, 40), _sphere(rng, gc, 45)
+    e, e2 = _sphere(rng, ge, 15), _sphere(rng, ge, 12)
+    nv, nc = 3, 5
+    tdt = torch.complex128 if dtype == np.complex128 else torch.complex64
+    av, bc = _bands(rng, nv, a, dtype), _bands(rng, nc, b, dtype)
+    ctx = P.Context(0)
+    # every sphere is known, and the workspace is large enough, but (a, b, e) is new
+    for g, eps in ((a, e), (b, e2)):
+        w = _bands(rng, 16, g, dtype)
+        P.gw_mtxel_spinor(ctx, box, 2, g, w, g, w, eps,
+                          torch.empty((16, 16, len(eps)), dtype=tdt, device="cuda"))
+    out = torch.zeros((nv, nc, len(e)), dtype=tdt, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        P.gw_mtxel_spinor(ctx, box, 2, a, av, b, bc, e, out)
+    want = torch.zeros_like(out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        P.gw_mtxel_spinor(ctx, box, 2, a, av, b, bc, e, want)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and bool(want.abs().max() > 0)
+    ref = oracle.mtxel_convolution(av.cpu().numpy().astype(np.complex128), a,
+                                   bc.cpu().numpy().astype(np.complex128), b, e)
+    assert oracle.rel_f(want.cpu().numpy(), ref) < (1e-13 if dtype == np.complex128 else 1e-5)
+    ctx.close()
+
+
+def test_many_sets_in_turn():
+    import paper_2206_00808_amd as P
+    rng = np.random.default_rng(5)
+    box = (12, 12, 12)
+    sph = [_sphere(rng, 3, 20 + i) for i in range(18)]
+    eps = [_sphere(rng, 2, 8 + i) for i in range(3)]
+    bands = [_bands(rng, 2, g, np.complex128) for g in sph]
+    ctx = P.Context(0)
+    for i in range(18):
+        for j in range(18):  # 324 sets of three spheres, twice
+            e = eps[(i + j) % 3]
+            out = torch.empty((2, 2, len(e)), dtype=torch.complex128, device="cuda")
+            for _ in range(2):
+                P.gw_mtxel_spinor(ctx, box, 2, sph[i], bands[i], sph[j], bands[j], e, out)
+            if (i * 18 + j) % 29 == 0:
+                ref = oracle.mtxel_convolution(bands[i].cpu().numpy(), sph[i],
+                                               bands[j].cpu().numpy(), sph[j], e)
+                assert oracle.rel_f(out.cpu().numpy(), ref) < 1e-13
+    ctx.close()
