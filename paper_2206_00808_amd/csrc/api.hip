@@ -110,6 +110,25 @@ gw_status stage_h2d(gw_ctx* c, void* dst, const void* src, size_t bytes) {
   return GW_OK;
 }
 
+gw_status upload(gw_ctx* c, const void* src, size_t bytes, char** out) {
+  struct Relaxed {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  } relaxed;
+  if (!c->up) GW_HIP(c, hipStreamCreateWithFlags(&c->up, hipStreamNonBlocking));
+  void* d = nullptr;
+  GW_HIP(c, hipMalloc(&d, bytes));
+  hipError_t e = hipMemcpyAsync(d, src, bytes, hipMemcpyHostToDevice, c->up);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->up);
+  if (e != hipSuccess) {
+    (void)hipFree(d);
+    return hip_fail(c, e, "upload of a table");
+  }
+  *out = static_cast<char*>(d);
+  return GW_OK;
+}
+
 static uint64_t fnv1a(const void* data, size_t n, uint64_t h = 1469598103934665603ull) {
   const unsigned char* p = static_cast<const unsigned char*>(data);
   for (size_t i = 0; i < n; ++i) { h ^= p[i]; h *= 1099511628211ull; }

@@ -112,7 +112,7 @@ struct gw_ctx {
   std::map<std::pair<const gw::SphereMap*, int>, std::shared_ptr<gw::MmEps>> mm_eps;
   size_t mm_grid_bytes = 0, mm_eps_bytes = 0;
   std::set<std::shared_ptr<void>> mm_held;        // those that captured graphs read
-  hipStream_t up = nullptr;                       // uploads of those tables
+  hipStream_t up = nullptr;                       // uploads of tables
   std::map<std::pair<int, int>, void*> twiddles;  // (n, is_double) -> device table
   std::map<long long, void*> tile_orders;         // (tiles, block shape) -> chi0 tile order (int2)
   int* d_flag = nullptr;                          // device status flags
@@ -154,6 +154,9 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 gw_status stage_h2d(gw_ctx* c, void* dst, const void* src, size_t bytes);
 
 // Device tables.
+// Host memory to a new allocation, on a stream of its own: neither waits for the
+// context's stream nor ends a capture of it.
+gw_status upload(gw_ctx* c, const void* src, size_t bytes, char** out);
 gw_status sphere_map(gw_ctx* c, const int32_t* g, int n, const int box[3], SphereMap** out);
 gw_status twiddle_table(gw_ctx* c, int n, bool dbl, const void** out);
 

@@ -61,16 +61,12 @@ gw_status twiddle_table(gw_ctx* c, int n, bool dbl, const void** out) {
   if (it != c->twiddles.end()) { *out = it->second; return GW_OK; }
   std::vector<double> h(2 * (size_t)n);
   for (int m = 0; m < n; ++m) unit_root(m, n, &h[2 * m], &h[2 * m + 1]);
-  void* d = nullptr;
-  size_t bytes = (size_t)n * (dbl ? 16 : 8);
-  GW_HIP(c, hipMalloc(&d, bytes));
-  if (dbl) {
-    GW_HIP(c, hipMemcpy(d, h.data(), bytes, hipMemcpyHostToDevice));
-  } else {
-    std::vector<float> f(2 * (size_t)n);
-    for (size_t i = 0; i < f.size(); ++i) f[i] = (float)h[i];
-    GW_HIP(c, hipMemcpy(d, f.data(), bytes, hipMemcpyHostToDevice));
-  }
+  std::vector<float> f(dbl ? 0 : h.size());
+  for (size_t i = 0; i < f.size(); ++i) f[i] = (float)h[i];
+  const void* src = dbl ? static_cast<const void*>(h.data()) : f.data();
+  char* d = nullptr;
+  gw_status st = upload(c, src, (size_t)n * (dbl ? 16 : 8), &d);
+  if (st != GW_OK) return st;
   c->twiddles[key] = d;
   *out = d;
   return GW_OK;

@@ -801,24 +801,6 @@ DevBuf::~DevBuf() {
   if (p) (void)hipFree(p);
 }
 
-// Host memory to a new allocation, on a stream of its own: neither waits for the
-// context's stream nor ends a capture of it.
-static gw_status upload(gw_ctx* c, const std::vector<char>& h, DevBuf* out) {
-  struct Relaxed {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-    ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-  } relaxed;
-  if (!c->up) GW_HIP(c, hipStreamCreateWithFlags(&c->up, hipStreamNonBlocking));
-  void* d = nullptr;
-  GW_HIP(c, hipMalloc(&d, h.size()));
-  out->p = static_cast<char*>(d);
-  out->bytes = h.size();
-  GW_HIP(c, hipMemcpyAsync(d, h.data(), h.size(), hipMemcpyHostToDevice, c->up));
-  GW_HIP(c, hipStreamSynchronize(c->up));
-  return GW_OK;
-}
-
 static bool being_captured(gw_ctx* c) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   return c->stream && hipStreamIsCapturing(c->stream, &cap) == hipSuccess &&
@@ -912,7 +894,8 @@ static gw_status grid_tables(gw_ctx* c, const SphereMap* sv, const SphereMap* sc
   put_band(b, *t, t->gv, &t->bv);
   put_band(b, *t, t->gc, &t->bc);
   t->grid = std::make_shared<DevBuf>();
-  gw_status st = upload(c, b.h, t->grid.get());
+  gw_status st = upload(c, b.h.data(), b.h.size(), &t->grid->p);
+  t->grid->bytes = b.h.size();
   if (st == GW_OK) *out = t;
   return st;
 }
@@ -958,7 +941,8 @@ static gw_status eps_tables(gw_ctx* c, const MmTables& t, const SphereMap* se,
           }
           b.put_int(idx);
         }
-  gw_status st = upload(c, b.h, &x->dev);
+  gw_status st = upload(c, b.h.data(), b.h.size(), &x->dev.p);
+  x->dev.bytes = b.h.size();
   if (st == GW_OK) *out = x;
   return st;
 }

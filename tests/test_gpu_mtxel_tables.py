@@ -59,6 +59,35 @@ def test_new_set_of_known_spheres_under_capture(gv, gc, ge, dtype):
     ctx.close()
 
 
+# on two axes beyond the dense kernels: the general transforms, on a grid of new lengths
+def test_new_set_of_wide_spheres_under_capture():
+    import paper_2206_00808_amd as P
+    rng = np.random.default_rng(9)
+    box = (80, 81, 9)
+    flat = [np.concatenate([rng.integers(-m, m + 1, (30, 2)), [[m, m], [-m, -m], [0, 0]]])
+            for m in (24, 28, 16)]
+    a, b, e = (np.unique(np.c_[g, np.zeros(len(g))], axis=0).astype(np.int32) for g in flat)
+    av, bc = _bands(rng, 2, a, np.complex128), _bands(rng, 3, b, np.complex128)
+    ctx = P.Context(0)
+    for g, w in ((a, av), (b, bc)):
+        big = torch.cat([w] * 4)
+        P.gw_mtxel_spinor(ctx, box, 2, g, big, g, big, e,
+                          torch.empty((len(big), len(big), len(e)), dtype=torch.complex128,
+                                      device="cuda"))
+    out = torch.zeros((2, 3, len(e)), dtype=torch.complex128, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        P.gw_mtxel_spinor(ctx, box, 2, a, av, b, bc, e, out)
+    ref = oracle.mtxel_convolution(av.cpu().numpy(), a, bc.cpu().numpy(), b, e)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert oracle.rel_f(out.cpu().numpy(), ref) < 1e-13
+    ctx.close()
+
+
 def test_many_sets_in_turn():
     import paper_2206_00808_amd as P
     rng = np.random.default_rng(5)
