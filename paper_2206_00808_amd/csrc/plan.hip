@@ -123,7 +123,8 @@ struct gw_plan {
   std::vector<gw_plan_q> q;
   bool shared_c = false;
   int nc_shared = 0;
-  bool mm = false;       // every q on the dense-transform path
+  bool general = false;  // some q is too wide for the dense transforms
+  int grid[3] = {1, 1, 1};  // of the general transforms: one for every such q
   // device memory (one allocation)
   char* base = nullptr;
   size_t bytes = 0;
@@ -250,25 +251,25 @@ static gw_status enqueue_front(gw_plan* p) {
   const bool dbl = p->dtype == GW_C128;
   const int ns = p->nspinor;
   auto conduction = [&](int nbs, int ng, const void* cc, const SphereMap* sc) {
-    return dbl ? band_to_grid<double>(c, p->box, nbs, ng, cc, sc, p->uc, p->bscr, p->bscr_bytes)
-               : band_to_grid<float>(c, p->box, nbs, ng, cc, sc, p->uc, p->bscr, p->bscr_bytes);
+    return dbl ? band_to_grid<double>(c, p->grid, nbs, ng, cc, sc, p->uc, p->bscr, p->bscr_bytes)
+               : band_to_grid<float>(c, p->grid, nbs, ng, cc, sc, p->uc, p->bscr, p->bscr_bytes);
   };
-  if (p->shared_c && !p->mm) {
+  if (p->shared_c && p->general) {
     const auto& q0 = p->q[0];
     if ((st = conduction(p->nc_shared * ns, q0.d.ngc, q0.d.cc, q0.sc)) != GW_OK) return st;
   }
   for (auto& q : p->q) {
     const int nv = q.d.nv, nc = q.d.nc;
-    if (p->mm) {
+    if (q.mm) {
       st = mm_mtxel(c, *q.mm, nv, q.d.ngv, q.d.cv, nc, q.d.ngc, q.d.cc, q.M, p->pscr);
       if (st != GW_OK) return st;
     } else {
       if (!p->shared_c) {
         if ((st = conduction(nc * ns, q.d.ngc, q.d.cc, q.sc)) != GW_OK) return st;
       }
-      st = dbl ? band_to_grid<double>(c, p->box, nv * ns, q.d.ngv, q.d.cv, q.sv, p->uv, p->bscr,
+      st = dbl ? band_to_grid<double>(c, p->grid, nv * ns, q.d.ngv, q.d.cv, q.sv, p->uv, p->bscr,
                                       p->bscr_bytes)
-               : band_to_grid<float>(c, p->box, nv * ns, q.d.ngv, q.d.cv, q.sv, p->uv, p->bscr,
+               : band_to_grid<float>(c, p->grid, nv * ns, q.d.ngv, q.d.cv, q.sv, p->uv, p->bscr,
                                      p->bscr_bytes);
       if (st != GW_OK) return st;
       const int vt = std::min(nv, p->pair_chunk);
@@ -276,9 +277,9 @@ static gw_status enqueue_front(gw_plan* p) {
       for (int v0 = 0; v0 < nv; v0 += vt)
         for (int c0 = 0; c0 < nc; c0 += ct) {
           const int nvt = std::min(vt, nv - v0), nct = std::min(ct, nc - c0);
-          st = dbl ? pair_to_eps<double>(c, p->box, ns, p->uv, p->uc, v0, nvt, c0, nct, nc, q.se,
+          st = dbl ? pair_to_eps<double>(c, p->grid, ns, p->uv, p->uc, v0, nvt, c0, nct, nc, q.se,
                                          q.M, p->pscr)
-                   : pair_to_eps<float>(c, p->box, ns, p->uv, p->uc, v0, nvt, c0, nct, nc, q.se,
+                   : pair_to_eps<float>(c, p->grid, ns, p->uv, p->uc, v0, nvt, c0, nct, nc, q.se,
                                         q.M, p->pscr);
           if (st != GW_OK) return st;
         }
@@ -471,28 +472,42 @@ gw_status gw_plan_compile(gw_plan* p) {
   if (p->compiled) return GW_OK;
   (void)hipSetDevice(c->device);
   const size_t elem = p->dtype == GW_C128 ? 16 : 8;
-  const size_t nbox = (size_t)p->box[0] * p->box[1] * p->box[2];
   const int ns = p->nspinor;
+  // The transforms of each q: dense ones where they are built, in a workspace of their
+  // own; the others share the fields and scratch of the general ones, on the shortest
+  // grid that holds every such q.
+  size_t pscr_bytes = 0;
   int nv_max = 0, nc_max = 0;
-  size_t band_per = 0, pair_per = 0;
   for (auto& q : p->q) {
+    if (q.mm) {
+      pscr_bytes = std::max(pscr_bytes, mm_workspace(*q.mm, q.d.nv, q.d.nc));
+      continue;
+    }
+    int grid[3];
+    fft_grid(p->box, q.sv, q.sc, q.se, grid);
+    for (int a = 0; a < 3; ++a) p->grid[a] = std::max(p->grid[a], grid[a]);
+    p->general = true;
     nv_max = std::max(nv_max, q.d.nv);
     nc_max = std::max(nc_max, q.d.nc);
-    band_per = std::max({band_per, band_scratch_bytes(p->box, q.sv, 1, elem),
-                         band_scratch_bytes(p->box, q.sc, 1, elem)});
-    pair_per = std::max(pair_per, pair_scratch_bytes(p->box, q.se, 1, elem));
   }
-  const int nbs_max = std::max(nv_max, p->shared_c ? p->nc_shared : nc_max) * ns;
-  const int band_chunk = (int)std::max<size_t>(1, std::min<size_t>(nbs_max, (512ull << 20) / band_per));
-  p->bscr_bytes = band_per * band_chunk;
-  p->pair_chunk = (int)std::max<size_t>(1, std::min<size_t>(65535, (1ull << 30) / pair_per));
-  size_t pscr_bytes = pair_per * p->pair_chunk;
-  p->mm = true;
-  for (auto& q : p->q) p->mm = p->mm && q.mm;
-  if (p->mm) {
-    pscr_bytes = 0;
-    for (auto& q : p->q) pscr_bytes = std::max(pscr_bytes, mm_workspace(*q.mm, q.d.nv, q.d.nc));
-    p->bscr_bytes = 0;
+  size_t uc_bytes = 0, uv_bytes = 0;
+  if (p->general) {
+    const size_t ngrid = (size_t)p->grid[0] * p->grid[1] * p->grid[2];
+    size_t band_per = 0, pair_per = 0;
+    for (auto& q : p->q) {
+      if (q.mm) continue;
+      band_per = std::max({band_per, band_scratch_bytes(p->grid, q.sv, 1, elem),
+                           band_scratch_bytes(p->grid, q.sc, 1, elem)});
+      pair_per = std::max(pair_per, pair_scratch_bytes(p->grid, q.se, 1, elem));
+    }
+    const int nc = p->shared_c ? p->nc_shared : nc_max;
+    const int band_chunk = (int)std::max<size_t>(
+        1, std::min<size_t>(std::max(nv_max, nc) * ns, (512ull << 20) / band_per));
+    p->bscr_bytes = band_per * band_chunk;
+    p->pair_chunk = (int)std::max<size_t>(1, std::min<size_t>(65535, (1ull << 30) / pair_per));
+    pscr_bytes = std::max(pscr_bytes, pair_per * p->pair_chunk);
+    uc_bytes = (size_t)nc * ns * ngrid * elem;
+    uv_bytes = (size_t)nv_max * ns * ngrid * elem;
   }
   // matrices
   p->nmat = (int)p->q.size() * p->nfreq;
@@ -511,9 +526,6 @@ gw_status gw_plan_compile(gw_plan* p) {
   p->nitems = (int)items;
   // one allocation
   std::vector<std::pair<void**, size_t>> parts;
-  size_t uc_bytes = (size_t)(p->shared_c ? p->nc_shared : nc_max) * ns * nbox * elem;
-  size_t uv_bytes = (size_t)nv_max * ns * nbox * elem;
-  if (p->mm) uc_bytes = uv_bytes = 0;  // the fields are part of the pair scratch
   parts.push_back({&p->uc, uc_bytes});
   parts.push_back({&p->uv, uv_bytes});
   parts.push_back({&p->bscr, p->bscr_bytes});
