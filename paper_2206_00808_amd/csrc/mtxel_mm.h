@@ -37,6 +37,7 @@ struct MmTables {
   int rt = 1, ks = 1, jt = 1;           // row tiles of 16, K steps of 4, groups of 16 entries
   int ncz = 1, nry = 1, nx = 1;         // tiles of 8 kept |g| per axis 2, 1, 0
   int kx = 1;                           // K steps of the last transform
+  bool rows = false;                    // pair planes by rows
   size_t plane = 0;                     // elements of a plane of one band, all spinor components
   size_t o_zc = 0, o_yc = 0, o_xc = 0;
   struct Band {

@@ -159,87 +159,88 @@ __global__ void __launch_bounds__(256) k_mm_band_x(BandSet<T> bv, BandSet<T> bc,
 }
 
 // ---------------------------------------------------------------- bands, axes 1 and 2
-// One wavefront per plane of one band and spinor component.  The plane's t1, folded
-// over +-g1, goes to LDS by tiles of eight +-g2 pairs (rows g2, +g2 and -g2 of a pair
-// in one lane); then for every tile of 16 y and of g2,
+// RT wavefronts per plane of one band and spinor component, one for each tile of 16 rows.
+// The plane's t1, folded over +-g1, goes to LDS by tiles of eight +-g2 pairs (rows g2, +g2
+// and -g2 of a pair in one lane), each wavefront a part; then for every tile of g2,
 // Y(g2, y) = sum_g1 t1 exp(+2 pi i g1 y / n1), folded over +-g2 in place into the B
 // operand of u(z, y) += sum_g2 [cos | sin](z, g2) Y, whose result is in the fragment
-// order of the fields.
+// order of the fields.  Bound: latency of its loads and of the dependent products.
 template <typename T, int JT>
-__global__ void __launch_bounds__(256) k_mm_band_plane(BandSet<T> bv, BandSet<T> bc, int kmax,
+__global__ void __launch_bounds__(256, 3) k_mm_band_plane(BandSet<T> bv, BandSet<T> bc, int kmax,
                                                        int n0, int ns, int rt, int ks,
                                                        size_t plane) {
   using D = MmType<double>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, q = lane >> 4;
-  int p = blockIdx.x * (blockDim.x >> 6) + wave;  // (band, spin, x)
+  const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = wave % rt;
+  const int slot = wave / rt;                              // plane of the workgroup
+  int p = blockIdx.x * ((blockDim.x >> 6) / rt) + slot;    // (band, spin, x)
   const bool val = p < bv.nbs * n0;
   const BandSet<T>& B = val ? bv : bc;
   if (!val) p -= bv.nbs * n0;
-  if (p >= B.nbs * n0) return;
-  cpx<double>* S = reinterpret_cast<cpx<double>*>(smem_raw) + (size_t)wave * kmax * 64 + lane;
-  const int G1 = B.G1, G2 = B.G2, ky = B.ky;
+  const bool mine = p < B.nbs * n0;
+  if (!mine) p = 0;
+  cpx<double>* S = reinterpret_cast<cpx<double>*>(smem_raw) + (size_t)slot * kmax * 64 + lane;
+  const int G1 = B.G1, G2 = B.G2, ky = B.ky, lr = l16 >> 2, e2 = 2 * G2 + 1;
   const int bs = p / n0, x = p - bs * n0, band = bs / ns, sp = bs - band * ns;
-  const int e2 = 2 * G2 + 1;
   const cpx<T>* src = B.t1 + (size_t)p * (2 * G1 + 1) * e2;
-  cpx<T>* dst = B.u + ((size_t)band * n0 + x) * plane + (size_t)sp * rt * ks * 64 + lane;
-  const int lr = l16 >> 2;
-  for (int tz = 0; tz < B.ntz; ++tz) {
-    // this lane's operand row: g2 = +-ga
-    const int ga = 8 * tz + (l16 & 3) + 4 * (lr >> 1), g2 = (lr & 1) ? -ga : ga;
-    const bool live = ga <= G2 && !((lr & 1) && ga == 0);
-    const cpx<T>* row = src + (live ? G2 + g2 : 0);
-#pragma unroll 4
-    for (int s = 0; s < ky; ++s) {
-      bool sine;
-      const int k = 4 * s + q, g = kappa_g(k, G1, &sine);
-      const bool in = live && k <= 2 * G1;
-      const int gi = in ? g : 0;
-      const cpx<double> a = widen(row[(G1 + gi) * e2]), b = widen(row[(G1 - gi) * e2]),
-                        z = mk(0.0, 0.0);
-      S[(tz * ky + s) * 64] = fold(in ? a : z, in && g ? b : z, sine);
-    }
-  }
-  __builtin_amdgcn_wave_barrier();  // each lane reads its own entries only
-  for (int t = 0; t < rt; ++t) {
-    D4 ur[JT], ui[JT];
-#pragma unroll
-    for (int j = 0; j < JT; ++j) ur[j] = ui[j] = (D4){0, 0, 0, 0};
+  if (mine)
     for (int tz = 0; tz < B.ntz; ++tz) {
-      D4 yr = {0, 0, 0, 0}, yi = yr;
-      const double* w = B.by + (size_t)t * ky * 64 + lane;
-#pragma unroll 1
-      for (int s = 0; s < ky; s += 2) {
-        const bool two = s + 1 < ky;
-        const int s1 = two ? s + 1 : s;
-        const cpx<double> d0 = S[(tz * ky + s) * 64], d1 = S[(tz * ky + s1) * 64];
-        const double w0 = w[s * 64], w1 = w[s1 * 64];
-        yr += mfma2(d0.x, w0, d1.x, w1, two);
-        yi += mfma2(d0.y, w0, d1.y, w1, two);
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (8 * tz + 4 * h > G2) break;
-        const double pr = yr[2 * h] + yr[2 * h + 1], pi = yi[2 * h] + yi[2 * h + 1];
-        const double mr = yr[2 * h] - yr[2 * h + 1], mi = yi[2 * h] - yi[2 * h + 1];
-        const D4 none = {0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < JT; ++j) {
-          const double* wz = B.bz + ((size_t)(j * B.ntz + tz) * 4 + 2 * h) * 64 + lane;
-          const double wc = wz[0], wsn = wz[64];
-          const D4 cr = D::mfma(wc, pr, none), ci = D::mfma(wc, pi, none);
-          ur[j] += D::mfma(wsn, -mi, cr);
-          ui[j] += D::mfma(wsn, mr, ci);
-        }
+      // this lane's operand row: g2 = +-ga
+      const int ga = 8 * tz + (l16 & 3) + 4 * (lr >> 1), g2 = (lr & 1) ? -ga : ga;
+      const bool live = ga <= G2 && !((lr & 1) && ga == 0);
+      const cpx<T>* row = src + (live ? G2 + g2 : 0);
+#pragma unroll 4
+      for (int s = t; s < ky; s += rt) {
+        bool sine;
+        const int k = 4 * s + q, g = kappa_g(k, G1, &sine);
+        const bool in = live && k <= 2 * G1;
+        const int gi = in ? g : 0;
+        const cpx<double> a = widen(row[(G1 + gi) * e2]), b = widen(row[(G1 - gi) * e2]),
+                          z = mk(0.0, 0.0);
+        S[(tz * ky + s) * 64] = fold(in ? a : z, in && g ? b : z, sine);
       }
     }
+  __syncthreads();
+  if (!mine) return;
+  cpx<T>* dst = B.u + ((size_t)band * n0 + x) * plane + (size_t)sp * rt * ks * 64 + lane;
+  D4 ur[JT], ui[JT];
 #pragma unroll
-    for (int j = 0; j < JT; ++j)
+  for (int j = 0; j < JT; ++j) ur[j] = ui[j] = (D4){0, 0, 0, 0};
+  for (int tz = 0; tz < B.ntz; ++tz) {
+    D4 yr = {0, 0, 0, 0}, yi = yr;
+    const double* w = B.by + (size_t)t * ky * 64 + lane;
+#pragma unroll 2
+    for (int s = 0; s < ky; s += 2) {
+      const bool two = s + 1 < ky;
+      const int s1 = two ? s + 1 : s;
+      const cpx<double> d0 = S[(tz * ky + s) * 64], d1 = S[(tz * ky + s1) * 64];
+      const double w0 = w[s * 64], w1 = w[s1 * 64];
+      yr += mfma2(d0.x, w0, d1.x, w1, two);
+      yi += mfma2(d0.y, w0, d1.y, w1, two);
+    }
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (4 * j + r < ks)
-          dst[(size_t)(t * ks + 4 * j + r) * 64] = mk((T)ur[j][r], (T)ui[j][r]);
+    for (int h = 0; h < 2; ++h) {
+      if (8 * tz + 4 * h > G2) break;
+      const double pr = yr[2 * h] + yr[2 * h + 1], pi = yi[2 * h] + yi[2 * h + 1];
+      const double mr = yr[2 * h] - yr[2 * h + 1], mi = yi[2 * h] - yi[2 * h + 1];
+      const D4 none = {0, 0, 0, 0};
+#pragma unroll
+      for (int j = 0; j < JT; ++j) {
+        const double* wz = B.bz + ((size_t)(j * B.ntz + tz) * 4 + 2 * h) * 64 + lane;
+        const double wc = wz[0], wsn = wz[64];
+        const D4 cr = D::mfma(wc, pr, none), ci = D::mfma(wc, pi, none);
+        ur[j] += D::mfma(wsn, -mi, cr);
+        ui[j] += D::mfma(wsn, mr, ci);
+      }
+    }
   }
+#pragma unroll
+  for (int j = 0; j < JT; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (4 * j + r < ks)
+        dst[(size_t)(t * ks + 4 * j + r) * 64] = mk((T)ur[j][r], (T)ui[j][r]);
 }
 
 // ---------------------------------------------------------------- pair planes
@@ -253,15 +254,16 @@ __global__ void __launch_bounds__(256) k_mm_band_plane(BandSet<T> bv, BandSet<T>
 // plane per row tile of |g1|); the valence plane is read from L2 once per four pairs.
 // 12,800 pairs of the Si-like case in double: 485 us, 25.5 TFLOP/s of products without
 // padding (4.9 ms for both halves of the FFT planes on the vector ALU).
-template <typename T, int NS, int RT, int KS>
-constexpr int mm_waves() {
-  // conduction entries, two result tiles per row tile and the output tiles: two
-  // wavefronts per SIMD while they leave room in 256 registers
-  return (NS * RT * KS * 2 + 8 * RT + 16) * (int)sizeof(T) / 4 <= 160 ? 2 : 1;
+// Registers of a band's entries, the result and output tiles and the coefficients, in
+// words: up to these counts the kernels take at most 256 registers, two wavefronts per
+// SIMD, without scratch memory (one spinor component keeps more loads ahead).
+__host__ __device__ constexpr bool mm_band_fits(bool dbl, int ns, int rt, int ks) {
+  return rt <= 3 && ks <= 12 &&
+         (2 * ns * rt * ks + 8 * rt + 16 + ks) * (dbl ? 2 : 1) <= (ns == 2 ? 172 : 160);
 }
 
 template <typename T, int NS, int RT, int KS>
-__global__ void __launch_bounds__(256, (mm_waves<T, NS, RT, KS>())) k_mm_pair(
+__global__ void __launch_bounds__(256, 2) k_mm_pair(
     const cpx<T>* __restrict__ uv, const cpx<T>* __restrict__ uc, size_t plane, int nvt, int nct,
     int nvs, int n0, int n1, int ncz, int nry, const T* __restrict__ zc, const T* __restrict__ yc,
     const int* __restrict__ qpos, int G1, int G2, int nq4, cpx<T>* __restrict__ t2) {
@@ -336,6 +338,9 @@ __global__ void __launch_bounds__(256, (mm_waves<T, NS, RT, KS>())) k_mm_pair(
       const int t = ch % RT;
       xr[t] = ch < RT ? pr : xr[t] + pr;
       xi[t] = ch < RT ? pi : xi[t] + pi;
+      // Here and not at the end, where every chunk's result would be held until then: of 36
+      // rows in single precision 240 -> 212 us, of 32 and 16 rows up to 2% slower.
+      if constexpr (RT == 3) asm volatile("" : "+v"(xr[t]), "+v"(xi[t]));
     };
     read(0);
 #pragma unroll
@@ -409,6 +414,249 @@ __global__ void __launch_bounds__(256, (mm_waves<T, NS, RT, KS>())) k_mm_pair(
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   }
+}
+
+// ---------------------------------------------------------------- pair planes by rows
+// The same for planes whose conduction entries do not fit one wavefront's registers
+// (mm_band_fits): rt wavefronts share a band, each with the entries of 16 rows.  A
+// wavefront forms its rows' products once for all NZ column tiles and contracts them over
+// the entries.  Then, with at least one output tile for each wavefront (EX), the results
+// X are exchanged through LDS and the wavefronts take the tiles in turn, K over all rows;
+// with fewer, every wavefront contracts its own rows for each tile, and the rt partial
+// results go through LDS (two buffers, one barrier per tile) and are added while the next
+// tile's products run.  The valence entries come straight from L2 in fragment order, D K
+// steps ahead.
+//
+// Bound: issue of the matrix cores and of the products on the same ALUs (44-55% of the
+// cycles are the matrix cores'), with three wavefronts of a 48-row plane on four SIMDs.
+// 16 x 64 pairs in double, pair planes: 48 points per axis 2484 -> 781 us, 40 points 1374
+// -> 566 us (with a whole band per wavefront, 130-930 spilled bytes), 52 x 52 x 34 points
+// 1031 -> 326 us (general transforms).  31 points, 16 x 128 pairs: 579 -> 441 us.
+template <typename T, int NS, int KS>
+constexpr int mm_rows_depth() {
+  // K steps in flight: a divisor of KS, so that slots keep their place from band to band
+  return KS == 4 || KS == 6 ? KS : KS == 8 || KS == 12 || KS == 16 ? 4 : KS / 2;
+}
+constexpr int kPartPitch = 66;  // entries per register of a partial tile in LDS
+
+template <typename T, int NS, int KS, int NZ, bool EX>
+__global__ void __launch_bounds__(256, 2) k_mm_pair_rows(
+    const cpx<T>* __restrict__ uv, const cpx<T>* __restrict__ uc, size_t plane, int nvt, int nct,
+    int nvs, int n0, int n1, int rt, int ct0, int nry, const T* __restrict__ zc,
+    const T* __restrict__ yc, const int* __restrict__ qpos, int G1, int G2, int nq4,
+    cpx<T>* __restrict__ t2) {
+  using V = typename MmType<T>::v4;
+  constexpr int D = mm_rows_depth<T, NS, KS>(), NCH = KS / 2;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), t = wave % rt, b = wave / rt;
+  const int nb = (blockDim.x >> 6) / rt, ncg = (nct + nb - 1) / nb;
+  const long long lin = xcd_linear(blockIdx.x, (long long)n0 * nvs * ncg);
+  if (lin < 0) return;
+  const int cg = (int)(lin % ncg), vx = (int)(lin / ncg), x = vx / nvs;
+  const int vb = (int)((long long)nvt * (vx % nvs) / nvs),
+            ve = (int)((long long)nvt * (vx % nvs + 1) / nvs);
+  T* Z = reinterpret_cast<T*>(smem_raw);
+  T* Y = Z + NZ * KS * 64;
+  int* Qp = reinterpret_cast<int*>(Y + (size_t)nry * rt * 256);
+  // partial tiles [2][rt][4][kPartPitch], or the results X [rt][NZ][4][64]
+  cpx<T>* Ps = reinterpret_cast<cpx<T>*>(Qp + nry * NZ * 64) +
+               (size_t)b * rt * (EX ? NZ * 256 : 8 * kPartPitch);
+  const int cl = cg * nb + b;
+  const bool mine = cl < nct;
+  // valence entries of this wavefront's rows, D K steps ahead of their use
+  // (uniform base and one lane offset: the steps' addresses take no vector registers)
+  const cpx<T>* src = uv + ((size_t)vb * n0 + x) * plane + (size_t)t * KS * 64;
+  const size_t sps = (size_t)rt * KS * 64;  // from spinor component to component
+  cpx<T> d[D][NS], cr[NS][KS];
+#pragma unroll
+  for (int k = 0; k < D; ++k)
+#pragma unroll
+    for (int s = 0; s < NS; ++s) d[k][s] = (src + s * sps + k * 64)[lane];
+  {
+    const cpx<T>* c = uc + ((size_t)(mine ? cl : nct - 1) * n0 + x) * plane + (size_t)t * KS * 64;
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int k = 0; k < KS; ++k) cr[s][k] = (c + s * sps + k * 64)[lane];
+  }
+  for (int i = tid; i < NZ * KS * 64; i += blockDim.x) Z[i] = zc[(size_t)ct0 * KS * 64 + i];
+  for (int i = tid; i < nry * rt * 256; i += blockDim.x) Y[i] = yc[i];
+  for (int i = tid; i < nry * NZ * 64; i += blockDim.x) {
+    const int g1 = i / (NZ * 8), g2 = ct0 * 8 + i % (NZ * 8);
+    const int qd = g1 <= G1 && g2 <= G2 ? qpos[g1 * (G2 + 1) + g2] : -1;
+    Qp[i] = qd < 0 ? -1 : 4 * qd;
+  }
+  __syncthreads();
+  // the sum of a tile's partials, stored as whole quads
+  int par = 0, last = -1;
+  cpx<T>* lout = t2;
+  auto flush = [&]() {
+    if (last < 0) return;
+    const cpx<T>* P = Ps + (size_t)(par ^ 1) * rt * 4 * kPartPitch;
+    for (int e = t * 64 + lane; e < 256; e += 64 * rt) {
+      const int slot = e & 3, g2i = (e >> 2) & 7, g1i = e >> 5;
+      const int at = (2 * (g1i >> 2) + (slot >> 1)) * kPartPitch + (g1i & 3) * 16 + 2 * g2i + (slot & 1);
+      const int qd = mine ? Qp[last + g1i * NZ * 8 + g2i] : -1;
+      cpx<T> v = P[at];
+      for (int w = 1; w < rt; ++w) v = v + P[(size_t)w * 4 * kPartPitch + at];
+      if (qd >= 0) lout[(unsigned)(qd + slot)] = v;
+    }
+  };
+  for (int vl = vb; vl < ve; ++vl) {
+    const cpx<T>* nsrc = vl + 1 < ve ? src + (size_t)n0 * plane : src;
+    V xr[NZ], xi[NZ], pr, pi;
+    int zl = lane;
+    asm volatile("" : "+v"(zl));  // the coefficients stay in LDS
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      T re[2], im[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int k = 2 * ch + i;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const cpx<T> v = d[k % D][s], c = cr[s][k];
+          re[i] = s ? fma(v.x, c.x, fma(v.y, c.y, re[i])) : fma(v.x, c.x, v.y * c.y);
+          im[i] = s ? fma(v.x, c.y, fma(-v.y, c.x, im[i])) : fma(v.x, c.y, -(v.y * c.x));
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int k = 2 * ch + i;
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+          d[k % D][s] = k + D < KS ? (src + s * sps + (k + D) * 64)[lane]
+                                   : (nsrc + s * sps + (k + D - KS) * 64)[lane];
+      }
+      T z[NZ][2];
+#pragma unroll
+      for (int c = 0; c < NZ; ++c)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) z[c][i] = Z[(c * KS + 2 * ch + i) * 64 + zl];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < NZ; ++c) {
+        V ar = {0, 0, 0, 0}, ai = {0, 0, 0, 0};
+        ar = MmType<T>::mfma(re[0], z[c][0], ar);
+        ai = MmType<T>::mfma(im[0], z[c][0], ai);
+        ar = MmType<T>::mfma(re[1], z[c][1], ar);
+        ai = MmType<T>::mfma(im[1], z[c][1], ai);
+        // the result before this one
+        const int it = ch * NZ + c - 1, pc = (it + NZ) % NZ;
+        if (it >= 0) {
+          xr[pc] = it < NZ ? pr : xr[pc] + pr;
+          xi[pc] = it < NZ ? pi : xi[pc] + pi;
+          // here and not at the end, where every chunk's result would be held until then
+          asm volatile("" : "+v"(xr[pc]), "+v"(xi[pc]));
+        }
+        pr = ar;
+        pi = ai;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    xr[NZ - 1] = NCH == 1 ? pr : xr[NZ - 1] + pr;
+    xi[NZ - 1] = NCH == 1 ? pi : xi[NZ - 1] + pi;
+    cpx<T>* out = t2 + (((size_t)cl * nvt + vl) * n0 + x) * (size_t)nq4 * 4;
+    // bare barriers: a fence would wait for the stores and loads in flight
+    auto barrier = [] {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
+    if constexpr (EX) {
+      barrier();  // the last band's X has been read
+#pragma unroll
+      for (int c = 0; c < NZ; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Ps[((t * NZ + c) * 4 + r) * 64 + lane] = mk(xr[c][r], xi[c][r]);
+      barrier();
+      for (int i = t; i < nry * NZ; i += rt) {
+        const int ty = i / NZ, c = i - ty * NZ;
+        const cpx<T>* X = Ps + c * 256 + lane;
+        const T* y = Y + (size_t)ty * rt * 256 + lane;
+        cpx<T> xf[4];
+        T yf[4];
+        auto fetch = [&](int w) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            xf[r] = X[(size_t)w * NZ * 256 + r * 64];
+            yf[r] = y[w * 256 + r * 64];
+          }
+        };
+        fetch(0);
+        V o_r = {0, 0, 0, 0}, o_i = {0, 0, 0, 0};
+        for (int w = 0; w < rt; ++w) {
+          cpx<T> xc[4];
+          T yc4[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            xc[r] = xf[r];
+            yc4[r] = yf[r];
+          }
+          if (w + 1 < rt) fetch(w + 1);
+          V a_r = {0, 0, 0, 0}, a_i = {0, 0, 0, 0}, b_r = {0, 0, 0, 0}, b_i = {0, 0, 0, 0};
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            a_r = MmType<T>::mfma(yc4[r], xc[r].x, a_r);
+            a_i = MmType<T>::mfma(yc4[r], xc[r].y, a_i);
+          }
+          if (16 * w + 8 < n1) {  // rows past n1 have zero coefficients
+#pragma unroll
+            for (int r = 2; r < 4; ++r) {
+              b_r = MmType<T>::mfma(yc4[r], xc[r].x, b_r);
+              b_i = MmType<T>::mfma(yc4[r], xc[r].y, b_i);
+            }
+          }
+          o_r = (o_r + a_r) + b_r;
+          o_i = (o_i + a_i) + b_i;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int qd = mine ? Qp[(ty * 8 + 4 * h + (lane >> 4)) * NZ * 8 + c * 8 + ((lane & 15) >> 1)] : -1;
+          if (qd >= 0) {
+            out[(unsigned)(qd + (lane & 1))] = mk(o_r[2 * h], o_i[2 * h]);
+            out[(unsigned)(qd + 2 + (lane & 1))] = mk(o_r[2 * h + 1], o_i[2 * h + 1]);
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < NZ; ++c)
+        for (int ty = 0; ty < nry; ++ty) {
+          const T* y = Y + (size_t)(ty * rt + t) * 256 + lane;
+          V o_r = {0, 0, 0, 0}, o_i = {0, 0, 0, 0};
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            const T a = y[r * 64];
+            o_r = MmType<T>::mfma(a, xr[c][r], o_r);
+            o_i = MmType<T>::mfma(a, xi[c][r], o_i);
+          }
+          if (16 * t + 8 < n1) {  // rows past n1 have zero coefficients
+            V b_r = {0, 0, 0, 0}, b_i = {0, 0, 0, 0};
+#pragma unroll
+            for (int r = 2; r < 4; ++r) {
+              const T a = y[r * 64];
+              b_r = MmType<T>::mfma(a, xr[c][r], b_r);
+              b_i = MmType<T>::mfma(a, xi[c][r], b_i);
+            }
+            o_r += b_r;
+            o_i += b_i;
+          }
+          flush();
+          cpx<T>* P = Ps + (size_t)(par * rt + t) * 4 * kPartPitch + lane;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) P[r * kPartPitch] = mk(o_r[r], o_i[r]);
+          last = ty * 8 * NZ * 8 + c * 8;
+          lout = out;
+          par ^= 1;
+          barrier();  // this tile's partials are written, and the last tile's have been read
+        }
+    }
+    src = nsrc;
+  }
+  if constexpr (!EX) flush();
 }
 
 // ---------------------------------------------------------------- axis 0 and scatter
@@ -614,20 +862,36 @@ void put_band(Blob& b, const MmTables& t, const int* g, MmTables::Band* o) {
         }
 }
 
-// K steps and row tiles the pair kernel is built for
-constexpr int kKs[] = {2, 3, 4, 5, 6, 7, 8, 10, 12};
-constexpr int kMaxRt = 3, kMaxNx = 4;
+// K steps and row tiles the pair kernels are built for
+constexpr int kKs[] = {2, 3, 4, 5, 6, 7, 8, 10, 12}, kKsRows[] = {4, 6, 8, 10, 12, 14, 16};
+constexpr int kMaxRt = 4, kMaxNx = 4, kMaxNz = 3;
 constexpr size_t kLds = 160 * 1024;
 
 size_t pair_lds(bool dbl, int ns, int rt, int ks, int nry) {
   const size_t ch = ((size_t)ns * rt * ks * (dbl ? 1024 : 512) + 1023) / 1024;
   return 2 * ch * 1024 + (size_t)nry * rt * 4 * 64 * (dbl ? 8 : 4) + (size_t)nry * 64 * 4;
 }
+// bands of a workgroup of the rows kernel, whether it exchanges X, and its LDS
+int rows_bands(int rt) { return rt == 1 ? 4 : rt == 2 ? 2 : 1; }
+bool rows_exchange(int rt, int nz, int nry) { return nry * nz >= rt; }
+size_t rows_lds(bool dbl, int rt, int ks, int nz, int nry) {
+  const size_t w = dbl ? 8 : 4;
+  return ((size_t)nz * ks * 64 + (size_t)nry * rt * 256) * w + (size_t)nry * nz * 256 +
+         (size_t)rows_bands(rt) * rt * (rows_exchange(rt, nz, nry) ? nz * 256 : 8 * kPartPitch) *
+             2 * w;
+}
 size_t pairx_lds(bool dbl, int nx, int kx) {
   return (size_t)std::min(nx, kMaxNx) * kx * 64 * (dbl ? 8 : 4);
 }
-// wavefronts per workgroup of the band transforms: `k` KiB of folded entries each
-int band_waves(int k) { return std::max(1, std::min(4, 128 / k)); }
+// wavefronts (or planes) per workgroup of the band transforms, at most `most`, with `k` KiB
+// of folded entries each: fewer where that puts half as many again on a CU (of 16)
+int band_waves(int k, int most) {
+  auto on_cu = [k](int w) { return std::min(16, 160 / (w * k) * w); };
+  int best = most;
+  for (int w = most - 1; w >= 1; --w)
+    if (2 * on_cu(w) >= 3 * on_cu(best)) best = w;
+  return best;
+}
 
 // Intermediate and band fields of a chunk of conduction bands.  Chunks that stay in the
 // 256 MB last-level cache were slower: the Si-like case took 1.22 ms in chunks of 96 MB,
@@ -679,8 +943,8 @@ BandSet<T> band_set(const MmTables& t, bool val, int nb, int ng, const cpx<T>* c
 // coefficients -> fields in fragment order, valence and conduction in one launch each
 template <typename T>
 gw_status run_bands(gw_ctx* c, const MmTables& t, const BandSet<T>& v, const BandSet<T>& k) {
-  const int kx = std::max(v.kx, k.kx), nw = band_waves(kx);
-  const int ky = std::max(v.ky * v.ntz, k.ky * k.ntz), nwp = band_waves(ky);
+  const int kx = std::max(v.kx, k.kx), nw = band_waves(kx, 4);
+  const int ky = std::max(v.ky * v.ntz, k.ky * k.ntz), nwp = band_waves(ky, 4 / t.rt);
   const int ncol = std::max(t.bv.ncol, t.bc.ncol), nbs = v.nbs + k.nbs;
   const size_t lx = (size_t)nw * kx * 1024, lp = (size_t)nwp * ky * 1024;
   {
@@ -691,14 +955,14 @@ gw_status run_bands(gw_ctx* c, const MmTables& t, const BandSet<T>& v, const Ban
     GW_CHECK_LAUNCH(c, "k_mm_band_x");
   }
   ProfScope ps(c, "band_plane");
-  const dim3 gr((unsigned)(((long long)nbs * t.n[0] + nwp - 1) / nwp)), bl(64 * nwp);
+  const dim3 gr((unsigned)(((long long)nbs * t.n[0] + nwp - 1) / nwp)), bl(64 * nwp * t.rt);
 #define GW_MM_BP(J)                                                                             \
   if (t.jt == J) {                                                                              \
     if (!c->capturing) GW_HIP(c, allow(c, k_mm_band_plane<T, J>, lp));                          \
     hipLaunchKernelGGL((k_mm_band_plane<T, J>), gr, bl, lp, c->stream, v, k, ky, t.n[0],         \
                        t.nspinor, t.rt, t.ks, t.plane);                                         \
   }
-  GW_MM_BP(1) GW_MM_BP(2) GW_MM_BP(3)
+  GW_MM_BP(1) GW_MM_BP(2) GW_MM_BP(3) GW_MM_BP(4)
 #undef GW_MM_BP
   GW_CHECK_LAUNCH(c, "k_mm_band_plane");
   return GW_OK;
@@ -723,26 +987,82 @@ gw_status launch_pair(gw_ctx* c, const MmTables& t, const cpx<T>* uv, const cpx<
   return GW_OK;
 }
 
+template <typename T, int NS, int KS, int NZ>
+gw_status launch_rows(gw_ctx* c, const MmTables& t, const cpx<T>* uv, const cpx<T>* uc, int nv,
+                      int nct, int ct0, cpx<T>* t2) {
+  auto* k = rows_exchange(t.rt, NZ, t.nry) ? &k_mm_pair_rows<T, NS, KS, NZ, true>
+                                           : &k_mm_pair_rows<T, NS, KS, NZ, false>;
+  const size_t lds = rows_lds(sizeof(T) == 8, t.rt, KS, NZ, t.nry);
+  if (!c->capturing) GW_HIP(c, allow(c, k, lds));
+  const int nb = rows_bands(t.rt);
+  const long long base = (long long)t.n[0] * ((nct + nb - 1) / nb);
+  const int nvs = (int)std::max<long long>(1, std::min<long long>(nv / 6, (kPairGroups - 1) / base + 1));
+  const long long tot = base * nvs;
+  hipLaunchKernelGGL(k, dim3((unsigned)((tot + kXcd - 1) / kXcd * kXcd)), dim3(64 * t.rt * nb), lds,
+                     c->stream, uv, uc, t.plane, nv, nct, nvs, t.n[0], t.n[1], t.rt, ct0, t.nry,
+                     reinterpret_cast<const T*>(t.grid->p + t.o_zc),
+                     reinterpret_cast<const T*>(t.grid->p + t.o_yc),
+                     reinterpret_cast<const int*>(t.eps->dev.p + t.eps->o_qpos), t.ge[1], t.ge[2],
+                     t.eps->nq4, t2);
+  GW_CHECK_LAUNCH(c, "k_mm_pair_rows");
+  return GW_OK;
+}
+
+// column tiles in launches of up to kMaxNz, evenly
+template <typename T, int NS, int KS>
+gw_status run_rows(gw_ctx* c, const MmTables& t, const cpx<T>* uv, const cpx<T>* uc, int nv,
+                   int nct, cpx<T>* t2) {
+  const int parts = (t.ncz + kMaxNz - 1) / kMaxNz;
+  for (int i = 0; i < parts; ++i) {
+    const int c0 = t.ncz * i / parts, nz = t.ncz * (i + 1) / parts - c0;
+    gw_status st = nz == 1   ? launch_rows<T, NS, KS, 1>(c, t, uv, uc, nv, nct, c0, t2)
+                   : nz == 2 ? launch_rows<T, NS, KS, 2>(c, t, uv, uc, nv, nct, c0, t2)
+                             : launch_rows<T, NS, KS, 3>(c, t, uv, uc, nv, nct, c0, t2);
+    if (st != GW_OK) return st;
+  }
+  return GW_OK;
+}
+
+template <typename T, int NS, int RT, int KS>
+gw_status band_or_rows(gw_ctx* c, const MmTables& t, const cpx<T>* uv, const cpx<T>* uc, int nv,
+                       int nct, cpx<T>* t2) {
+  if constexpr (mm_band_fits(sizeof(T) == 8, NS, RT, KS))
+    return launch_pair<T, NS, RT, KS>(c, t, uv, uc, nv, nct, t2);
+  return fail(c, GW_EUNSUPPORTED, "no pair kernel for %d row tiles, %d K steps", RT, KS);
+}
+
 template <typename T, int NS, int RT>
 gw_status pick_ks(gw_ctx* c, const MmTables& t, const cpx<T>* uv, const cpx<T>* uc, int nv, int nct,
                   cpx<T>* t2) {
   switch (t.ks) {
-    case 2: return launch_pair<T, NS, RT, 2>(c, t, uv, uc, nv, nct, t2);
-    case 3: return launch_pair<T, NS, RT, 3>(c, t, uv, uc, nv, nct, t2);
-    case 4: return launch_pair<T, NS, RT, 4>(c, t, uv, uc, nv, nct, t2);
-    case 5: return launch_pair<T, NS, RT, 5>(c, t, uv, uc, nv, nct, t2);
-    case 6: return launch_pair<T, NS, RT, 6>(c, t, uv, uc, nv, nct, t2);
-    case 7: return launch_pair<T, NS, RT, 7>(c, t, uv, uc, nv, nct, t2);
-    case 8: return launch_pair<T, NS, RT, 8>(c, t, uv, uc, nv, nct, t2);
-    case 10: return launch_pair<T, NS, RT, 10>(c, t, uv, uc, nv, nct, t2);
-    case 12: return launch_pair<T, NS, RT, 12>(c, t, uv, uc, nv, nct, t2);
+    case 2: return band_or_rows<T, NS, RT, 2>(c, t, uv, uc, nv, nct, t2);
+    case 3: return band_or_rows<T, NS, RT, 3>(c, t, uv, uc, nv, nct, t2);
+    case 4: return band_or_rows<T, NS, RT, 4>(c, t, uv, uc, nv, nct, t2);
+    case 5: return band_or_rows<T, NS, RT, 5>(c, t, uv, uc, nv, nct, t2);
+    case 6: return band_or_rows<T, NS, RT, 6>(c, t, uv, uc, nv, nct, t2);
+    case 7: return band_or_rows<T, NS, RT, 7>(c, t, uv, uc, nv, nct, t2);
+    case 8: return band_or_rows<T, NS, RT, 8>(c, t, uv, uc, nv, nct, t2);
+    case 10: return band_or_rows<T, NS, RT, 10>(c, t, uv, uc, nv, nct, t2);
+    case 12: return band_or_rows<T, NS, RT, 12>(c, t, uv, uc, nv, nct, t2);
   }
   return fail(c, GW_EUNSUPPORTED, "no pair kernel for %d K steps", t.ks);
 }
 
 template <typename T, int NS>
-gw_status pick_rt(gw_ctx* c, const MmTables& t, const cpx<T>* uv, const cpx<T>* uc, int nv, int nct,
-                  cpx<T>* t2) {
+gw_status run_pairs(gw_ctx* c, const MmTables& t, const cpx<T>* uv, const cpx<T>* uc, int nv,
+                    int nct, cpx<T>* t2) {
+  if (t.rows) {
+    switch (t.ks) {
+      case 4: return run_rows<T, NS, 4>(c, t, uv, uc, nv, nct, t2);
+      case 6: return run_rows<T, NS, 6>(c, t, uv, uc, nv, nct, t2);
+      case 8: return run_rows<T, NS, 8>(c, t, uv, uc, nv, nct, t2);
+      case 10: return run_rows<T, NS, 10>(c, t, uv, uc, nv, nct, t2);
+      case 12: return run_rows<T, NS, 12>(c, t, uv, uc, nv, nct, t2);
+      case 14: return run_rows<T, NS, 14>(c, t, uv, uc, nv, nct, t2);
+      case 16: return run_rows<T, NS, 16>(c, t, uv, uc, nv, nct, t2);
+    }
+    return fail(c, GW_EUNSUPPORTED, "no pair kernel for %d K steps", t.ks);
+  }
   if (t.rt == 1) return pick_ks<T, NS, 1>(c, t, uv, uc, nv, nct, t2);
   if (t.rt == 2) return pick_ks<T, NS, 2>(c, t, uv, uc, nv, nct, t2);
   return pick_ks<T, NS, 3>(c, t, uv, uc, nv, nct, t2);
@@ -768,8 +1088,8 @@ gw_status run_mtxel(gw_ctx* c, const MmTables& t, int nv, int ngv, const cpx<T>*
     if (st != GW_OK) return st;
     {
       ProfScope ps(c, "pair_plane");
-      st = t.nspinor == 2 ? pick_rt<T, 2>(c, t, uv, uc, nv, nct, t2)
-                          : pick_rt<T, 1>(c, t, uv, uc, nv, nct, t2);
+      st = t.nspinor == 2 ? run_pairs<T, 2>(c, t, uv, uc, nv, nct, t2)
+                          : run_pairs<T, 1>(c, t, uv, uc, nv, nct, t2);
       if (st != GW_OK) return st;
     }
     ProfScope ps(c, "pair_xpass");
@@ -840,11 +1160,18 @@ static gw_status grid_tables(gw_ctx* c, const SphereMap* sv, const SphereMap* sc
       n[a] = sv->gmax[p[a]] + sc->gmax[p[a]] + g[a] + 1;
     }
     const int rt = (n[1] + 15) / 16, need = (n[2] + 3) / 4;
+    const int ncz = g[2] / 8 + 1, nry = g[1] / 8 + 1, nx = g[0] / 8 + 1, kx = (n[0] + 3) / 4;
     int ks = 0;
     for (int k : kKs)
       if (!ks && k >= need) ks = k;
-    const int ncz = g[2] / 8 + 1, nry = g[1] / 8 + 1, nx = g[0] / 8 + 1, kx = (n[0] + 3) / 4;
-    if (rt > kMaxRt || !ks || pair_lds(dbl, nspinor, rt, ks, nry) > kLds ||
+    const bool rows = !ks || !mm_band_fits(dbl, nspinor, rt, ks) ||
+                      pair_lds(dbl, nspinor, rt, ks, nry) > kLds;
+    if (rows) {
+      ks = 0;
+      for (int k : kKsRows)
+        if (!ks && k >= need) ks = k;
+    }
+    if (rt > kMaxRt || !ks || (rows && rows_lds(dbl, rt, ks, std::min(ncz, kMaxNz), nry) > kLds) ||
         pairx_lds(dbl, nx, kx) > kLds ||
         (size_t)fold_steps(std::max(sv->gmax[p[0]], sc->gmax[p[0]])) * 1024 > kLds ||
         (size_t)std::max(fold_steps(sv->gmax[p[1]]) * (sv->gmax[p[2]] / 8 + 1),
@@ -852,12 +1179,16 @@ static gw_status grid_tables(gw_ctx* c, const SphereMap* sv, const SphereMap* sc
       continue;
     // 16 x 16 x 4 products per pair over 1,024 SIMDs; the intermediate written and
     // read at about 1.6 bytes per SIMD and cycle
-    const double mm = n[0] * (double)ncz * (2.0 * rt * ks + 2.0 * nry * ((n[1] + 3) / 4)) * cyc;
+    // (the rows kernel keeps the matrix cores busy for two thirds of the time that the
+    // other does: 64 x 21 x 22 points in single precision 136 us, 21 x 64 x 22 by rows 180)
+    const double mm = n[0] * (double)ncz * (2.0 * rt * ks + 2.0 * nry * ((n[1] + 3) / 4)) * cyc *
+                      (rows ? 1.4 : 1.0);
     const double tr = n[0] * (g[1] + 1.0) * (g[2] + 1.0) * 4.0 * 2.0 * el / 1.6;
     if (mm + tr < best) {
       best = mm + tr;
       t->rt = rt;
       t->ks = ks;
+      t->rows = rows;
       t->jt = (ks + 3) / 4;
       t->ncz = ncz;
       t->nry = nry;
