@@ -667,8 +667,12 @@ gw_status gj_steps(gw_ctx* c, M ms, int nmat, int nmax, const char* sdiag, const
       GW_CHECK_LAUNCH(c, "k_gj_panel");
     }
     ProfScope ps(c, supd);
-    // operands staged in LDS from N = 2048 (N = 4000, one matrix: 8.8 vs 9.7 ms per
-    // inversion); below, fragments straight from L2 (nine of N = 1000: 1.68 vs 1.84 ms)
+    // Operands staged in LDS (each fetched once per workgroup) pay where the matrices pass
+    // the last-level cache, or every block is updated, which the host does not know.  One
+    // matrix, inversion with fragments straight from L2 / through LDS, half the blocks:
+    // 2047 rows 2.50 / 2.65 ms, 3000 3.82 / 4.07, 4000 6.60 / 6.51, 5000 11.7 / 10.3, three
+    // of 3000 8.67 / 6.94; every block: 2047 rows 2.70 / 2.82, 3000 5.23 / 4.94, 4000
+    // 12.5 / 10.2.  At 2048 half the blocks lose at most 7%, every block at most 4%.
     auto* update = nmax >= 2048 ? &k_gj_update<true, M> : &k_gj_update<false, M>;
     hipLaunchKernelGGL(update, dim3(gj_update_grid(nmat, nmax)), dim3(256), 0, c->stream, ms, nmat,
                        nmax, k, s);
