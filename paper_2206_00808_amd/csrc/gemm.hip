@@ -170,26 +170,6 @@ __global__ void __launch_bounds__(256) k_bf16_split(const cpx<float>* __restrict
   }
 }
 
-// Range s of the pair blocks of frequency f, from the pre-split operands.
-template <int WM>
-__global__ void __launch_bounds__(64 * WM * WM) k_chi0_bf16s(const unsigned short* __restrict__ X,
-                                                             int Pb, int neps,
-                                                             cpx<double>* __restrict__ chi, int nt,
-                                                             int skip_head, int pbc,
-                                                             cpx<double>* __restrict__ part) {
-  int ti, tj;
-  tri_tile(blockIdx.x, nt, &ti, &tj);
-  const int f = blockIdx.y, s = blockIdx.z, nf = gridDim.y;
-  const int pb0 = s * pbc, npb = min(Pb, pb0 + pbc) - pb0;
-  const size_t nn = (size_t)neps * neps, osz = (size_t)Pb * 4 * neps * BK;
-  const unsigned short* XB = X + (size_t)(1 + f) * osz;
-  if (s == 0)
-    chi0_bf16s_tile<WM>(X, XB, pb0, npb, neps, chi + (size_t)f * nn, ti, tj, skip_head, false);
-  else
-    chi0_bf16s_tile<WM>(X, XB, pb0, npb, neps, part + ((size_t)(s - 1) * nf + f) * nn, ti, tj,
-                        skip_head, true);
-}
-
 // The 128 x 128 tiles: grid = the tile order table x ranges x frequencies,
 // renumbered per XCD so that each XCD takes a contiguous run of the order, in
 // which consecutive tiles form 4 x 8 blocks of the tile grid (the concurrent
@@ -326,7 +306,6 @@ int chi0_split(gw_ctx* c, int P, int neps, int nfreq, gw_prec prec, gw_dtype dt)
   }
   return best;
 }
-
 
 static gw_status chi0_reduce(gw_ctx* c, int neps, int nfreq, double* chi0, int split,
                              const double* part) {
