@@ -20,7 +20,7 @@
 // formed once at the end.
 // Bound: FP64 vector instructions (the ALUs issue 96% of the time).  An element and
 // energy of an empty n'' takes 9 of them, and its share of M M* with three energies 2
-// more: 11.1 of 11.7 issued.  8 bands, 816 states, 3 energies, 1000 vectors: 8.9 ms;
+// more: 11.1 of 11.7 issued.  8 bands, 816 states, 3 energies, 1000 vectors: 8.5 ms;
 // 10.9 ms with conj(M(G)) A summed over the thread's rows and multiplied by v M(G') for
 // every n'' (14.5 FP64 instructions).  Two wavefronts per SIMD, because at three the
 // accumulators move between registers (34 of 190 instructions; 9.9 ms).

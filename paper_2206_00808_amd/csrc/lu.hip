@@ -127,8 +127,9 @@ __global__ void __launch_bounds__(1024) k_lu_panel(cpx<double>* __restrict__ A, 
 // Bound: latency of the columns' chains; one workgroup per matrix.  A 32-column panel
 // of up to 768 rows takes 101 us, of up to 512 rows 72 and of up to 256 rows 42 (mean
 // over a 613-row factorisation; 265 us with the columns in global memory, two passes
-// over them and 12 barriers per column).  eps^-1 of five 613-row matrices: 8.27 ms
-// before, 3.58 ms with these panels and the four-lane triangular solves.
+// over them and 12 barriers per column).  eps^-1 of four 613-row matrices by LU alone:
+// 7.73 ms before, 2.89 ms with these panels (5.36 -> 1.37 ms) and the four-lane
+// triangular solves (1.50 -> 0.83 ms).
 constexpr int SW = 8;           // sub-panel width
 constexpr int kPanelT = 256;    // threads: one wavefront per SIMD, up to 12 rows each
 
