@@ -18,7 +18,7 @@
 // thread) and streams every n'' past it.  A factors out of the sum over n'': each
 // element and energy accumulates S = sum conj(M(G)) M(G') / (d - wt), and A v S is
 // formed once at the end.
-// Bound: FP64 vector instructions (the ALUs issue 96% of the time).  An element and
+// Bound: FP64 vector instructions (the ALUs issue 87% of the time).  An element and
 // energy of an empty n'' takes 9 of them, and its share of M M* with three energies 2
 // more: 11.1 of 11.7 issued.  8 bands, 816 states, 3 energies, 1000 vectors: 8.5 ms;
 // 10.9 ms with conj(M(G)) A summed over the thread's rows and multiplied by v M(G') for
